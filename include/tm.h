@@ -103,8 +103,9 @@ typedef struct {
                              (4^4 where it divides dims, else 2 or 1 per axis);
                              tm_sap_smooth always tiles by its block_dims */
     unsigned long long gauge_tag; /* 0: rebuild the gauge copy every call; else cache key (see above) */
-    int sys_tile;         /* SAP: systems per workgroup (0 = all systems of the call in one workgroup,
-                             so links and clover are read once per half-sweep) */
+    int sys_tile;         /* SAP: systems per workgroup (0 = the library's choice: all systems of the call
+                             in one workgroup, so links and clover are read once per half-sweep, where
+                             the blocks fill the device, else split over several; same results) */
     int sap_eo;           /* SAP block solves (section 2.5): 0 = MR on D_BB; 1 = even-odd
                              preconditioned: MR on the odd-site Schur complement
                              D_oo - D_oe D_ee^-1 D_eo (parity of t+z+y+x), e_e recovered after.
@@ -226,7 +227,7 @@ typedef struct {
     long long sap_sys_cycles;           /* SAP cycles times the systems they carried */
     int group;                          /* systems solved together (after fitting device memory) */
     int block_dims[4];                  /* Schwarz block shape the smoother used */
-    int sys_tile;                       /* SAP systems per workgroup used (0 = all of a group) */
+    int sys_tile;                       /* SAP systems per workgroup asked for or tuned (0 = the library's choice) */
 } tm_solve_report;
 
 /*

@@ -368,7 +368,7 @@ int run_sap(const Geo& g, const GaugeDev& G, const SpinorBuf& b, const SpinorBuf
     a.x = x.data;
     a.x_scale = x.scale;
     a.nsys = nsys;
-    a.sys_tile = sys_tile > 0 ? sys_tile : nsys;
+    a.sys_tile = sys_tile;
     a.mr_iters = mr_iters;
     for (int k = 0; k < kMaxSys; ++k) a.mu[k] = mu[k];
     const Prec cp = b.prec == P_F64 ? P_F64 : P_F32;

@@ -56,7 +56,9 @@ __global__ void __launch_bounds__(kThreads) k_dirac(DiracArgs a) {
     }
     const size_t in_stride = (size_t)6 * g.V * Unit<Si>::bytes;
     const size_t out_stride = (size_t)6 * g.V * Unit<So>::bytes;
-    for (int sys = 0; sys < a.nsys; ++sys) {
+    const int sys_begin = blockIdx.y * a.sys_tile;
+    const int sys_end = min(a.nsys, sys_begin + a.sys_tile);
+    for (int sys = sys_begin; sys < sys_end; ++sys) {
         const void* in = reinterpret_cast<const char*>(a.in) + sys * in_stride;
         const float* isc = a.in_scale ? a.in_scale + (size_t)sys * g.V : nullptr;
         Spinor<R> acc;
@@ -132,7 +134,9 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
     __syncthreads();
     const size_t in_stride = (size_t)6 * g.V * Unit<Si>::bytes;
     const size_t out_stride = (size_t)6 * g.V * Unit<So>::bytes;
-    for (int sys = 0; sys < a.nsys; ++sys) {
+    const int sys_begin = blockIdx.y * a.sys_tile;
+    const int sys_end = min(a.nsys, sys_begin + a.sys_tile);
+    for (int sys = sys_begin; sys < sys_end; ++sys) {
         const void* in = reinterpret_cast<const char*>(a.in) + sys * in_stride;
         const float* isc = a.in_scale ? a.in_scale + (size_t)sys * g.V : nullptr;
         // the thread index again through a barrier the compiler cannot see through: the LDS reads
@@ -186,16 +190,19 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
 }
 
 template <class Si, class So, class G, class C, class R>
-hipError_t run(const DiracArgs& a, hipStream_t st) {
-    unsigned grid = (unsigned)((a.g.V + kThreads - 1) / kThreads);
+hipError_t run(const DiracArgs& args, hipStream_t st) {
+    DiracArgs a = args;
+    const unsigned nwg = (unsigned)((a.g.V + kThreads - 1) / kThreads);
+    a.sys_tile = pick_sys_tile(nwg, a.nsys, kCUs, 0.4);
+    const dim3 grid(nwg, (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
     if constexpr (std::is_same<R, double>::value && std::is_same<G, double>::value) {
         const int* lb = a.g.lb;
         if (lb[0] == 4 && lb[1] == 4 && lb[2] == 4 && lb[3] == 4 && a.g.V % kThreads == 0) {
-            hipLaunchKernelGGL((k_dirac_lk<Si, So, C>), dim3(grid), dim3(kThreads), 0, st, a);
+            hipLaunchKernelGGL((k_dirac_lk<Si, So, C>), grid, dim3(kThreads), 0, st, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((k_dirac<Si, So, G, C, R>), dim3(grid), dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((k_dirac<Si, So, G, C, R>), grid, dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
 

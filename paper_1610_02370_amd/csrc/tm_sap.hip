@@ -1340,7 +1340,9 @@ __global__ void __launch_bounds__(kV2) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int i = 0; i < 72; ++i) A.a[i] *= -2.f;
 
-    for (int sys = 0; sys < a.nsys; ++sys) {
+    const int sys_begin = blockIdx.y * a.sys_tile;
+    const int sys_end = min(a.nsys, sys_begin + a.sys_tile);
+    for (int sys = sys_begin; sys < sys_end; ++sys) {
         // indices used outside the stencil's own loops recomputed per system (see k_sap_half_44)
         int lx = l;
         asm volatile("" : "+v"(lx));
@@ -1365,17 +1367,29 @@ __global__ void __launch_bounds__(kV2) __attribute__((amdgpu_waves_per_eu(2, 2))
 }
 
 template <class Si, class So, class G, class C>
-hipError_t run_dirac_44(const DiracArgs& a, hipStream_t st) {
+hipError_t run_dirac_44(const DiracArgs& args, hipStream_t st) {
+    DiracArgs a = args;
     const long long nblocks = (long long)a.g.nb[0] * a.g.nb[1] * a.g.nb[2] * a.g.nb[3];
     const long long n = a.colour >= 0 ? nblocks / 2 : nblocks;
-    hipLaunchKernelGGL((k_dirac_44<Si, So, G, C>), dim3((unsigned)n), dim3(kV2), 0, st, a);
+    // two workgroups per CU; the tile's links and clover cost about 0.4 of one system's stencil
+    a.sys_tile = pick_sys_tile(n, a.nsys, 2 * kCUs, 0.4);
+    const dim3 grid((unsigned)n, (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
+    hipLaunchKernelGGL((k_dirac_44<Si, So, G, C>), grid, dim3(kV2), 0, st, a);
     return hipGetLastError();
 }
 
 template <class S, class G, class C, class R>
-hipError_t run(const SapArgs& a, hipStream_t st) {
+hipError_t run(const SapArgs& args, hipStream_t st) {
+    SapArgs a = args;
     const int nt = (a.g.Vb + 63) & ~63;
     const long long nblocks = (long long)a.g.nb[0] * a.g.nb[1] * a.g.nb[2] * a.g.nb[3];
+    if (a.sys_tile <= 0) {
+        // two workgroups per CU with FP32 arithmetic (of 256 threads; smaller blocks allow more, but
+        // not to count on), one with FP64; the block's links and clover cost about 0.15 of one
+        // system's residual and MR steps
+        const int per_cu = sizeof(R) == 4 && nt <= 256 && !a.eo ? 2 : 1;
+        a.sys_tile = pick_sys_tile(nblocks / 2, a.nsys, per_cu * kCUs, 0.15);
+    }
     dim3 grid((unsigned)(nblocks / 2), (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
     const size_t lds = sap_lds_bytes(a.g.Vb, sizeof(R) == 8 ? P_F64 : P_F32);
     int dev = 0, max_lds = 0;

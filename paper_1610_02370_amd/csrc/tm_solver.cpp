@@ -82,7 +82,7 @@ struct Ctx {
     int nsys;
     double mu[kMaxSys];
     int n_cycles, mr_iters;
-    int sys_tile;  // SAP systems per workgroup (0 = all)
+    int sys_tile;  // SAP systems per workgroup (0 = the launch decides)
     bool eo;       // even-odd preconditioned SAP block solves
     const GaugeDev* op;  // operator for w = D z and residuals
     Prec op_compute;

@@ -215,7 +215,7 @@ int tm_autotune_sap(const tm_geom* geom, const void* U, double kappa, double c_s
     if (!ds) return rc;
     hipStream_t st = (hipStream_t)opts->stream;
 
-    // stage 1: block shape with all systems in one workgroup; stage 2: systems per workgroup for that shape
+    // stage 1: block shape with the launch's own choice of systems per workgroup; stage 2: other splits for that shape
     double best = 0;
     int bb[4] = {0, 0, 0, 0}, btile = 0;
     for (auto& c : cand) {

@@ -42,6 +42,20 @@ def test_sys_tile_is_bit_identical(field, prec):
     assert np.array_equal(out[0], out[2])
 
 
+@pytest.mark.parametrize("prec,dims,nsys", [("f32", (8, 8, 8, 8), 12), ("f64", (8, 8, 8, 8), 5), ("f64", (3, 5, 2, 7), 4),
+                                            ("f32", (6, 4, 2, 5), 3)])
+def test_split_application_is_bit_identical(prec, dims, nsys):
+    # lattices with far fewer tiles than the device holds: the systems of one call go to several
+    # workgroups per tile and give what one system at a time gives
+    mus = [0.01 * (k + 1) for k in range(nsys)]
+    U, psi = synth.gauge_field(dims, 0.6, seed=62), synth.gaussian_spinor(dims, nsys, seed=162)
+    announce(f"application split prec={prec} dims={dims}")
+    got = host(tm.tm_dirac_apply(dims, dev(U), dev(psi), KAPPA, mus, CSW, storage=prec))
+    for k in range(nsys):
+        one = host(tm.tm_dirac_apply(dims, dev(U), dev(psi[k:k + 1]), KAPPA, [mus[k]], CSW, storage=prec))
+        assert np.array_equal(got[k], one[0])
+
+
 def test_autotune_round_trip(field, tmp_path, monkeypatch):
     cache = tmp_path / "tune.txt"
     monkeypatch.setenv("TM_TUNE_CACHE", str(cache))
