@@ -183,6 +183,9 @@ hipError_t launch_dirac_44(const DiracArgs& a, Prec in_p, Prec out_p, Prec link_
                            hipStream_t st);
 hipError_t launch_sap_half(const SapArgs& a, Prec spinor_p, Prec link_p, Prec clover_p, Prec compute,
                            hipStream_t st);
+// Half-sweeps with two lanes per site (tm_sap_pair.hip): FP64, and even-odd block solves at every
+// precision; hipErrorNotSupported for other blocks than 4^4 and for plain FP32 solves.
+hipError_t launch_sap_pair(const SapArgs& a, Prec spinor_p, Prec link_p, Prec clover_p, hipStream_t st);
 bool sap_supported(Prec spinor_p, Prec link_p, Prec clover_p, Prec compute);
 // True when a half-sweep with these storage/link/clover precisions runs the 4^4 FP32 kernel with
 // FP32 storage, whose w_out output is then available.

@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "tm_internal.h"
+#include "tm_reduce.h"
 #include "tm_sap_index.h"
 
 namespace tmsap {
@@ -40,41 +41,6 @@ bool sap_v2_forced() {
     return forced == 1;
 }
 
-template <class R>
-__device__ inline R wave_sum(R v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-// Wavefront sum with DPP row operations (no LDS crossbar): quad and row
-// reductions, then row broadcasts; the total ends in lane 63.
-template <int CTRL, int ROW_MASK>
-__device__ inline float dpp_f(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf,
-                                                                   true));
-}
-
-template <>
-__device__ inline float wave_sum<float>(float v) {
-    v += dpp_f<0xb1, 0xf>(v);   // quad_perm [1,0,3,2]
-    v += dpp_f<0x4e, 0xf>(v);   // quad_perm [2,3,0,1]
-    v += dpp_f<0x114, 0xf>(v);  // row_shr:4
-    v += dpp_f<0x118, 0xf>(v);  // row_shr:8
-    v += dpp_f<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    v += dpp_f<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-
-// Smallest normal number.  An MR step is taken only when <q,q> is at least
-// this: a block whose residual has (nearly) vanished keeps e, and neither the
-// hardware reciprocal nor a flushed division meets a subnormal divisor
-// (which would turn the step length into inf or NaN).
-template <class R>
-__device__ constexpr R min_normal() {
-    return sizeof(R) == 8 ? (R)2.2250738585072014e-308 : (R)1.17549435e-38f;
-}
-
 // The minimal-residual step's local sums <q, rho> and <q, q> (section 2.4's block
 // solver), added one product at a time so that each product is one fused
 // multiply-add (a sum of two products added in one step costs a third instruction).
@@ -97,27 +63,6 @@ __device__ inline void mr_residual_update(cplx<R> alpha, const Spinor<R>& q, Spi
     const cplx<R> na = cmk(-alpha.re, -alpha.im);
 #pragma unroll
     for (int i = 0; i < 12; ++i) rho.v[i] = cmad(na, q.v[i], rho.v[i]);
-}
-
-// Sum of three values over the workgroup; every thread gets the result.
-template <class R>
-__device__ inline void block_sum3(R* red, R& a, R& b, R& c) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    c = wave_sum(c);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-    if (lane == 0) {
-        red[4 * w] = a;
-        red[4 * w + 1] = b;
-        red[4 * w + 2] = c;
-    }
-    __syncthreads();
-    a = b = c = (R)0;
-    for (int i = 0; i < nw; ++i) {
-        a += red[4 * i];
-        b += red[4 * i + 1];
-        c += red[4 * i + 2];
-    }
 }
 
 template <class R>
@@ -1468,6 +1413,10 @@ bool sap_supported(Prec sp, Prec lp, Prec cp, Prec r) {
 }
 
 hipError_t launch_sap_half(const SapArgs& a, Prec sp, Prec lp, Prec cp, Prec r, hipStream_t st) {
+    if ((a.eo || r == P_F64) && !sap_v1_forced()) {
+        const hipError_t e = launch_sap_pair(a, sp, lp, cp, st);
+        if (e != hipErrorNotSupported) return e;
+    }
     if (sp == P_F64 && lp == P_F64 && cp == P_F64 && r == P_F64) return run<double, double, double, double>(a, st);
     if (sp == P_F32 && lp == P_F32 && cp == P_F32 && r == P_F32) return run<float, float, float, float>(a, st);
     if (sp == P_F16 && lp == P_F16 && cp == P_F32 && r == P_F32) return run<f16, f16, float, float>(a, st);

@@ -36,13 +36,15 @@ struct S44Site {
 
 // Block coordinates of workgroup j in the half-sweep of `colour` (g.nb[3] even).
 __host__ __device__ inline void s44_block(const Geo& g, int colour, long long j, int B[4]) {
-    const int half3 = g.nb[3] >> 1;
-    const int k3 = (int)(j % half3);
-    j /= half3;
-    B[2] = (int)(j % g.nb[2]);
-    j /= g.nb[2];
-    B[1] = (int)(j % g.nb[1]);
-    B[0] = (int)(j / g.nb[1]);
+    // 32-bit unsigned: fewer than 2^31 blocks (a lattice has at most 2^29 sites)
+    const unsigned half3 = (unsigned)g.nb[3] >> 1, n2 = (unsigned)g.nb[2], n1 = (unsigned)g.nb[1];
+    unsigned u = (unsigned)j;
+    const int k3 = (int)(u % half3);
+    u /= half3;
+    B[2] = (int)(u % n2);
+    u /= n2;
+    B[1] = (int)(u % n1);
+    B[0] = (int)(u / n1);
     B[3] = 2 * k3 + ((colour + B[0] + B[1] + B[2]) & 1);
 }
 
