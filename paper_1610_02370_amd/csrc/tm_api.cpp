@@ -2,6 +2,7 @@
 // workspaces, and the entry points declared in include/tm.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -230,8 +231,6 @@ int get_gauge(DeviceState* ds, const Geo& g, const void* U, double kappa, double
     if (h != hipSuccess) return hip_fail(h, "stats");
     unsigned* stats = (unsigned*)ds->stats.ptr;
     if ((h = hipMemsetAsync(stats, 0, 2 * sizeof(unsigned), st)) != hipSuccess) return hip_fail(h, "memset");
-    if ((h = launch_link_ingest(g, link_p, U, slot->dev.links, stats, st)) != hipSuccess)
-        return hip_fail(h, "link ingest");
     // an FP32 clover is the FP64 one rounded: converted from an FP64 copy of the same field,
     // parameters and tiling made or used in this call, else built
     const GaugeEntry* c64 = nullptr;
@@ -247,10 +246,20 @@ int get_gauge(DeviceState* ds, const Geo& g, const void* U, double kappa, double
         }
     const double m4 = 1.0 / (2.0 * kappa);
     if (c64) {
+        if ((h = launch_link_ingest(g, link_p, U, slot->dev.links, stats, st)) != hipSuccess)
+            return hip_fail(h, "link ingest");
         if ((h = launch_clover_to_f32(g, c64->dev.clover, slot->dev.clover, st)) != hipSuccess)
             return hip_fail(h, "clover conversion");
-    } else if ((h = launch_clover_build(g, cl_p, U, m4, csw, slot->dev.clover, st)) != hipSuccess) {
-        return hip_fail(h, "clover build");
+    } else {
+        // the links are staged in the canonical-buffer workspace: as much of it as there is, at least
+        // 256 MiB of slices (or the lattice, or one row of tiles, if that is less / more); without the memory
+        // the build reads the canonical links
+        const size_t whole = gauge_stage_bytes(g, g.d[0]), row = gauge_stage_bytes(g, std::min(g.d[0], g.lb[0] + 2));
+        const size_t want = std::min(whole, std::max(row, (size_t)256 << 20));
+        if (csw != 0.0 && ds->io.ensure(want) != hipSuccess) (void)hipGetLastError();
+        if ((h = launch_gauge_build(g, link_p, cl_p, U, m4, csw, slot->dev.links, slot->dev.clover, stats, ds->io.ptr,
+                                    ds->io.bytes, st)) != hipSuccess)
+            return hip_fail(h, "gauge build");
     }
     unsigned host[2];
     if ((h = hipMemcpyAsync(host, stats, sizeof host, hipMemcpyDeviceToHost, st)) != hipSuccess)

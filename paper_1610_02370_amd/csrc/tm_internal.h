@@ -157,11 +157,16 @@ hipError_t launch_cg_scalars(int mode, int nsys, unsigned long long frozen, doub
                              double* out, double* neg, hipStream_t st);
 
 // ---- layout kernels (tm_layout.hip)
+// Internal links from the canonical ones, with the SU(3) check.
 hipError_t launch_link_ingest(const Geo& g, Prec G, const void* Ucanon, void* links, unsigned* stats, hipStream_t st);
+// The same and the clover term (FP64 arithmetic on the canonical links).  `stage` (stage_bytes, may be none)
+// holds time slices of the links as a structure of arrays while the clover is built from them; without
+// room for a row of tiles and its neighbours the clover reads the canonical array.
+hipError_t launch_gauge_build(const Geo& g, Prec G, Prec C, const void* Ucanon, double m4, double csw, void* links,
+                              void* clover, unsigned* stats, void* stage, size_t stage_bytes, hipStream_t st);
+size_t gauge_stage_bytes(const Geo& g, int slices);
 // FP32 clover [18][V] units from the FP64 one (FP64 [18][V] double4 units) of the same geometry.
 hipError_t launch_clover_to_f32(const Geo& g, const void* clover64, void* clover32, hipStream_t st);
-hipError_t launch_clover_build(const Geo& g, Prec C, const void* Ucanon, double m4, double csw, void* clover,
-                               hipStream_t st);
 hipError_t launch_spinor_import(const Geo& g, const SpinorBuf& dst, const void* canon, unsigned* flag,
                                 hipStream_t st);
 hipError_t launch_spinor_export(const Geo& g, const SpinorBuf& src, void* canon, hipStream_t st);

@@ -109,9 +109,9 @@ int tm_sap_smooth_noalloc(const tm_geom* geom, const void* U, const void* b, voi
     // the gauge copy and clover term, validated as tm_sap_smooth validates them
     hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, st, flags, 4);
     if ((h = hipGetLastError()) != hipSuccess) return hip_fail(h, "clear flags");
-    if ((h = launch_link_ingest(g, sp, U, G.links, flags, st)) != hipSuccess) return hip_fail(h, "link ingest");
-    if ((h = launch_clover_build(g, cp, U, 1.0 / (2.0 * kappa), c_sw, G.clover, st)) != hipSuccess)
-        return hip_fail(h, "clover build");
+    if ((h = launch_gauge_build(g, sp, cp, U, 1.0 / (2.0 * kappa), c_sw, G.links, G.clover, flags, nullptr, 0, st)) !=
+        hipSuccess)
+        return hip_fail(h, "gauge build");
     unsigned host[2];
     if ((h = hipMemcpyAsync(host, flags, sizeof host, hipMemcpyDeviceToHost, st)) != hipSuccess)
         return hip_fail(h, "flags copy");

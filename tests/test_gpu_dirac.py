@@ -183,3 +183,32 @@ def test_dirac_64_systems_match_single_calls(prec):
     for k in (0, 63):
         ref = op.with_mu(mus[k]).apply(psi[k]).reshape(-1, 4, 3)
         check_close(allsys[k], ref, "dirac", prec, f"64 systems, system {k}")
+
+
+@pytest.mark.parametrize("dims,csw", [((4, 4, 4, 4), 1.5), ((1, 3, 2, 5), 1.2), ((5, 3, 7, 9), 0.7), ((2, 8, 4, 12), 0.0)])
+def test_gauge_build_with_and_without_staged_links(dims, csw):
+    # the clover term from time slices staged as a structure of arrays, against the oracle, on lattices whose
+    # slices are not multiples of a workgroup's 64 sites, extents of 1 and 2 wrap onto themselves, or the term is zero
+    U, psi = synth.gauge_field(dims, 0.6, seed=81), synth.gaussian_spinor(dims, 1, seed=181)
+    op = oracle.Operator(dims, U, oracle.kappa_to_m(0.14), 0.1, csw)
+    ref = op.apply(psi[0]).reshape(psi[0].shape)
+    announce(f"gauge build dims={dims} csw={csw}")
+    for tag in (0, 7):
+        got = host(tm.tm_dirac_apply(dims, dev(U), dev(psi), 0.14, [0.1], csw, gauge_tag=tag))
+        check_close(got[0], ref, "dirac", "f64", f"gauge build {dims} c_sw {csw} tag {tag}")
+
+
+def test_gauge_build_in_chunks_of_slices():
+    # more slices than the staging workspace holds at once: rows of tiles with one slice on either side, the first and
+    # last of them wrapping around the lattice
+    dims = (48, 32, 32, 32)
+    U, psi = synth.gauge_field(dims, 0.6, seed=82), synth.gaussian_spinor(dims, 1, seed=182)
+    tm.tm_finalize()  # no workspace from an earlier call: 256 MiB hold 14 of the 48 slices
+    announce("gauge build in chunks 32^3x48")
+    got = host(tm.tm_dirac_apply(dims, dev(U), dev(psi), 0.1373, [0.001], 1.5))[0].reshape(dims + (4, 3))
+    for t in (0, 1, 11, 12, 23, 47):  # windows of slices t - 2 .. t + 2 hold everything that slice t needs
+        w = [(t + k) % dims[0] for k in range(-2, 3)]
+        Uw = U.reshape(dims + (4, 3, 3))[w].reshape(-1, 4, 3, 3)
+        op = oracle.Operator((5,) + dims[1:], Uw, oracle.kappa_to_m(0.1373), 0.001, 1.5)
+        ref = op.apply(psi[0].reshape(dims + (4, 3))[w].reshape(-1, 4, 3)).reshape((5,) + dims[1:] + (4, 3))[2]
+        check_close(got[t], ref, "dirac", "f64", f"slice {t}")
