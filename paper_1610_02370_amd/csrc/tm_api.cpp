@@ -619,6 +619,24 @@ int tm_dirac_apply(const tm_geom* geom, const void* U, const void* psi, void* ou
         SpinorBuf o = wrap_internal(out, g, geom->nsys, sp);
         return run_dirac(g, *G, in, o, mu, geom->nsys, cp, st);
     }
+    // FP64 storage: the operator reads and writes the canonical buffers themselves, unless they overlap
+    // (then out must not be written before all of psi is read)
+    const size_t span = (size_t)geom->nsys * g.V * 12 * 2 * sizeof(double);
+    const uintptr_t pa = (uintptr_t)psi, pb = (uintptr_t)out;
+    if (sp == P_F64 && (pa + span <= pb || pb + span <= pa)) {
+        DiracArgs a;
+        a.g = g;
+        a.links = G->links;
+        a.clover = G->clover;
+        a.in = psi;
+        a.in_scale = nullptr;
+        a.out = out;
+        a.out_scale = nullptr;
+        a.nsys = geom->nsys;
+        for (int k = 0; k < kMaxSys; ++k) a.mu[k] = mu[k];
+        const hipError_t e = launch_dirac_canonical(a, st);
+        return e == hipSuccess ? TM_OK : hip_fail(e, "dirac");
+    }
     size_t nb = internal_bytes(g, geom->nsys, sp);
     hipError_t h = ds->io.ensure(2 * nb);
     if (h != hipSuccess) return hip_fail(h, "workspace");

@@ -7,12 +7,16 @@
 #include <type_traits>
 
 #include "tm_internal.h"
+#include "tm_pair.h"
 
 namespace tmsap {
 
 namespace {
 
 constexpr int kThreads = 256;
+// Up to here (sites times systems) the FP64 operator splits the directions over wavefronts: below, one
+// workgroup of the unsplit kernel or less falls on each compute unit.
+constexpr long long kSplitSites = 32768;
 
 // Link from its first two rows, stored as 12 reals (row-major, re/im pairs); third row rebuilt.
 template <class R>
@@ -109,8 +113,9 @@ __global__ void __launch_bounds__(kThreads) k_dirac(DiracArgs a) {
 // Here the workgroup stages its tile's own links (two rows each, 96 KiB) in LDS once, and every
 // system takes its forward links there.  The backward links U_mu(x - mu) stay loads from memory:
 // inside the tile they are the links just staged, still in L2, and read from LDS as well they
-// made the compiler spill a kilobyte per lane.
-template <class Si, class So, class C>
+// made the compiler spill a kilobyte per lane.  Kept for several FP64 systems in the internal layout: 32^3x64 in
+// 820 us for one system and 490 per system for six, against 800 and 700 with two lanes per site, whose
+// neighbour reads all go to L2.
 __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
     __shared__ double2 lk[4][6][kThreads];  // [mu][row-major pair][site in tile]
     const Geo& g = a.g;
@@ -130,10 +135,10 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
     unsigned wrap;
     tiled_neighbours(g, s, nf, nbk, &wrap, &par);
     Clover<double> A;
-    load_clover<double, C>(a.clover, g.V, s, A);
+    load_clover<double, double>(a.clover, g.V, s, A);
     __syncthreads();
-    const size_t in_stride = (size_t)6 * g.V * Unit<Si>::bytes;
-    const size_t out_stride = (size_t)6 * g.V * Unit<So>::bytes;
+    const size_t in_stride = (size_t)6 * g.V * Unit<double>::bytes;
+    const size_t out_stride = (size_t)6 * g.V * Unit<double>::bytes;
     const int sys_begin = blockIdx.y * a.sys_tile;
     const int sys_end = min(a.nsys, sys_begin + a.sys_tile);
     for (int sys = sys_begin; sys < sys_end; ++sys) {
@@ -161,7 +166,7 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
                 }
                 link_from_rows(u, L);
             }
-            load_spinor<double, Si>(in, isc, g.V, nf[mu], p);
+            load_spinor<double, double>(in, isc, g.V, nf[mu], p);
             {  // boundary phase (1 for hops inside the lattice)
                 const bool w = wrap & (1u << mu);
                 const double re = w ? g.bcr[mu] : 1.0, im = w ? g.bci[mu] : 0.0;
@@ -170,7 +175,7 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
             }
             hop_forward(mu, L, p, 1.0, acc);
             load_link<double, double>(a.links, g.V, nbk[mu], mu, L);
-            load_spinor<double, Si>(in, isc, g.V, nbk[mu], p);
+            load_spinor<double, double>(in, isc, g.V, nbk[mu], p);
             {
                 const bool w = wrap & (16u << mu);
                 const double re = w ? g.bcr[mu] : 1.0, im = w ? -g.bci[mu] : 0.0;
@@ -180,28 +185,276 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
             hop_backward(mu, L, p, 1.0, acc);
         }
         Spinor<double> self, out;
-        load_spinor<double, Si>(in, isc, g.V, s, self);
+        load_spinor<double, double>(in, isc, g.V, s, self);
         clover_apply(A, a.mu[sys] + g.mu_shift[par], self, out);
 #pragma unroll
         for (int i = 0; i < 12; ++i) out.v[i] = out.v[i] - 0.5 * acc.v[i];
-        store_spinor<double, So>(reinterpret_cast<char*>(a.out) + sys * out_stride,
+        store_spinor<double, double>(reinterpret_cast<char*>(a.out) + sys * out_stride,
                                  a.out_scale ? a.out_scale + (size_t)sys * g.V : nullptr, g.V, s, out);
     }
+}
+
+// ---------------------------------------------------------------------------
+// FP64 arithmetic: two lanes per site (tm_pair.h), any tiles, fields in the internal layout (any
+// storage in) or in the canonical one, which spares the conversions of canonical buffers.
+//
+// At FP64 one lane per site holds the clover and little else at one wavefront per SIMD, and waits for its
+// neighbours one hop at a time.  A pair's lanes each read the two spins of a neighbour that their
+// half spinor needs, and both hops of a direction are read before either is used.
+//
+// Measured, with the calls' canonical buffers: 6x10x7x9, 3 systems, 26.6 -> 13.3 us; 4^4, 2 systems, 19.6 ->
+// 13.2; 32^3x64, one system, 1170 -> 830, six systems 5060 -> 3980; FP32 in and FP64 out, 32^3x64, two
+// systems, 1740 -> 1180.  Large lattices are bound by the neighbours' reads from L2 (about 3 KB per
+// site and system, 8 TB/s).
+
+// A field of spinors: a site's chirality c, and the two spins that lane c needs of a neighbour.
+template <class S> struct FieldOf {  // internal layout, units of four reals
+    const void* base;
+    const float* scale;
+    long long V;
+    __device__ inline FieldOf(const void* p, const float* sc, int sys, const Geo& g)
+        : base(static_cast<const char*>(p) + (size_t)sys * 6 * g.V * Unit<S>::bytes),
+          scale(sc ? sc + (size_t)sys * g.V : nullptr), V(g.V) {}
+    __device__ inline void chirality(long long s, int c, Chir<double>& v) const {
+        load_chir<double, S>(base, scale, V, s, c, v);
+    }
+    struct Raw {
+        Chir<double> v;
+    };
+    template <int MU> __device__ inline void read(long long s, int c, Raw& r) const { chirality(s, c, r.v); }
+    template <int MU> static __device__ inline void spins(const Raw& r, int c, Col<double>& p, Col<double>& q) {
+        pair_spins<MU>(r.v, c != 0, p, q);
+    }
+    static constexpr bool kCanonical = false;
+};
+struct Canonical {
+    const double2* base;
+    __device__ inline Canonical(const void* p, const float*, int sys, const Geo& g)
+        : base(static_cast<const double2*>(p) + (size_t)sys * 12 * g.V) {}
+    __device__ inline void chirality(long long lex, int c, Chir<double>& v) const {
+        const double2* r = base + 12 * (size_t)lex + 6 * c;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) v.v[i] = cmk(r[i].x, r[i].y);
+    }
+    struct Raw {
+        Col<double> p, q;
+    };
+    template <int MU> __device__ inline void read(long long lex, int c, Raw& r) const {
+        const double2* a = base + 12 * (size_t)lex + 3 * c;
+        const double2* b = base + 12 * (size_t)lex + 3 * (pair_cross(MU) ? 3 - c : 2 + c);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            r.p.v[k] = cmk(a[k].x, a[k].y);
+            r.q.v[k] = cmk(b[k].x, b[k].y);
+        }
+    }
+    template <int MU> static __device__ inline void spins(const Raw& r, int, Col<double>& p, Col<double>& q) {
+        p = r.p;
+        q = r.q;
+    }
+    static constexpr bool kCanonical = true;
+};
+
+template <int MU>
+__device__ inline void link_read(const DiracArgs& a, long long site, cplx<double> u[6]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        double w[4];
+        Unit<double>::load(plane<double>(a.links, 3 * MU + q, a.g.V), (size_t)site, w);
+        u[2 * q] = cmk(w[0], w[1]);
+        u[2 * q + 1] = cmk(w[2], w[3]);
+    }
+}
+
+template <int MU, int DIR, class F>
+__device__ inline void hop_add(const Geo& g, const typename F::Raw& psi, const cplx<double> u[6], bool wrap, int c,
+                               double s, PairAcc<double>& acc) {
+    Col<double> p, q, h, t;
+    F::template spins<MU>(psi, c, p, q);
+    pair_project<MU, DIR>(p, q, s, h);
+    if (wrap) {  // boundary phase
+        const cplx<double> ph = cmk(g.bcr[MU], DIR > 0 ? g.bci[MU] : -g.bci[MU]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) h.v[k] = ph * h.v[k];
+    }
+    if constexpr (DIR > 0)
+        pair_mul(u, h, t);
+    else
+        pair_dag_mul(u, h, t);
+    pair_accumulate<MU, DIR>(t, s, acc);
+}
+
+// The site's neighbours: tiled (links) and, for canonical fields, lexicographic.
+struct PairSite {
+    long long s, lex;
+    int nf[4], nbk[4], cf[4], cb[4];
+    unsigned wrap;
+    int parity;
+};
+template <bool CANON> __device__ inline void pair_site(const Geo& g, long long s, PairSite& t) {
+    t.s = s;
+    tiled_neighbours(g, s, t.nf, t.nbk, &t.wrap, &t.parity);
+    t.lex = s;
+    if constexpr (CANON) {
+        unsigned blk = (unsigned)s / (unsigned)g.Vb, l = (unsigned)s - blk * (unsigned)g.Vb;
+        int c[4], st[4];
+#pragma unroll
+        for (int a = 3; a >= 0; --a) {
+            const unsigned nb = (unsigned)g.nb[a], lb = (unsigned)g.lb[a], bq = blk / nb, lq = l / lb;
+            c[a] = (int)((blk - bq * nb) * lb + (l - lq * lb));
+            blk = bq;
+            l = lq;
+        }
+        st[3] = 1;
+#pragma unroll
+        for (int a = 2; a >= 0; --a) st[a] = st[a + 1] * g.d[a + 1];
+        const int lex = c[0] * st[0] + c[1] * st[1] + c[2] * st[2] + c[3];
+        t.lex = lex;
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu) {
+            const int a = axis_of(mu), span = (g.d[a] - 1) * st[a];
+            t.cf[mu] = c[a] + 1 < g.d[a] ? lex + st[a] : lex - span;
+            t.cb[mu] = c[a] > 0 ? lex - st[a] : lex + span;
+        }
+    }
+}
+
+// Both hops of direction MU.
+template <int MU, class F>
+__device__ inline void dir_add(const DiracArgs& a, const F& in, const PairSite& t, int c, double s,
+                               PairAcc<double>& acc) {
+    __builtin_amdgcn_sched_barrier(0);  // one direction's operands live at a time
+    cplx<double> uf[6], ub[6];
+    typename F::Raw pf, pb;
+    in.template read<MU>(F::kCanonical ? t.cf[MU] : t.nf[MU], c, pf);
+    link_read<MU>(a, t.s, uf);
+    in.template read<MU>(F::kCanonical ? t.cb[MU] : t.nbk[MU], c, pb);
+    link_read<MU>(a, t.nbk[MU], ub);
+    hop_add<MU, +1, F>(a.g, pf, uf, t.wrap & (1u << MU), c, s, acc);
+    hop_add<MU, -1, F>(a.g, pb, ub, t.wrap & (16u << MU), c, s, acc);
+    pin(acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Clover, twist and the store for one system, its hop sum formed.
+template <class F, class So>
+__device__ inline void site_finish(const DiracArgs& a, int sys, const PairSite& t, int c, const double A[36], bool on,
+                                   const PairAcc<double>& acc) {
+    const Geo& g = a.g;
+    const bool lower = c != 0;
+    const F in(a.in, a.in_scale, sys, g);
+    Chir<double> hop, self, out;
+    pair_finish(acc, lower, hop);
+    in.chirality(t.lex, c, self);
+    const double mu = a.mu[sys] + g.mu_shift[t.parity];
+    clover_block_apply(A, lower ? -mu : mu, self.v, out.v);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) out.v[i] = out.v[i] - 0.5 * hop.v[i];
+    if (!on) return;
+    if constexpr (F::kCanonical) {
+        double2* o = static_cast<double2*>(a.out) + ((size_t)sys * g.V + t.lex) * 12 + 6 * c;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) o[i] = make_double2(out.v[i].re, out.v[i].im);
+    } else {
+        store_chir<double, So>(static_cast<char*>(a.out) + (size_t)sys * 6 * g.V * Unit<So>::bytes, nullptr, g.V, t.s, c,
+                               out);
+    }
+}
+
+__device__ inline void clover_read(const DiracArgs& a, size_t s, int c, double A[36]) {
+    const size_t at = (size_t)(9 * c) * a.g.V + s;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) Unit<double>::load(plane<double>(a.clover, k, a.g.V), at, A + 4 * k);
+}
+
+// 32 sites of one system per wavefront.  The four wavefronts of a workgroup take `sys_tile` (1, 2 or 4)
+// systems of the same sites, so that the later ones find the links and the clover in the vector cache.
+template <class F, class So>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) k_dirac_pair(DiracArgs a) {
+    const Geo& g = a.g;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 1;
+    const double s = c != 0 ? 1.0 : -1.0;
+    const int groups = 4 / a.sys_tile, sys = blockIdx.y * a.sys_tile + w / groups;
+    if (sys >= a.nsys) return;
+    // workgroups of one XCD on consecutive sites (their neighbours' spinors and links share an L2)
+    const long long at = (xcd_swizzle(blockIdx.x, gridDim.x) * groups + w % groups) * 32 + (lane >> 1);
+    const bool on = at < g.V;
+    PairSite t;
+    pair_site<F::kCanonical>(g, on ? at : 0, t);
+    const F in(a.in, a.in_scale, sys, g);
+    PairAcc<double> acc;
+    pair_zero(acc);
+    dir_add<0>(a, in, t, c, s, acc);
+    dir_add<1>(a, in, t, c, s, acc);
+    dir_add<2>(a, in, t, c, s, acc);
+    dir_add<3>(a, in, t, c, s, acc);
+    double A[36];
+    clover_read(a, (size_t)t.s, c, A);
+    site_finish<F, So>(a, sys, t, c, A, on, acc);
+}
+
+// 32 sites of one system per workgroup, wavefront w on direction w, summed through LDS.
+template <class F, class So>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) k_dirac_pair_split(DiracArgs a) {
+    __shared__ double2 part[3][9][64];
+    const Geo& g = a.g;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 1;
+    const double s = c != 0 ? 1.0 : -1.0;
+    const long long at = (long long)blockIdx.x * 32 + (lane >> 1);
+    const bool on = at < g.V;
+    const int sys = blockIdx.y;
+    PairSite t;
+    pair_site<F::kCanonical>(g, on ? at : 0, t);
+    double A[36];
+    if (w == 0) clover_read(a, (size_t)t.s, c, A);
+    const F in(a.in, a.in_scale, sys, g);
+    PairAcc<double> acc;
+    pair_zero(acc);
+    switch (w) {
+        case 0: dir_add<0>(a, in, t, c, s, acc); break;
+        case 1: dir_add<1>(a, in, t, c, s, acc); break;
+        case 2: dir_add<2>(a, in, t, c, s, acc); break;
+        default: dir_add<3>(a, in, t, c, s, acc); break;
+    }
+    cplx<double>* v[9] = {&acc.up.v[0],   &acc.up.v[1],    &acc.up.v[2],    &acc.same.v[0], &acc.same.v[1],
+                          &acc.same.v[2], &acc.cross.v[0], &acc.cross.v[1], &acc.cross.v[2]};
+    if (w > 0) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) part[w - 1][i][lane] = make_double2(v[i]->re, v[i]->im);
+    }
+    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const double2 p = part[q][i][lane];
+            *v[i] = *v[i] + cmk(p.x, p.y);
+        }
+    site_finish<F, So>(a, sys, t, c, A, on, acc);
+}
+
+template <class F, class So>
+hipError_t run_pair(const DiracArgs& args, hipStream_t st) {
+    DiracArgs a = args;
+    if (a.g.V * a.nsys <= kSplitSites) {
+        hipLaunchKernelGGL((k_dirac_pair_split<F, So>), dim3((unsigned)((a.g.V + 31) / 32), (unsigned)a.nsys),
+                           dim3(kThreads), 0, st, a);
+    } else {
+        a.sys_tile = a.nsys > 2 ? 4 : a.nsys;
+        const long long per = 128 / a.sys_tile;  // sites of a workgroup
+        hipLaunchKernelGGL((k_dirac_pair<F, So>), dim3((unsigned)((a.g.V + per - 1) / per),
+                           (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile)), dim3(kThreads), 0, st, a);
+    }
+    return hipGetLastError();
 }
 
 template <class Si, class So, class G, class C, class R>
 hipError_t run(const DiracArgs& args, hipStream_t st) {
     DiracArgs a = args;
     const unsigned nwg = (unsigned)((a.g.V + kThreads - 1) / kThreads);
-    a.sys_tile = pick_sys_tile(nwg, a.nsys, kCUs, 0.4);
+    a.sys_tile = pick_sys_tile(nwg, a.nsys, kCUs, 0.4, true);
     const dim3 grid(nwg, (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
-    if constexpr (std::is_same<R, double>::value && std::is_same<G, double>::value) {
-        const int* lb = a.g.lb;
-        if (lb[0] == 4 && lb[1] == 4 && lb[2] == 4 && lb[3] == 4 && a.g.V % kThreads == 0) {
-            hipLaunchKernelGGL((k_dirac_lk<Si, So, C>), grid, dim3(kThreads), 0, st, a);
-            return hipGetLastError();
-        }
-    }
     hipLaunchKernelGGL((k_dirac<Si, So, G, C, R>), grid, dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
@@ -222,17 +475,31 @@ hipError_t launch_dirac(const DiracArgs& a, Prec in_p, Prec out_p, Prec link_p, 
 #define TM_CASE(PI, PO, PL, PC, PR, TI, TO, TL, TC, TR)                                      \
     if (in_p == PI && out_p == PO && link_p == PL && clover_p == PC && compute == PR) \
         return run<TI, TO, TL, TC, TR>(a, st);
-    TM_CASE(P_F64, P_F64, P_F64, P_F64, P_F64, double, double, double, double, double)
     TM_CASE(P_F32, P_F32, P_F32, P_F32, P_F32, float, float, float, float, float)
     TM_CASE(P_F16, P_F16, P_F16, P_F32, P_F32, f16, f16, f16, float, float)
     TM_CASE(P_BF16, P_BF16, P_BF16, P_F32, P_F32, bf16, bf16, bf16, float, float)
-    TM_CASE(P_F32, P_F64, P_F64, P_F64, P_F64, float, double, double, double, double)
-    TM_CASE(P_F16, P_F64, P_F64, P_F64, P_F64, f16, double, double, double, double)
-    TM_CASE(P_BF16, P_F64, P_F64, P_F64, P_F64, bf16, double, double, double, double)
     TM_CASE(P_F16, P_F32, P_F32, P_F32, P_F32, f16, float, float, float, float)
     TM_CASE(P_BF16, P_F32, P_F32, P_F32, P_F32, bf16, float, float, float, float)
 #undef TM_CASE
+    if (out_p == P_F64 && link_p == P_F64 && clover_p == P_F64 && compute == P_F64) {
+        const int* lb = a.g.lb;
+        if (in_p == P_F64 && a.nsys > 1 && lb[0] == 4 && lb[1] == 4 && lb[2] == 4 && lb[3] == 4 &&
+            a.g.V * a.nsys > kSplitSites) {
+            DiracArgs t = a;
+            const unsigned nwg = (unsigned)(a.g.V / kThreads);  // a tile has kThreads sites
+            t.sys_tile = pick_sys_tile(nwg, a.nsys, kCUs, 0.4, true);
+            hipLaunchKernelGGL(k_dirac_lk, dim3(nwg, (unsigned)((a.nsys + t.sys_tile - 1) / t.sys_tile)), dim3(kThreads), 0,
+                               st, t);
+            return hipGetLastError();
+        }
+        if (in_p == P_F64) return run_pair<FieldOf<double>, double>(a, st);
+        if (in_p == P_F32) return run_pair<FieldOf<float>, double>(a, st);
+        if (in_p == P_F16) return run_pair<FieldOf<f16>, double>(a, st);
+        if (in_p == P_BF16) return run_pair<FieldOf<bf16>, double>(a, st);
+    }
     return hipErrorInvalidValue;
 }
+
+hipError_t launch_dirac_canonical(const DiracArgs& a, hipStream_t st) { return run_pair<Canonical, double>(a, st); }
 
 }  // namespace tmsap

@@ -34,18 +34,23 @@ inline size_t spinor_scale_bytes(long long V, int nsys, Prec p) {
 // system's work) and then takes its systems in turn, so all systems in one workgroup is best as long
 // as the tiles fill the device; with fewer tiles than slots most of the chip idles while each
 // workgroup runs through every system.  The split with the least ceil(workgroups / slots) x
-// (systems + load) is taken, the coarsest one when several are within 2 %.  Results do not depend on
-// the split.  Measured at 16^4 with 12 FP32 systems (128 blocks of a colour, 512 slots): the half-sweep
+// (systems + load) is taken, unless a coarser one is within 10 % of it (24^3x32 with 2 FP64 systems,
+// estimated 5 % better, ran 6 % worse).  Results do not depend on the split.  Measured at 16^4 with 12 FP32 systems (128 blocks of a colour, 512 slots): the half-sweep
 // 230 us unsplit, the whole defect-correction solve 31.1 -> 13.4 ms with the split; a 6x10x7x9 FP64
 // application of 3 systems 44 -> 27 us.  At 48^3x96 (20736 blocks) no split is taken.
-inline int pick_sys_tile(long long blocks, int nsys, int slots, double load) {
+//
+// fill_only (the operator kernels, bound by memory): no split once the tiles fill the slots.  Their last,
+// partly filled wave of workgroups runs faster than a full one, so splitting to even it out lost 10 %
+// (16^3x36, 2 systems: FP64 86 -> 97 us, FP32 41 -> 45).
+inline int pick_sys_tile(long long blocks, int nsys, int slots, double load, bool fill_only) {
+    if (fill_only && blocks >= slots) return nsys;
     int best = nsys;
     double best_cost = 0;
     for (int groups = 1; groups <= nsys; ++groups) {
         const int tile = (nsys + groups - 1) / groups;
         const long long wg = blocks * ((nsys + tile - 1) / tile);
         const double cost = (double)((wg + slots - 1) / slots) * (tile + load);
-        if (groups == 1 || cost < 0.98 * best_cost) {
+        if (groups == 1 || cost < 0.9 * best_cost) {
             best = tile;
             best_cost = cost;
         }
@@ -180,6 +185,9 @@ inline size_t eo_inverse_bytes(const Geo& g, Prec C) { return (size_t)36 * (g.V 
 // ---- operator (tm_dirac.hip)
 hipError_t launch_dirac(const DiracArgs& a, Prec in_p, Prec out_p, Prec link_p, Prec clover_p, Prec compute,
                         hipStream_t st);
+
+// The FP64 operator on canonical complex128 fields (a.in, a.out [nsys][V][4][3], not overlapping).
+hipError_t launch_dirac_canonical(const DiracArgs& a, hipStream_t st);
 
 // ---- smoother (tm_sap.hip)
 // The operator on 4^4 tiles with FP32 arithmetic (tm_sap.hip); hipErrorNotSupported for other

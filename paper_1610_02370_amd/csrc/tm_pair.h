@@ -42,6 +42,28 @@ template <class R> struct Chir {
     cplx<R> v[6];
 };
 
+// An index the compiler cannot see through: what is read or computed from it stays where it is
+// written, instead of being hoisted out of the system and MR loops (the link reads above all, which
+// do not change there) and spilled.
+__device__ inline int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Keeps a formed vector formed: without it the compiler moves the arithmetic down to the vector's use
+// and holds everything it is formed from until then.
+template <class R> __device__ inline void pin(Col<R>& v) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(v.v[k].re), "+v"(v.v[k].im));
+}
+
+// Before a store: at this register pressure ROCm 7.2's compiler has put a store's address into registers
+// that still held part of its data (x read as 16-byte pieces, updated, and stored as those pieces).
+template <class R> __device__ inline void pin(Chir<R>& v) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(v.v[k].re), "+v"(v.v[k].im));
+}
+
 // Directions whose partner of spin c is 3 - c (else 2 + c).
 __host__ __device__ constexpr bool pair_cross(int mu) { return mu == 1 || mu == 2; }
 
@@ -63,6 +85,12 @@ __device__ inline void pair_project(const Col<R>& p, const Col<R>& q, R s, Col<R
 template <class R> struct PairAcc {
     Col<R> up, same, cross;
 };
+
+template <class R> __device__ inline void pin(PairAcc<R>& a) {
+    pin(a.up);
+    pin(a.same);
+    pin(a.cross);
+}
 
 template <class R> __device__ inline void pair_zero(PairAcc<R>& a) {
 #pragma unroll

@@ -1317,7 +1317,7 @@ hipError_t run_dirac_44(const DiracArgs& args, hipStream_t st) {
     const long long nblocks = (long long)a.g.nb[0] * a.g.nb[1] * a.g.nb[2] * a.g.nb[3];
     const long long n = a.colour >= 0 ? nblocks / 2 : nblocks;
     // two workgroups per CU; the tile's links and clover cost about 0.4 of one system's stencil
-    a.sys_tile = pick_sys_tile(n, a.nsys, 2 * kCUs, 0.4);
+    a.sys_tile = pick_sys_tile(n, a.nsys, 2 * kCUs, 0.4, true);
     const dim3 grid((unsigned)n, (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
     hipLaunchKernelGGL((k_dirac_44<Si, So, G, C>), grid, dim3(kV2), 0, st, a);
     return hipGetLastError();
@@ -1333,7 +1333,7 @@ hipError_t run(const SapArgs& args, hipStream_t st) {
         // not to count on), one with FP64; the block's links and clover cost about 0.15 of one
         // system's residual and MR steps
         const int per_cu = sizeof(R) == 4 && nt <= 256 && !a.eo ? 2 : 1;
-        a.sys_tile = pick_sys_tile(nblocks / 2, a.nsys, per_cu * kCUs, 0.15);
+        a.sys_tile = pick_sys_tile(nblocks / 2, a.nsys, per_cu * kCUs, 0.15, false);
     }
     dim3 grid((unsigned)(nblocks / 2), (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
     const size_t lds = sap_lds_bytes(a.g.Vb, sizeof(R) == 8 ? P_F64 : P_F32);

@@ -30,28 +30,6 @@ template <class R> struct Pad {
     static constexpr int full = sizeof(R) == 8 ? 264 : 272, half = sizeof(R) == 8 ? 136 : 144;
 };
 
-// An index the compiler cannot see through: what is read or computed from it stays where it is
-// written, instead of being hoisted out of the system and MR loops (the link reads above all, which
-// do not change there) and spilled.
-__device__ inline int opaque(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
-// Keeps a formed vector formed: without it the compiler moves the arithmetic down to the vector's use
-// and holds everything it is formed from until then.
-template <class R> __device__ inline void pin(Col<R>& v) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(v.v[k].re), "+v"(v.v[k].im));
-}
-
-// Before a store: at this register pressure ROCm 7.2's compiler has put a store's address into registers
-// that still held part of its data (x read as 16-byte pieces, updated, and stored as those pieces).
-template <class R> __device__ inline void pin(Chir<R>& v) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(v.v[k].re), "+v"(v.v[k].im));
-}
-
 // log2 of the local-index stride of direction mu (t, x, y, z) and its axis.
 __host__ __device__ constexpr int dir_shift(int mu) { return mu == 0 ? 6 : 2 * (mu - 1); }
 __host__ __device__ constexpr int dir_axis(int mu) { return mu == 0 ? 0 : 4 - mu; }
@@ -186,9 +164,7 @@ __device__ inline void hops(const cplx<R>* xs, const LinkLds<R>& lk, int l, int 
     hops_mu<1, ST, CS>(xs, lk, l, par, c, s, acc);
     hops_mu<2, ST, CS>(xs, lk, l, par, c, s, acc);
     hops_mu<3, ST, CS>(xs, lk, l, par, c, s, acc);
-    pin(acc.up);
-    pin(acc.same);
-    pin(acc.cross);
+    pin(acc);
 }
 
 // One halo duty (entry e = axis * 64 + position, axis the same for the wavefront).  The reads are
@@ -695,7 +671,7 @@ hipError_t run(const SapArgs& args, hipStream_t st) {
     if (!args.eo && sizeof(R) == 4) return hipErrorNotSupported;  // FP32 arithmetic: k_sap_half_44
     SapArgs a = args;
     const long long n = (long long)a.g.nb[0] * a.g.nb[1] * a.g.nb[2] * a.g.nb[3] / 2;
-    if (a.sys_tile <= 0) a.sys_tile = pick_sys_tile(n, a.nsys, (a.eo && sizeof(R) == 4 ? 2 : 1) * kCUs, 0.2);
+    if (a.sys_tile <= 0) a.sys_tile = pick_sys_tile(n, a.nsys, (a.eo && sizeof(R) == 4 ? 2 : 1) * kCUs, 0.2, false);
     const dim3 grid((unsigned)n, (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
     if (a.own_zero && a.halo_zero)
         launch<S, G, C, R, kFromZero>(a, grid, st);

@@ -212,3 +212,31 @@ def test_gauge_build_in_chunks_of_slices():
         op = oracle.Operator((5,) + dims[1:], Uw, oracle.kappa_to_m(0.1373), 0.001, 1.5)
         ref = op.apply(psi[0].reshape(dims + (4, 3))[w].reshape(-1, 4, 3)).reshape((5,) + dims[1:] + (4, 3))[2]
         check_close(got[t], ref, "dirac", "f64", f"slice {t}")
+
+
+@pytest.mark.parametrize("dims,nsys", [((3, 5, 7, 9), 1), ((3, 5, 7, 9), 2), ((6, 10, 7, 9), 9), ((8, 8, 16, 20), 5), ((4, 4, 4, 4), 2)])
+def test_canonical_application_matches_staged_one(dims, nsys):
+    # FP64 on the caller's canonical buffers (directions split over wavefronts up to 32768 sites times systems, one
+    # wavefront per system and site above), against internal buffers and, with overlapping buffers, the staged path
+    import torch
+
+    mus = [0.1 * (k - 1) for k in range(nsys)]
+    U, psi = synth.gauge_field(dims, 0.6, seed=91), synth.gaussian_spinor(dims, nsys, seed=191)
+    kw = dict(antiperiodic_t=True, theta=(0.2, 0.3, -0.9, 0.5), mu_shift=(0.03, -0.02))
+    op = oracle.Operator(dims, U, oracle.kappa_to_m(0.14), 0.0, 1.2, **kw)
+    announce(f"canonical application dims={dims} nsys={nsys}")
+    Ud, p = dev(U), dev(psi)
+    got = host(tm.tm_dirac_apply(dims, Ud, p, 0.14, mus, 1.2, **kw))
+    for k in range(nsys):
+        check_close(got[k], op.with_mu(mus[k]).apply(psi[k]), "dirac", "f64", f"canonical {dims} system {k}")
+    n = tm.tm_spinor_bytes(dims, nsys, "f64")
+    a, b = (torch.zeros(n, dtype=torch.uint8, device="cuda") for _ in range(2))
+    tm.tm_spinor_import(dims, p, a, storage="f64")
+    tm.tm_dirac_apply(dims, Ud, a, 0.14, mus, 1.2, b, io="internal", **kw)
+    inner = host(tm.tm_spinor_export(dims, b, torch.empty_like(p), storage="f64"))
+    assert rel_err(inner, got) < 1e-13
+    both = torch.empty((p.numel() + 12,), dtype=torch.complex128, device="cuda")  # out one site behind psi
+    both[:p.numel()] = p.reshape(-1)
+    out = both[12:].view(p.shape)
+    tm.tm_dirac_apply(dims, Ud, both[:p.numel()].view(p.shape), 0.14, mus, 1.2, out, **kw)
+    assert rel_err(host(out), got) < 1e-13
