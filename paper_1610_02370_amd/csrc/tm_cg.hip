@@ -6,6 +6,8 @@
 // is a compact field [nsys][6 units][V/2] indexed by h = s / 2.  FP64 only:
 // the CG is the plain FP64 baseline.
 #include "tm_internal.h"
+#include "tm_pair.h"
+#include "tm_reduce.h"
 
 namespace tmsap {
 
@@ -29,87 +31,152 @@ __device__ inline int site_parity_tiled(const Geo& g, unsigned s) {
     return sum & 1;
 }
 
-__device__ inline void gamma5(Spinor<double>& v) {
-#pragma unroll
-    for (int i = 6; i < 12; ++i) v.v[i] = -v.v[i];
-}
-
 // out_p = (D_pp^-1)? [ hop_sign * H in_hop + D_pp in_diag + add_sign * in_add ], H = -1/2 sum of hops
 // between the parities, D_pp = (m+4) + clover + i mu Gamma5 on parity p; the Gamma5 flags multiply
-// the hop input, the diagonal input and the output.
+// the hop input, the diagonal input and the output.  With `partials`, also ||out||^2 per workgroup and
+// system at partials[sys * gridDim.x + blockIdx.x].
+//
+// Two lanes per site (tm_pair.h), 32 sites of one system per wavefront, the four wavefronts of a workgroup on
+// `sys_tile` (1, 2 or 4) systems of the same sites.  Bound by the links and the site matrices: on 16^3x32,
+// 126 MB (diagonal) to 150 MB (site inverse) per launch in 31-32 us, 4.0-4.8 TB/s, where a copy reaches 4.7;
+// one lane per site kept that half lattice at one wavefront per SIMD and took 36 us.
+template <int MU, bool G5HOP>
+__device__ inline void parity_dir(const ParityArgs& a, const FieldOf<double>& in, unsigned s, const int nf[4],
+                                  const int nbk[4], unsigned wrap, int c, double sg, PairAcc<double>& acc) {
+    const Geo& g = a.g;
+    __builtin_amdgcn_sched_barrier(0);  // one direction's operands live at a time
+    cplx<double> uf[6], ub[6];
+    FieldOf<double>::Raw pf, pb;
+    in.read<MU>(nf[MU] >> 1, c, pf);
+    link_read<MU>(a.links, g.V, s, uf);
+    in.read<MU>(nbk[MU] >> 1, c, pb);
+    link_read<MU>(a.links, g.V, nbk[MU], ub);
+    Col<double> p, q, h, t;
+    FieldOf<double>::spins<MU>(pf, c, p, q);
+    if (G5HOP) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) q.v[k] = -q.v[k];
+    }
+    pair_project<MU, +1>(p, q, sg, h);
+    if (wrap & (1u << MU)) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) h.v[k] = cmk(g.bcr[MU], g.bci[MU]) * h.v[k];
+    }
+    pair_mul(uf, h, t);
+    pair_accumulate<MU, +1>(t, sg, acc);
+    FieldOf<double>::spins<MU>(pb, c, p, q);
+    if (G5HOP) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) q.v[k] = -q.v[k];
+    }
+    pair_project<MU, -1>(p, q, sg, h);
+    if (wrap & (16u << MU)) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) h.v[k] = cmk(g.bcr[MU], -g.bci[MU]) * h.v[k];
+    }
+    pair_dag_mul(ub, h, t);
+    pair_accumulate<MU, -1>(t, sg, acc);
+    pin(acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 template <bool HOP, bool DIAG, bool INV, bool G5HOP>
-__global__ void __launch_bounds__(kThreads) k_parity_op(ParityArgs a) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) k_parity_op(ParityArgs a) {
+    __shared__ double nrm[4];
     const Geo& g = a.g;
     const long long half = g.V / 2;
-    const long long h = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= half) return;
-    unsigned s = 2u * (unsigned)h;
-    if (site_parity_tiled(g, s) != a.p) ++s;
-    int nf[4], nbk[4], par = a.p;
-    unsigned wrap = 0;
-    if (HOP) tiled_neighbours(g, s, nf, nbk, &wrap, &par);
-    const size_t vs = (size_t)6 * half;  // units per system
-    for (int sys = 0; sys < a.nsys; ++sys) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 1;
+    const bool lower = c != 0;
+    const double sg = lower ? 1.0 : -1.0;
+    const int groups = 4 / a.sys_tile, sys = blockIdx.y * a.sys_tile + w / groups;
+    double n2 = 0;
+    for (int vb = blockIdx.x; vb < a.chunks && sys < a.nsys; vb += gridDim.x) {
+        const long long at = (xcd_swizzle(vb, a.chunks) * groups + w % groups) * 32 + (lane >> 1);
+        const bool on = at < half;
+        const long long h = on ? at : 0;
+        unsigned s = 2u * (unsigned)h;
+        if (site_parity_tiled(g, s) != a.p) ++s;
         const double mu = a.mu_sign * (a.mu[sys] + g.mu_shift[a.p]);
-        Spinor<double> v;
+        Chir<double> v;
 #pragma unroll
-        for (int i = 0; i < 12; ++i) v.v[i] = cmk(0.0, 0.0);
-        if (DIAG) {
-            Spinor<double> d;
-            load_spinor<double, double>(a.in_diag + sys * vs * 4, nullptr, half, h, d);
-            if (a.g5_diag) gamma5(d);
-            Clover<double> A;
-            load_clover<double, double>(a.clover, g.V, s, A);
-            clover_acc(A, mu, d, v);
-        }
+        for (int i = 0; i < 6; ++i) v.v[i] = cmk(0.0, 0.0);
         if (HOP) {
-            const double* in = a.in_hop + sys * vs * 4;
-            Spinor<double> acc;
+            int nf[4], nbk[4], par;
+            unsigned wrap;
+            tiled_neighbours(g, s, nf, nbk, &wrap, &par);
+            const FieldOf<double> in(a.in_hop, nullptr, sys, half);
+            PairAcc<double> acc;
+            pair_zero(acc);
+            parity_dir<0, G5HOP>(a, in, s, nf, nbk, wrap, c, sg, acc);
+            parity_dir<1, G5HOP>(a, in, s, nf, nbk, wrap, c, sg, acc);
+            parity_dir<2, G5HOP>(a, in, s, nf, nbk, wrap, c, sg, acc);
+            parity_dir<3, G5HOP>(a, in, s, nf, nbk, wrap, c, sg, acc);
+            pair_finish(acc, lower, v);
+            const double f = -0.5 * a.hop_sign;
 #pragma unroll
-            for (int i = 0; i < 12; ++i) acc.v[i] = cmk(0.0, 0.0);
+            for (int i = 0; i < 6; ++i) v.v[i] = f * v.v[i];
+        }
+        if (DIAG) {
+            Chir<double> d;
+            FieldOf<double>(a.in_diag, nullptr, sys, half).chirality(h, c, d);
+            if (a.g5_diag && lower) {
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                Link<double> L;
-                Spinor<double> p;
-                load_link<double, double>(a.links, g.V, s, m, L);
-                load_spinor<double, double>(in, nullptr, half, nf[m] >> 1, p);
-                if (G5HOP) gamma5(p);
-                {  // boundary phase (1 inside the lattice), branch-free: fewer registers
-                    const bool w = wrap & (1u << m);
-                    const double re = w ? g.bcr[m] : 1.0, im = w ? g.bci[m] : 0.0;
-#pragma unroll
-                    for (int i = 0; i < 12; ++i)
-                        p.v[i] = cmk(re * p.v[i].re - im * p.v[i].im, re * p.v[i].im + im * p.v[i].re);
-                }
-                hop_forward(m, L, p, 1.0, acc);
-                load_link<double, double>(a.links, g.V, nbk[m], m, L);
-                load_spinor<double, double>(in, nullptr, half, nbk[m] >> 1, p);
-                if (G5HOP) gamma5(p);
-                {
-                    const bool w = wrap & (16u << m);
-                    const double re = w ? g.bcr[m] : 1.0, im = w ? -g.bci[m] : 0.0;
-#pragma unroll
-                    for (int i = 0; i < 12; ++i)
-                        p.v[i] = cmk(re * p.v[i].re - im * p.v[i].im, re * p.v[i].im + im * p.v[i].re);
-                }
-                hop_backward(m, L, p, 1.0, acc);
+                for (int i = 0; i < 6; ++i) d.v[i] = -d.v[i];
             }
+            double A[36];
+            const size_t ca = (size_t)(9 * c) * g.V + s;
 #pragma unroll
-            for (int i = 0; i < 12; ++i) v.v[i] = v.v[i] + (-0.5 * a.hop_sign) * acc.v[i];
+            for (int k = 0; k < 9; ++k) Unit<double>::load(plane<double>(a.clover, k, g.V), ca, A + 4 * k);
+            clover_block_acc(A, lower ? -mu : mu, d.v, v.v);
         }
         if (a.in_add) {
-            Spinor<double> d;
-            load_spinor<double, double>(a.in_add + sys * vs * 4, nullptr, half, h, d);
+            Chir<double> d;
+            FieldOf<double>(a.in_add, nullptr, sys, half).chirality(h, c, d);
 #pragma unroll
-            for (int i = 0; i < 12; ++i) v.v[i] = v.v[i] + a.add_sign * d.v[i];
+            for (int i = 0; i < 6; ++i) v.v[i] = v.v[i] + a.add_sign * d.v[i];
         }
         if (INV) {
-            Spinor<double> t;
-            eo_inverse_apply<double, double>(a.inv[a.sel[sys]], half, h, mu < 0, v, t);
-            v = t;
+            const void* inv = a.inv[a.sel[sys]];
+            const size_t ia = (size_t)(18 * c) * half + h;
+            Chir<double> o;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) o.v[i] = cmk(0.0, 0.0);
+#pragma unroll
+            for (int u = 0; u < 18; ++u) {
+                double m[4];
+                Unit<double>::load(plane<double>(inv, u, half), ia, m);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int e = 2 * u + k, i = e / 6, j = e % 6;
+                    const cplx<double> z = cmk(m[2 * k], m[2 * k + 1]);
+                    if (mu < 0)  // the adjoint: the inverse for the opposite twist
+                        o.v[j] = cjmad(z, v.v[i], o.v[j]);
+                    else
+                        o.v[i] = cmad(z, v.v[j], o.v[i]);
+                }
+            }
+            v = o;
         }
-        if (a.g5_out) gamma5(v);
-        store_spinor<double, double>(a.out + sys * vs * 4, nullptr, half, h, v);
+        if (a.g5_out && lower) {
+#pragma unroll
+            for (int i = 0; i < 6; ++i) v.v[i] = -v.v[i];
+        }
+        if (on) {
+            store_chir<double, double>(a.out + (size_t)sys * 6 * half * 4, nullptr, half, h, c, v);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) n2 += v.v[i].re * v.v[i].re + v.v[i].im * v.v[i].im;
+        }
+    }
+    if (a.partials) {
+        n2 = wave_sum(n2);
+        if (lane == 0) nrm[w] = n2;
+        __syncthreads();
+        const int k = threadIdx.x;
+        if (k < a.sys_tile && (int)blockIdx.y * a.sys_tile + k < a.nsys) {
+            double t = 0;
+            for (int i = 0; i < groups; ++i) t += nrm[k * groups + i];
+            a.partials[(size_t)(blockIdx.y * a.sys_tile + k) * gridDim.x + blockIdx.x] = t;
+        }
     }
 }
 
@@ -168,30 +235,102 @@ __global__ void __launch_bounds__(kThreads) k_axpby(const double* __restrict__ x
         ys[i] = fa * xs[i] + fb * ys[i];
 }
 
-// CG scalars per system (frozen systems take zero steps):
-//   mode 0: alpha = gamma / qq,  neg = -alpha
-//   mode 1: beta = gnew / gamma, gamma = gnew
-__global__ void k_cg_scalars(int mode, int nsys, unsigned long long frozen, double* gamma, const double* v,
-                             double* out, double* neg) {
-    const int k = threadIdx.x;
-    if (k >= nsys) return;
-    const bool off = (frozen >> k) & 1ull;
-    if (mode == 0) {
-        const double a = (off || !(v[k] > 0)) ? 0.0 : gamma[k] / v[k];
-        out[k] = a;
-        neg[k] = -a;
-    } else {
-        const double b = (off || !(gamma[k] > 0)) ? 0.0 : v[k] / gamma[k];
-        out[k] = b;
-        if (!off) gamma[k] = v[k];
+// Sum of n partials, in the same order in every workgroup that forms it.
+__device__ inline double sum_partials(const double* p, int n, double* lds) {
+    double t = 0;
+    for (int i = threadIdx.x; i < n; i += kThreads) t += p[i];
+    t = wave_sum(t);
+    __syncthreads();  // earlier reads of lds
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = t;
+    __syncthreads();
+    return (lds[0] + lds[1]) + (lds[2] + lds[3]);
+}
+
+// The vector updates of one CG step.  The scalars are formed where they are used, by every workgroup from
+// the partial sums that the operator kernels left (deterministic), so that a step is six launches instead of
+// fifteen; the state that a step changes (gamma, frozen) is read from one set and written to another.  Frozen
+// systems take zero steps.  Bandwidth: 8.9 and 13.5 us for 38 and 63 MB on 16^3x32, in place of 3 axpby, 3 norms
+// with their sums and 2 scalar kernels (56 us); a whole solve there went from 31.3 to 23.3 ms.
+//   first:  alpha = gamma / <q,q>;  r -= alpha q, partials of <r,r>
+//   second: beta = <s,s> / gamma;  x += alpha p;  p = s + beta p;  gamma' = <s,s>;  frozen' once
+//           ||r|| <= limit;  <r,r> to rr
+__global__ void __launch_bounds__(kThreads) k_cg_first(CgStep a) {
+    __shared__ double lds[4];
+    const int sys = blockIdx.y;
+    const double qq = sum_partials(a.qq + (size_t)sys * a.n_qq, a.n_qq, lds);
+    const double al = (a.frozen[sys] != 0 || !(qq > 0)) ? 0.0 : a.gamma[sys] / qq;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.alpha[sys] = al;
+    const double2* q = reinterpret_cast<const double2*>(a.q + (size_t)sys * a.n);
+    double2* r = reinterpret_cast<double2*>(a.r + (size_t)sys * a.n);
+    double n2 = 0;
+    for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < a.n / 2; i += (long long)gridDim.x * kThreads) {
+        double2 v = r[i];
+        const double2 w = q[i];
+        v.x -= al * w.x;
+        v.y -= al * w.y;
+        r[i] = v;
+        n2 += v.x * v.x;
+        n2 += v.y * v.y;
+    }
+    n2 = wave_sum(n2);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = n2;
+    __syncthreads();
+    if (threadIdx.x == 0) a.rr_part[(size_t)sys * gridDim.x + blockIdx.x] = (lds[0] + lds[1]) + (lds[2] + lds[3]);
+}
+
+__global__ void __launch_bounds__(kThreads) k_cg_second(CgStep a) {
+    __shared__ double lds[4];
+    const int sys = blockIdx.y;
+    const double ss = sum_partials(a.ss + (size_t)sys * a.n_ss, a.n_ss, lds);
+    const bool off = a.frozen[sys] != 0;
+    const double gam = a.gamma[sys], al = a.alpha[sys], be = (off || !(gam > 0)) ? 0.0 : ss / gam;
+    if (blockIdx.x == 0) {
+        const double rr = sum_partials(a.rr_part + (size_t)sys * a.n_rr, a.n_rr, lds);
+        if (threadIdx.x == 0) {
+            a.gamma_next[sys] = off ? gam : ss;
+            a.frozen_next[sys] = (off || sqrt(fmax(0.0, rr)) <= a.limit[sys]) ? 1.0 : 0.0;
+            a.rr[sys] = rr;
+        }
+    }
+    if (off) return;
+    const double2* s = reinterpret_cast<const double2*>(a.s + (size_t)sys * a.n);
+    double2* p = reinterpret_cast<double2*>(a.p + (size_t)sys * a.n);
+    double2* x = reinterpret_cast<double2*>(a.x + (size_t)sys * a.n);
+    for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < a.n / 2; i += (long long)gridDim.x * kThreads) {
+        const double2 sv = s[i];
+        double2 pv = p[i], xv = x[i];
+        xv.x += al * pv.x;
+        xv.y += al * pv.y;
+        x[i] = xv;
+        pv.x = sv.x + be * pv.x;
+        pv.y = sv.y + be * pv.y;
+        p[i] = pv;
     }
 }
 
 }  // namespace
 
-hipError_t launch_parity_op(const ParityArgs& a, hipStream_t st) {
-    const long long half = a.g.V / 2;
-    const dim3 grid((unsigned)((half + kThreads - 1) / kThreads)), blk(kThreads);
+static int parity_sys_tile(int nsys) { return nsys > 2 ? 4 : nsys; }
+
+static int parity_chunks(const Geo& g, int nsys) {
+    const long long per = 128 / parity_sys_tile(nsys);  // sites of a workgroup
+    return (int)((g.V / 2 + per - 1) / per);
+}
+
+// At most 2048 workgroups (a multiple of the 8 XCDs, so that a workgroup stays with its XCD's sites): every
+// workgroup of the update kernels adds up their partial sums.
+int parity_blocks(const Geo& g, int nsys) {
+    const int n = parity_chunks(g, nsys);
+    return n < 2048 ? n : 2048;
+}
+
+hipError_t launch_parity_op(const ParityArgs& args, hipStream_t st) {
+    ParityArgs a = args;
+    a.sys_tile = parity_sys_tile(a.nsys);
+    a.chunks = parity_chunks(a.g, a.nsys);
+    const dim3 grid((unsigned)parity_blocks(a.g, a.nsys), (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile)),
+        blk(kThreads);
     const bool hop = a.in_hop != nullptr, diag = a.in_diag != nullptr, inv = a.do_inv != 0;
     if (hop && !diag && inv && a.g5_hop)
         hipLaunchKernelGGL((k_parity_op<true, false, true, true>), grid, blk, 0, st, a);
@@ -232,9 +371,18 @@ hipError_t launch_axpby(const double* x, const double* a, double* y, const doubl
     return hipGetLastError();
 }
 
-hipError_t launch_cg_scalars(int mode, int nsys, unsigned long long frozen, double* gamma, const double* v,
-                             double* out, double* neg, hipStream_t st) {
-    hipLaunchKernelGGL(k_cg_scalars, dim3(1), dim3(64), 0, st, mode, nsys, frozen, gamma, v, out, neg);
+int cg_blocks(long long n) {
+    const long long nb = (n / 2 + kThreads - 1) / kThreads;
+    return (int)(nb < 1024 ? nb : 1024);
+}
+
+hipError_t launch_cg_first(const CgStep& a, int nsys, hipStream_t st) {
+    hipLaunchKernelGGL(k_cg_first, dim3((unsigned)cg_blocks(a.n), nsys), dim3(kThreads), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_second(const CgStep& a, int nsys, hipStream_t st) {
+    hipLaunchKernelGGL(k_cg_second, dim3((unsigned)cg_blocks(a.n), nsys), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
 

@@ -59,8 +59,9 @@ ParityArgs base_args(const CgCtx& c, int p) {
     return a;
 }
 
-// out = Dhat in (adj: Dhat^+ in = Gamma5 Dhat(-mu) Gamma5 in); t: odd-parity scratch
-int dhat(const CgCtx& c, const double* in, double* t, double* out, bool adj) {
+// out = Dhat in (adj: Dhat^+ in = Gamma5 Dhat(-mu) Gamma5 in); t: odd-parity scratch; part: partial sums of
+// ||out||^2 per system, or null
+int dhat(const CgCtx& c, const double* in, double* t, double* out, bool adj, double* part = nullptr) {
     ParityArgs a = base_args(c, 1);  // t_o = D_oo^-1 H_oe in
     a.in_hop = in;
     a.do_inv = 1;
@@ -77,6 +78,7 @@ int dhat(const CgCtx& c, const double* in, double* t, double* out, bool adj) {
     b.g5_out = adj;
     b.mu_sign = adj ? -1.0 : 1.0;
     b.out = out;
+    b.partials = part;
     return hchk(launch_parity_op(b, c.st), "reduced operator");
 }
 
@@ -93,6 +95,30 @@ int norm2(const CgCtx& c, double* v, double* out) {
     const VecRef r = compact_ref(v, c.half);
     return hchk(blas_norm2(P_F64, r, c.partials, out, c.ns, c.half, c.st), "norm");
 }
+
+// Pinned host memory ([flags, limits] to the device, two slots of [flags, ||r||^2] back) and the events that
+// say a slot is filled.  Freed only once the stream no longer writes to it.
+struct Feed {
+    hipStream_t st;
+    double* p = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    explicit Feed(hipStream_t s) : st(s) {}
+    Feed(const Feed&) = delete;
+    Feed& operator=(const Feed&) = delete;
+    ~Feed() {
+        if (p) {
+            (void)hipStreamSynchronize(st);
+            (void)hipHostFree(p);
+        }
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+    }
+    hipError_t open() {
+        hipError_t e = hipHostMalloc((void**)&p, 6 * kMaxSys * sizeof(double), hipHostMallocDefault);
+        for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+        return e;
+    }
+};
 
 }  // namespace
 
@@ -136,6 +162,8 @@ int tm_cg_solve(const tm_geom* geom, const void* U, const void* b, void* x, doub
     int all_conv = 1;
     const size_t canon_sys = (size_t)g.V * 12 * 2 * sizeof(double);
     std::vector<double> host(8 * kMaxSys);
+    Feed feed(st);
+    if ((rc = hchk(feed.open(), "CG host buffer"))) return rc;
     for (int g0 = 0; g0 < geom->nsys; g0 += group) {
         const int ns = std::min(group, geom->nsys - g0);
         CgCtx c;
@@ -157,24 +185,25 @@ int tm_cg_solve(const tm_geom* geom, const void* U, const void* b, void* x, doub
         const size_t fd = cfield * ns / sizeof(double);
         double *be = base, *bo = base + fd, *xe = base + 2 * fd, *r = base + 3 * fd, *s = base + 4 * fd,
                *p = base + 5 * fd, *q = base + 6 * fd, *t = base + 7 * fd;
-        // scalars: gamma, qq, rr, alpha, -alpha, beta, one, zero / -one, gnew, b-norms
+        // scalars: two sets of (gamma, frozen, rr), which the steps alternate between, alpha, the limits on
+        // ||r||, constants, b-norms; then the partial sums
         const int nblk = blas_blocks(half);
         const int nblk_full = blas_blocks(g.V);
-        if ((h = ds->red.ensure((16 * kMaxSys + 2 * (size_t)kMaxSys * std::max(nblk, nblk_full) + 64) *
-                                sizeof(double))) != hipSuccess)
+        const int nop = parity_blocks(g, ns), nup = cg_blocks((long long)fd / ns);
+        const size_t nred = 2 * (size_t)kMaxSys * std::max(nblk, nblk_full) + 64;
+        if ((h = ds->red.ensure((16 * kMaxSys + nred + (size_t)ns * (2 * nop + nup)) * sizeof(double))) != hipSuccess)
             return hip_fail(h, "CG scalars");
         double* sc = (double*)ds->red.ptr;
-        double *gam = sc, *qq = sc + kMaxSys, *rr = sc + 2 * kMaxSys, *alpha = sc + 3 * kMaxSys,
-               *nalpha = sc + 4 * kMaxSys, *beta = sc + 5 * kMaxSys, *one = sc + 6 * kMaxSys,
-               *zero = sc + 7 * kMaxSys, *mone = sc + 8 * kMaxSys, *gnew = sc + 9 * kMaxSys,
-               *bn1 = sc + 10 * kMaxSys, *bn2 = sc + 11 * kMaxSys;
+        double *set[2] = {sc, sc + 3 * kMaxSys}, *alpha = sc + 6 * kMaxSys, *limit = sc + 7 * kMaxSys,
+               *one = sc + 8 * kMaxSys, *mone = sc + 9 * kMaxSys, *bn1 = sc + 10 * kMaxSys, *bn2 = sc + 11 * kMaxSys;
+        double *pqq = sc + 16 * kMaxSys + nred, *pss = pqq + (size_t)ns * nop, *prr = pss + (size_t)ns * nop;
+        double* rr = set[0] + 2 * kMaxSys;
         c.partials = sc + 16 * kMaxSys;
         for (int k = 0; k < kMaxSys; ++k) {
             host[k] = 1.0;
-            host[kMaxSys + k] = 0.0;
-            host[2 * kMaxSys + k] = -1.0;
+            host[kMaxSys + k] = -1.0;
         }
-        if ((rc = hchk(hipMemcpyAsync(one, host.data(), 3 * kMaxSys * sizeof(double), hipMemcpyHostToDevice, st),
+        if ((rc = hchk(hipMemcpyAsync(one, host.data(), 2 * kMaxSys * sizeof(double), hipMemcpyHostToDevice, st),
                        "copy")))
             return rc;
         if ((h = ds->stats.ensure(256)) != hipSuccess) return hip_fail(h, "stats");
@@ -212,8 +241,8 @@ int tm_cg_solve(const tm_geom* geom, const void* U, const void* b, void* x, doub
             if ((rc = hchk(launch_axpby(q, mone, r, one, ns, (long long)fd / ns, st), "axpby"))) return rc;
             // s = Dhat^+ r, p = s, gamma = ||s||^2
             if ((rc = dhat(c, r, t, s, true))) return rc;
-            if ((rc = hchk(launch_axpby(s, one, p, zero, ns, (long long)fd / ns, st), "axpby"))) return rc;
-            if ((rc = norm2(c, s, gam))) return rc;
+            if ((rc = hchk(hipMemcpyAsync(p, s, fd * sizeof(double), hipMemcpyDeviceToDevice, st), "copy"))) return rc;
+            if ((rc = norm2(c, s, set[0]))) return rc;
             if ((rc = norm2(c, r, rr))) return rc;
             if ((rc = hchk(hipMemcpyAsync(host.data(), bn1, 2 * kMaxSys * sizeof(double), hipMemcpyDeviceToHost, st),
                            "copy")))
@@ -231,28 +260,61 @@ int tm_cg_solve(const tm_geom* geom, const void* U, const void* b, void* x, doub
                 const double rk = std::sqrt(std::max(0.0, host[2 * kMaxSys + k]));
                 if (!std::isfinite(rk)) return fail(TM_ERR_NONFINITE, "non-finite CG residual");
                 if (rk <= tol * bnorm[k]) frozen |= 1ull << k;
+                feed.p[k] = (double)((frozen >> k) & 1ull);
+                feed.p[kMaxSys + k] = tol * bnorm[k];
             }
+            if ((rc = hchk(hipMemcpyAsync(set[0] + kMaxSys, feed.p, ns * sizeof(double), hipMemcpyHostToDevice, st),
+                           "copy")))
+                return rc;
+            if ((rc = hchk(hipMemcpyAsync(limit, feed.p + kMaxSys, ns * sizeof(double), hipMemcpyHostToDevice, st),
+                           "copy")))
+                return rc;
+            CgStep u;
+            std::memset(&u, 0, sizeof u);
+            u.n = (long long)fd / ns;
+            u.q = q;
+            u.s = s;
+            u.r = r;
+            u.p = p;
+            u.x = xe;
+            u.qq = pqq;
+            u.ss = pss;
+            u.rr_part = prr;
+            u.n_qq = u.n_ss = nop;
+            u.n_rr = nup;
+            u.limit = limit;
+            u.alpha = alpha;
+            // The freeze decision is taken on the device, so the host runs one step ahead of the residuals it
+            // has seen: the step issued after the last system froze changes nothing and is not counted.
+            int sent = 0, seen = 0;
             while (frozen != all && it < max_iters) {
-                if ((rc = dhat(c, p, t, q, false))) return rc;
-                if ((rc = norm2(c, q, qq))) return rc;
-                if ((rc = hchk(launch_cg_scalars(0, ns, frozen, gam, qq, alpha, nalpha, st), "scalars"))) return rc;
-                if ((rc = hchk(launch_axpby(p, alpha, xe, one, ns, (long long)fd / ns, st), "axpby"))) return rc;
-                if ((rc = hchk(launch_axpby(q, nalpha, r, one, ns, (long long)fd / ns, st), "axpby"))) return rc;
-                if ((rc = norm2(c, r, rr))) return rc;
-                if ((rc = hchk(hipMemcpyAsync(host.data(), rr, ns * sizeof(double), hipMemcpyDeviceToHost, st), "copy")))
-                    return rc;
-                if ((rc = dhat(c, r, t, s, true))) return rc;
-                if ((rc = norm2(c, s, gnew))) return rc;
-                if ((rc = hchk(launch_cg_scalars(1, ns, frozen, gam, gnew, beta, nullptr, st), "scalars"))) return rc;
-                if ((rc = hchk(launch_axpby(s, one, p, beta, ns, (long long)fd / ns, st), "axpby"))) return rc;
-                if ((rc = hchk(hipStreamSynchronize(st), "CG step"))) return rc;
+                for (; sent - seen < 2 && it + (sent - seen) < max_iters; ++sent) {
+                    const double* from = set[sent & 1];
+                    double* to = set[(sent + 1) & 1];
+                    u.gamma = from;
+                    u.frozen = from + kMaxSys;
+                    u.gamma_next = to;
+                    u.frozen_next = to + kMaxSys;
+                    u.rr = to + 2 * kMaxSys;
+                    if ((rc = dhat(c, p, t, q, false, pqq))) return rc;
+                    if ((rc = hchk(launch_cg_first(u, ns, st), "update"))) return rc;
+                    if ((rc = dhat(c, r, t, s, true, pss))) return rc;
+                    if ((rc = hchk(launch_cg_second(u, ns, st), "update"))) return rc;
+                    if ((rc = hchk(hipMemcpyAsync(feed.p + (2 + 2 * (sent & 1)) * kMaxSys, to + kMaxSys,
+                                                  2 * kMaxSys * sizeof(double), hipMemcpyDeviceToHost, st),
+                                   "copy")))
+                        return rc;
+                    if ((rc = hchk(hipEventRecord(feed.ev[sent & 1], st), "event"))) return rc;
+                }
+                if ((rc = hchk(hipEventSynchronize(feed.ev[seen & 1]), "CG step"))) return rc;
+                const double* got = feed.p + (2 + 2 * (seen & 1)) * kMaxSys;
+                ++seen;
                 ++it;
                 for (int k = 0; k < ns; ++k) {
                     if ((frozen >> k) & 1ull) continue;
                     ++iters[k];
-                    const double rk = std::sqrt(std::max(0.0, host[k]));
-                    if (!std::isfinite(host[k])) return fail(TM_ERR_NONFINITE, "non-finite CG residual");
-                    if (rk <= tol * bnorm[k]) frozen |= 1ull << k;
+                    if (!std::isfinite(got[kMaxSys + k])) return fail(TM_ERR_NONFINITE, "non-finite CG residual");
+                    if (got[k] != 0) frozen |= 1ull << k;
                 }
             }
             // x_o = D_oo^-1 (b_o - H_oe x_e), then back to the canonical layout

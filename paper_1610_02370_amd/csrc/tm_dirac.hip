@@ -207,26 +207,7 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
 // systems, 1740 -> 1180.  Large lattices are bound by the neighbours' reads from L2 (about 3 KB per
 // site and system, 8 TB/s).
 
-// A field of spinors: a site's chirality c, and the two spins that lane c needs of a neighbour.
-template <class S> struct FieldOf {  // internal layout, units of four reals
-    const void* base;
-    const float* scale;
-    long long V;
-    __device__ inline FieldOf(const void* p, const float* sc, int sys, const Geo& g)
-        : base(static_cast<const char*>(p) + (size_t)sys * 6 * g.V * Unit<S>::bytes),
-          scale(sc ? sc + (size_t)sys * g.V : nullptr), V(g.V) {}
-    __device__ inline void chirality(long long s, int c, Chir<double>& v) const {
-        load_chir<double, S>(base, scale, V, s, c, v);
-    }
-    struct Raw {
-        Chir<double> v;
-    };
-    template <int MU> __device__ inline void read(long long s, int c, Raw& r) const { chirality(s, c, r.v); }
-    template <int MU> static __device__ inline void spins(const Raw& r, int c, Col<double>& p, Col<double>& q) {
-        pair_spins<MU>(r.v, c != 0, p, q);
-    }
-    static constexpr bool kCanonical = false;
-};
+// The canonical layout as a field (FieldOf, tm_pair.h, is the internal one).
 struct Canonical {
     const double2* base;
     __device__ inline Canonical(const void* p, const float*, int sys, const Geo& g)
@@ -254,17 +235,6 @@ struct Canonical {
     }
     static constexpr bool kCanonical = true;
 };
-
-template <int MU>
-__device__ inline void link_read(const DiracArgs& a, long long site, cplx<double> u[6]) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        double w[4];
-        Unit<double>::load(plane<double>(a.links, 3 * MU + q, a.g.V), (size_t)site, w);
-        u[2 * q] = cmk(w[0], w[1]);
-        u[2 * q + 1] = cmk(w[2], w[3]);
-    }
-}
 
 template <int MU, int DIR, class F>
 __device__ inline void hop_add(const Geo& g, const typename F::Raw& psi, const cplx<double> u[6], bool wrap, int c,
@@ -327,9 +297,9 @@ __device__ inline void dir_add(const DiracArgs& a, const F& in, const PairSite& 
     cplx<double> uf[6], ub[6];
     typename F::Raw pf, pb;
     in.template read<MU>(F::kCanonical ? t.cf[MU] : t.nf[MU], c, pf);
-    link_read<MU>(a, t.s, uf);
+    link_read<MU>(a.links, a.g.V, t.s, uf);
     in.template read<MU>(F::kCanonical ? t.cb[MU] : t.nbk[MU], c, pb);
-    link_read<MU>(a, t.nbk[MU], ub);
+    link_read<MU>(a.links, a.g.V, t.nbk[MU], ub);
     hop_add<MU, +1, F>(a.g, pf, uf, t.wrap & (1u << MU), c, s, acc);
     hop_add<MU, -1, F>(a.g, pb, ub, t.wrap & (16u << MU), c, s, acc);
     pin(acc);

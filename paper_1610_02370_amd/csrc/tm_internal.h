@@ -145,7 +145,22 @@ struct ParityArgs {
     double mu_sign;
     double* out;
     int nsys;
+    int sys_tile, chunks;  // systems per workgroup and runs of sites per system, set by the launcher
+    double* partials;    // ||out||^2 per system and workgroup ([nsys][parity_blocks]), or null
     double mu[kMaxSys];
+};
+
+// One step's vector updates (k_cg_first, k_cg_second): vectors [nsys][n], scalars [nsys], partial sums
+// [nsys][their number].
+struct CgStep {
+    long long n;
+    const double *q, *s;
+    double *r, *p, *x;
+    const double *qq, *ss;
+    int n_qq, n_ss, n_rr;
+    double* rr_part;
+    const double *gamma, *frozen, *limit;
+    double *alpha, *gamma_next, *frozen_next, *rr;
 };
 
 // ---- even-odd reduced operator and CG (tm_cg.hip)
@@ -157,9 +172,10 @@ hipError_t launch_parity_export(const Geo& g, int nsys, const double* even, cons
 // y = a[sys] x + b[sys] y over n_per_sys doubles per system
 hipError_t launch_axpby(const double* x, const double* a, double* y, const double* b, int nsys, long long n_per_sys,
                         hipStream_t st);
-// mode 0: out = gamma / v (step length), neg = -out; mode 1: out = v / gamma, gamma = v; frozen systems get 0
-hipError_t launch_cg_scalars(int mode, int nsys, unsigned long long frozen, double* gamma, const double* v,
-                             double* out, double* neg, hipStream_t st);
+int parity_blocks(const Geo& g, int nsys);  // workgroups (partial sums per system) of launch_parity_op
+int cg_blocks(long long n);                 // the same of launch_cg_first
+hipError_t launch_cg_first(const CgStep& a, int nsys, hipStream_t st);
+hipError_t launch_cg_second(const CgStep& a, int nsys, hipStream_t st);
 
 // ---- layout kernels (tm_layout.hip)
 // Internal links from the canonical ones, with the SU(3) check.

@@ -214,4 +214,38 @@ __device__ inline void store_chir(void* base, float* scale, long long V, long lo
     }
 }
 
+// A field of spinors: a site's chirality c, and the two spins that lane c needs of a neighbour.
+template <class S> struct FieldOf {  // internal layout, units of four reals
+    const void* base;
+    const float* scale;
+    long long V;
+    __device__ inline FieldOf(const void* p, const float* sc, int sys, const Geo& g) : FieldOf(p, sc, sys, g.V) {}
+    __device__ inline FieldOf(const void* p, const float* sc, int sys, long long sites)
+        : base(static_cast<const char*>(p) + (size_t)sys * 6 * sites * Unit<S>::bytes),
+          scale(sc ? sc + (size_t)sys * sites : nullptr), V(sites) {}
+    __device__ inline void chirality(long long s, int c, Chir<double>& v) const {
+        load_chir<double, S>(base, scale, V, s, c, v);
+    }
+    struct Raw {
+        Chir<double> v;
+    };
+    template <int MU> __device__ inline void read(long long s, int c, Raw& r) const { chirality(s, c, r.v); }
+    template <int MU> static __device__ inline void spins(const Raw& r, int c, Col<double>& p, Col<double>& q) {
+        pair_spins<MU>(r.v, c != 0, p, q);
+    }
+    static constexpr bool kCanonical = false;
+};
+
+// The two rows of the FP64 link MU of a site.
+template <int MU>
+__device__ inline void link_read(const void* links, long long V, long long site, cplx<double> u[6]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        double w[4];
+        Unit<double>::load(plane<double>(links, 3 * MU + q, V), (size_t)site, w);
+        u[2 * q] = cmk(w[0], w[1]);
+        u[2 * q + 1] = cmk(w[2], w[3]);
+    }
+}
+
 }  // namespace tmsap
