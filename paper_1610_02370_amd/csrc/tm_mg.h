@@ -90,9 +90,9 @@ hipError_t mg_blas_axpy(const float2* basis, size_t vec_stride, int cnt, const d
 // out[s] = ||w_s||^2
 hipError_t mg_blas_norm2(const float2* w, size_t sys_stride, int nsys, long long n, double* partials, double* out,
                          hipStream_t st);
-// y_s = f[s] x_s (f double in device memory)
-hipError_t mg_blas_scale(const float2* x, const double* f, float2* y, size_t sys_stride, int nsys, long long n,
-                         hipStream_t st);
+// y_s = x_s / sqrt(n2[s]) (n2 in device memory); 0 where n2[s] is 0 or bit s of `off` is set; nsys <= 64
+hipError_t mg_blas_normalize(const float2* x, const double* n2, unsigned long long off, float2* y, size_t sys_stride,
+                             int nsys, long long n, hipStream_t st);
 // y_s = x_s - y_s
 hipError_t mg_blas_sub_from(const float2* x, float2* y, size_t sys_stride, int nsys, long long n, hipStream_t st);
 // Panels of vectors w_s = w + s * w_stride (s < nw <= 4) against one shared basis, each vector read once:

@@ -679,7 +679,6 @@ __global__ void __launch_bounds__(kThreads) k_cdots(const float2* __restrict__ b
     }
 }
 
-// out values (per system, nval consecutive doubles) from the per-workgroup partials, summed in order
 // Panel products for Gram-Schmidt of fields that share one basis: out (s, i) = <v_i, w_s> for
 // i < cnt <= kPanelDots and s < nw <= kPanel, every basis and panel vector read once.
 constexpr int kPanel = 4;
@@ -769,14 +768,24 @@ __global__ void __launch_bounds__(kThreads) k_paxpy(const float2* __restrict__ b
     }
 }
 
-__global__ void k_reduce(const double* __restrict__ partials, int nval, int nblk, int nsys, double* out,
-                         int out_stride) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+// out values (per system, nval consecutive doubles) from the per-workgroup partials: one wavefront per value,
+// summed in a fixed order.  One lane per value walked up to 512 partials one after the other: 26 us against 4.
+__global__ void __launch_bounds__(kThreads) k_reduce(const double* __restrict__ partials, int nval, int nblk,
+                                                     int nsys, double* out, int out_stride) {
+    const int k = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (k >= nval * nsys) return;
     const int sys = k / nval, v = k - sys * nval;
     double t = 0;
-    for (int b = 0; b < nblk; ++b) t += partials[(size_t)k * nblk + b];
-    out[(size_t)sys * out_stride + v] = t;
+    for (int b = lane; b < nblk; b += 64) t += partials[(size_t)k * nblk + b];
+    t = wave_sum_d(t);
+    if (lane == 0) out[(size_t)sys * out_stride + v] = t;
+}
+
+hipError_t reduce(const double* partials, int nval, int nblk, int nsys, double* out, int out_stride, hipStream_t st) {
+    constexpr int per = kThreads / 64;
+    hipLaunchKernelGGL(k_reduce, dim3((nval * nsys + per - 1) / per), dim3(kThreads), 0, st, partials, nval, nblk,
+                       nsys, out, out_stride);
+    return hipGetLastError();
 }
 
 __global__ void __launch_bounds__(kThreads) k_caxpy(const float2* __restrict__ basis, size_t vec_stride, int cnt,
@@ -828,10 +837,13 @@ __global__ void __launch_bounds__(kThreads) k_cnorm2(const float2* __restrict__ 
     }
 }
 
-__global__ void __launch_bounds__(kThreads) k_cscale(const float2* __restrict__ x, const double* __restrict__ f,
-                                                     float2* y, size_t sys_stride, long long n) {
+// y = x / ||x|| from n2 = ||x||^2; 0 for the systems in `off` and for x = 0
+__global__ void __launch_bounds__(kThreads) k_cnormalize(const float2* x, const double* __restrict__ n2,
+                                                         unsigned long long off, float2* y, size_t sys_stride,
+                                                         long long n) {
     const int sys = blockIdx.y;
-    const float a = (float)f[sys];
+    const double q = n2[sys];
+    const float a = (q > 0 && !((off >> sys) & 1ull)) ? (float)(1.0 / sqrt(q)) : 0.f;
     const float4* x4 = reinterpret_cast<const float4*>(x + (size_t)sys * sys_stride);
     float4* y4 = reinterpret_cast<float4*>(y + (size_t)sys * sys_stride);
     for (long long e = (long long)blockIdx.x * kThreads + threadIdx.x; e < n / 2; e += (long long)gridDim.x * kThreads) {
@@ -995,10 +1007,7 @@ hipError_t mg_blas_dots(const float2* basis, size_t vec_stride, int cnt, const f
     const int nblk = mg_blas_blocks(n);
     hipLaunchKernelGGL(k_cdots, dim3(nblk, nsys), dim3(kThreads), 0, st, basis, vec_stride, cnt, w, sys_stride, n,
                        partials);
-    const int tot = 2 * cnt * nsys;
-    hipLaunchKernelGGL(k_reduce, dim3((tot + 63) / 64), dim3(64), 0, st, partials, 2 * cnt, nblk, nsys,
-                       reinterpret_cast<double*>(out), 2 * out_stride);
-    return hipGetLastError();
+    return reduce(partials, 2 * cnt, nblk, nsys, reinterpret_cast<double*>(out), 2 * out_stride, st);
 }
 
 hipError_t mg_blas_axpy(const float2* basis, size_t vec_stride, int cnt, const double2* coef, int coef_stride,
@@ -1014,14 +1023,13 @@ hipError_t mg_blas_norm2(const float2* w, size_t sys_stride, int nsys, long long
     if (n & 1) return hipErrorInvalidValue;
     const int nblk = mg_blas_blocks(n);
     hipLaunchKernelGGL(k_cnorm2, dim3(nblk, nsys), dim3(kThreads), 0, st, w, sys_stride, n, partials);
-    hipLaunchKernelGGL(k_reduce, dim3((nsys + 63) / 64), dim3(64), 0, st, partials, 1, nblk, nsys, out, 1);
-    return hipGetLastError();
+    return reduce(partials, 1, nblk, nsys, out, 1, st);
 }
 
-hipError_t mg_blas_scale(const float2* x, const double* f, float2* y, size_t sys_stride, int nsys, long long n,
-                         hipStream_t st) {
-    if (n & 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_cscale, dim3(mg_blas_blocks(n), nsys), dim3(kThreads), 0, st, x, f, y, sys_stride, n);
+hipError_t mg_blas_normalize(const float2* x, const double* n2, unsigned long long off, float2* y, size_t sys_stride,
+                             int nsys, long long n, hipStream_t st) {
+    if ((n & 1) || nsys > 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_cnormalize, dim3(mg_blas_blocks(n), nsys), dim3(kThreads), 0, st, x, n2, off, y, sys_stride, n);
     return hipGetLastError();
 }
 
@@ -1030,10 +1038,7 @@ hipError_t mg_blas_panel_dots(const float2* basis, size_t vec_stride, int cnt, c
     if (cnt < 1 || cnt > kPanelDots || nw < 1 || nw > kPanel || (n & 1)) return hipErrorInvalidValue;
     const int nblk = mg_blas_blocks(n);
     hipLaunchKernelGGL(k_pdots, dim3(nblk), dim3(kThreads), 0, st, basis, vec_stride, cnt, w, w_stride, nw, n, partials);
-    const int tot = 2 * cnt * nw;
-    hipLaunchKernelGGL(k_reduce, dim3((tot + 63) / 64), dim3(64), 0, st, partials, 2 * cnt, nblk, nw,
-                       reinterpret_cast<double*>(out), 2 * out_stride);
-    return hipGetLastError();
+    return reduce(partials, 2 * cnt, nblk, nw, reinterpret_cast<double*>(out), 2 * out_stride, st);
 }
 
 hipError_t mg_blas_panel_axpy(const float2* basis, size_t vec_stride, int cnt, const double2* coef, int coef_stride,

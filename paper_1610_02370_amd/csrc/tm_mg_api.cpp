@@ -94,10 +94,8 @@ int check_device(const tm_mg* mg) {
 // Small device arrays of one coarse solve over ns systems with restart m.
 struct SmallBufs {
     double* mu;        // [ns]
-    double2* h1;       // [ns][m + 1]
-    double2* h2;       // [ns][m + 1]
-    double* nrm;       // [ns]
-    double* f;         // [ns]
+    double2* h;        // 2 [ns][m + 1], then nrm: a step's coefficients and norms go to the host as one piece
+    double* nrm;       // [ns] (coarse_norms, orthonormalisation)
     double2* y;        // [ns][m]
     double* partials;  // dots / norms
 };
@@ -105,16 +103,14 @@ struct SmallBufs {
 // partials sized for vectors of n complex entries
 int carve_small(tm_mg* mg, int ns, int m, long long n, SmallBufs& s) {
     const size_t nblk = (size_t)mg_blas_blocks(n);
-    const size_t doubles = 3 * (size_t)ns + 2 * 2 * (size_t)ns * (m + 1) + 2 * (size_t)ns * m +
+    const size_t doubles = 3 * (size_t)ns + 4 * (size_t)ns * (m + 1) + 2 * (size_t)ns * m +
                            (size_t)ns * 32 * nblk + 64;
     hipError_t e = mg->small.ensure(doubles * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "two-level scratch");
     double* p = static_cast<double*>(mg->small.ptr);
     s.mu = p; p += ns;
     s.nrm = p; p += ns;
-    s.f = p; p += ns;
-    s.h1 = reinterpret_cast<double2*>(p); p += 2 * (size_t)ns * (m + 1);
-    s.h2 = reinterpret_cast<double2*>(p); p += 2 * (size_t)ns * (m + 1);
+    s.h = reinterpret_cast<double2*>(p); p += 4 * (size_t)ns * (m + 1) + ns;
     s.y = reinterpret_cast<double2*>(p); p += 2 * (size_t)ns * m;
     s.partials = p;
     return TM_OK;
@@ -171,7 +167,7 @@ int gmres_core(tm_mg* mg, int ns, const CoarseOp& A, const double* bref, const f
     float2* w = V + (size_t)(m + 1) * vstride;
     std::vector<double> host(2 * 2 * (size_t)ns * (m + 1) + 4 * (size_t)ns);
     if ((rc = hc(blas_zero(x, (size_t)ns * n * sizeof(float2), st), "zero"))) return rc;
-    std::vector<double> bn(bref, bref + ns), beta(ns), fh(ns);
+    std::vector<double> bn(bref, bref + ns), beta(ns);
     std::vector<zc> H((size_t)ns * (m + 1) * m), sn((size_t)ns * m), gv((size_t)ns * (m + 1));
     std::vector<double> cs((size_t)ns * m);
     std::vector<int> kdim(ns);
@@ -179,68 +175,60 @@ int gmres_core(tm_mg* mg, int ns, const CoarseOp& A, const double* bref, const f
     int steps_max = 0;
     for (int cyc = 0; cyc < maxr; ++cyc) {
         // v0 = b - A x (b itself in the first cycle)
-        if (cyc == 0) {
-            for (int k = 0; k < ns; ++k) host[k] = 1.0;
-            if ((rc = hc(hipMemcpyAsync(sb.f, host.data(), ns * sizeof(double), hipMemcpyHostToDevice, st), "copy")))
-                return rc;
-            if ((rc = hc(mg_blas_scale(b, sb.f, V, vs, ns, n, st), "copy"))) return rc;
-        } else {
+        if (cyc > 0) {
             if ((rc = A(x, V))) return rc;
             if ((rc = hc(mg_blas_sub_from(b, V, vs, ns, n, st), "residual"))) return rc;
         }
-        if ((rc = hc(mg_blas_norm2(V, vs, ns, n, sb.partials, sb.nrm, st), "norm"))) return rc;
+        const float2* r0 = cyc == 0 ? b : V;
+        if ((rc = hc(mg_blas_norm2(r0, vs, ns, n, sb.partials, sb.nrm, st), "norm"))) return rc;
         if ((rc = hc(hipMemcpyAsync(host.data(), sb.nrm, ns * sizeof(double), hipMemcpyDeviceToHost, st), "copy")))
             return rc;
         if ((rc = hc(hipStreamSynchronize(st), "coarse solve"))) return rc;
         bool any = false;
+        unsigned long long off = 0;  // frozen systems get zero directions
         for (int k = 0; k < ns; ++k) {
             beta[k] = std::sqrt(std::max(0.0, host[k]));
             if (!std::isfinite(beta[k])) return fail(TM_ERR_NONFINITE, "non-finite coarse residual (system %d)", k);
             frozen[k] = beta[k] == 0.0 || (tol > 0 && beta[k] <= tol * bn[k]);
             any |= !frozen[k];
-            fh[k] = frozen[k] ? 0.0 : 1.0 / beta[k];
+            if (frozen[k]) off |= 1ull << k;
             for (int i = 0; i <= m; ++i) gv[(size_t)k * (m + 1) + i] = 0.0;
             gv[(size_t)k * (m + 1)] = frozen[k] ? 0.0 : beta[k];
             kdim[k] = 0;
         }
         if (!any) break;
-        if ((rc = hc(hipMemcpyAsync(sb.f, fh.data(), ns * sizeof(double), hipMemcpyHostToDevice, st), "copy"))) return rc;
-        if ((rc = hc(mg_blas_scale(V, sb.f, V, vs, ns, n, st), "scale"))) return rc;
+        if ((rc = hc(mg_blas_normalize(r0, sb.nrm, off, V, vs, ns, n, st), "scale"))) return rc;
         int jdone = 0;
         for (int j = 0; j < m; ++j) {
             float2* vj = V + (size_t)j * vstride;
             if ((rc = A(vj, w))) return rc;
             const int nb = j + 1;
-            if ((rc = basis_dots(V, vstride, nb, w, vs, ns, n, sb.partials, sb.h1, m + 1, st))) return rc;
-            if ((rc = basis_axpy(V, vstride, nb, sb.h1, m + 1, -1.0, w, vs, ns, n, st))) return rc;
-            if ((rc = basis_dots(V, vstride, nb, w, vs, ns, n, sb.partials, sb.h2, m + 1, st))) return rc;
-            if ((rc = basis_axpy(V, vstride, nb, sb.h2, m + 1, -1.0, w, vs, ns, n, st))) return rc;
-            if ((rc = hc(mg_blas_norm2(w, vs, ns, n, sb.partials, sb.nrm, st), "norm"))) return rc;
+            double2 *h1 = sb.h, *h2 = h1 + (size_t)ns * nb;
+            double* nrm = reinterpret_cast<double*>(h2 + (size_t)ns * nb);
+            if ((rc = basis_dots(V, vstride, nb, w, vs, ns, n, sb.partials, h1, nb, st))) return rc;
+            if ((rc = basis_axpy(V, vstride, nb, h1, nb, -1.0, w, vs, ns, n, st))) return rc;
+            if ((rc = basis_dots(V, vstride, nb, w, vs, ns, n, sb.partials, h2, nb, st))) return rc;
+            if ((rc = basis_axpy(V, vstride, nb, h2, nb, -1.0, w, vs, ns, n, st))) return rc;
+            if ((rc = hc(mg_blas_norm2(w, vs, ns, n, sb.partials, nrm, st), "norm"))) return rc;
             double* hh1 = host.data();
-            double* hh2 = hh1 + 2 * (size_t)ns * (m + 1);
-            double* hn2 = hh2 + 2 * (size_t)ns * (m + 1);
-            if ((rc = hc(hipMemcpyAsync(hh1, sb.h1, 2 * (size_t)ns * (m + 1) * sizeof(double), hipMemcpyDeviceToHost, st),
+            double* hh2 = hh1 + 2 * (size_t)ns * nb;
+            double* hn2 = hh2 + 2 * (size_t)ns * nb;
+            if ((rc = hc(hipMemcpyAsync(hh1, h1, (4 * (size_t)ns * nb + ns) * sizeof(double), hipMemcpyDeviceToHost, st),
                          "copy")))
                 return rc;
-            if ((rc = hc(hipMemcpyAsync(hh2, sb.h2, 2 * (size_t)ns * (m + 1) * sizeof(double), hipMemcpyDeviceToHost, st),
-                         "copy")))
-                return rc;
-            if ((rc = hc(hipMemcpyAsync(hn2, sb.nrm, ns * sizeof(double), hipMemcpyDeviceToHost, st), "copy"))) return rc;
             if ((rc = hc(hipStreamSynchronize(st), "coarse Arnoldi step"))) return rc;
             bool all_frozen = true;
             for (int k = 0; k < ns; ++k) {
-                fh[k] = 0.0;
                 if (frozen[k]) continue;
                 zc* Hk = &H[(size_t)k * (m + 1) * m];
                 for (int i = 0; i < nb; ++i) {
-                    const double* a = hh1 + ((size_t)k * (m + 1) + i) * 2;
-                    const double* c2 = hh2 + ((size_t)k * (m + 1) + i) * 2;
+                    const double* a = hh1 + ((size_t)k * nb + i) * 2;
+                    const double* c2 = hh2 + ((size_t)k * nb + i) * 2;
                     Hk[i * m + j] = zc(a[0] + c2[0], a[1] + c2[1]);
                 }
                 const double hn = std::sqrt(std::max(0.0, hn2[k]));
                 if (!std::isfinite(hn)) return fail(TM_ERR_NONFINITE, "non-finite coarse Arnoldi step (system %d)", k);
                 Hk[(j + 1) * m + j] = hn;
-                fh[k] = hn > 0 ? 1.0 / hn : 0.0;
                 double* csk = &cs[(size_t)k * m];
                 zc* snk = &sn[(size_t)k * m];
                 zc* gk = &gv[(size_t)k * (m + 1)];
@@ -265,16 +253,15 @@ int gmres_core(tm_mg* mg, int ns, const CoarseOp& A, const double* bref, const f
                 kdim[k] = j + 1;
                 if ((tol > 0 && std::abs(gk[j + 1]) <= tol * bn[k]) || hn == 0.0) {
                     frozen[k] = 1;
-                    fh[k] = 0.0;
+                    off |= 1ull << k;
                 }
                 all_frozen &= (bool)frozen[k];
             }
             jdone = j + 1;
             ++steps_max;
             if (all_frozen || j + 1 == m) break;
-            if ((rc = hc(hipMemcpyAsync(sb.f, fh.data(), ns * sizeof(double), hipMemcpyHostToDevice, st), "copy")))
+            if ((rc = hc(mg_blas_normalize(w, nrm, off, V + (size_t)(j + 1) * vstride, vs, ns, n, st), "scale")))
                 return rc;
-            if ((rc = hc(mg_blas_scale(w, sb.f, V + (size_t)(j + 1) * vstride, vs, ns, n, st), "scale"))) return rc;
         }
         // x += V y per system (zero beyond its Krylov dimension)
         std::vector<double> yh(2 * (size_t)ns * m, 0.0);
@@ -513,17 +500,18 @@ int orthonormalize_fields(tm_mg* mg, float2* v, int nv, hipStream_t st) {
     int rc;
     if ((rc = carve_small(mg, kPb, kMgMaxVec, n, sb))) return rc;
     const int hs = kMgMaxVec + 1;  // coefficient stride per panel vector
+    double* nrm = reinterpret_cast<double*>(sb.h + (size_t)kPb * hs);  // [nv], behind the coefficients
     for (int p0 = 0; p0 < nv; p0 += kPb) {
         const int pb = std::min(kPb, nv - p0);
         float2* W = v + (size_t)p0 * fs;
         for (int pass = 0; pass < 2 && p0 > 0; ++pass) {
             for (int i0 = 0; i0 < p0; i0 += kPd)
                 if ((rc = hc(mg_blas_panel_dots(v + (size_t)i0 * fs, fs, std::min(kPd, p0 - i0), W, fs, pb, n,
-                                                sb.partials, sb.h1 + i0, hs, st),
+                                                sb.partials, sb.h + i0, hs, st),
                              "panel dots")))
                     return rc;
             for (int i0 = 0; i0 < p0; i0 += kPa)
-                if ((rc = hc(mg_blas_panel_axpy(v + (size_t)i0 * fs, fs, std::min(kPa, p0 - i0), sb.h1 + i0, hs, W,
+                if ((rc = hc(mg_blas_panel_axpy(v + (size_t)i0 * fs, fs, std::min(kPa, p0 - i0), sb.h + i0, hs, W,
                                                 fs, pb, n, st),
                              "panel update")))
                     return rc;
@@ -532,21 +520,19 @@ int orthonormalize_fields(tm_mg* mg, float2* v, int nv, hipStream_t st) {
             float2* vi = v + (size_t)i * fs;
             if (i > p0) {
                 for (int pass = 0; pass < 2; ++pass) {
-                    if ((rc = basis_dots(W, fs, i - p0, vi, 0, 1, n, sb.partials, sb.h1, 0, st))) return rc;
-                    if ((rc = basis_axpy(W, fs, i - p0, sb.h1, 0, -1.0, vi, 0, 1, n, st))) return rc;
+                    if ((rc = basis_dots(W, fs, i - p0, vi, 0, 1, n, sb.partials, sb.h, 0, st))) return rc;
+                    if ((rc = basis_axpy(W, fs, i - p0, sb.h, 0, -1.0, vi, 0, 1, n, st))) return rc;
                 }
             }
-            if ((rc = hc(mg_blas_norm2(vi, 0, 1, n, sb.partials, sb.nrm, st), "norm"))) return rc;
-            double n2 = 0;
-            if ((rc = hc(hipMemcpyAsync(&n2, sb.nrm, sizeof(double), hipMemcpyDeviceToHost, st), "copy"))) return rc;
-            if ((rc = hc(hipStreamSynchronize(st), "orthonormalisation"))) return rc;
-            if (!std::isfinite(n2)) return fail(TM_ERR_NONFINITE, "non-finite test vector %d", i);
-            const double f = n2 > 0 ? 1.0 / std::sqrt(n2) : 0.0;
-            if ((rc = hc(hipMemcpyAsync(sb.f, &f, sizeof(double), hipMemcpyHostToDevice, st), "copy"))) return rc;
-            if ((rc = hc(mg_blas_scale(vi, sb.f, vi, 0, 1, n, st), "scale"))) return rc;
-            if ((rc = hc(hipStreamSynchronize(st), "orthonormalisation"))) return rc;
+            if ((rc = hc(mg_blas_norm2(vi, 0, 1, n, sb.partials, nrm + i, st), "norm"))) return rc;
+            if ((rc = hc(mg_blas_normalize(vi, nrm + i, 0, vi, 0, 1, n, st), "scale"))) return rc;
         }
     }
+    double host[kMgMaxVec];
+    if ((rc = hc(hipMemcpyAsync(host, nrm, nv * sizeof(double), hipMemcpyDeviceToHost, st), "copy"))) return rc;
+    if ((rc = hc(hipStreamSynchronize(st), "orthonormalisation"))) return rc;
+    for (int i = 0; i < nv; ++i)
+        if (!std::isfinite(host[i])) return fail(TM_ERR_NONFINITE, "non-finite test vector %d", i);
     return TM_OK;
 }
 
