@@ -27,17 +27,14 @@ struct MgArgs {
     size_t P_stride;      // bytes between fields
 };
 
-// out_b = term t of D applied to column b of P on every aggregate at once, for b in
-// [b0, b0 + nb): t = 0 the block-diagonal part (the diagonal at mu = 0 plus the
-// parity shift, and the hops inside the aggregate); t = 1 + mu the forward hop along
-// mu where it leaves the aggregate; t = 5 + mu the backward hop likewise.  out holds
-// nb FP32 internal fields.
-hipError_t launch_mg_term(const MgArgs& m, const void* links, const void* clover, int t, int b0, int nb, void* out,
-                          size_t out_stride, hipStream_t st);
-// c[s] = P^+ x_s for nsys FP32 internal fields x: c element (s, j, a) at
-// out[base + s*s_stride + j*j_stride + a] (float2 units).
-hipError_t launch_mg_restrict(const MgArgs& m, const void* x, size_t x_stride, int nsys, float2* out, size_t base,
-                              size_t s_stride, size_t j_stride, hipStream_t st);
+// The 9 stencil matrices of D per aggregate (n2 x n2 each, n2 = 2 nv, column-major, one after the other): t = 0
+// the block-diagonal part (the diagonal at mu = 0 plus the parity shift, and the hops inside the aggregate);
+// t = 1 + mu the forward hop along mu where it leaves the aggregate; t = 5 + mu the backward hop likewise.
+hipError_t launch_mg_stencil(const MgArgs& m, const void* links, const void* clover, float2* Dc, hipStream_t st);
+// c[s] = P^+ x_s for nsys FP32 internal fields x: c element (s, j, a) at out[s*s_stride + j*2nv + a] (float2
+// units).
+hipError_t launch_mg_restrict(const MgArgs& m, const void* x, size_t x_stride, int nsys, float2* out,
+                              size_t s_stride, hipStream_t st);
 // e_s = P c_s (coarse vectors [nsys][nc][2nv]) into nsys FP32 internal fields.
 hipError_t launch_mg_prolong(const MgArgs& m, const float2* c, int nsys, void* e, size_t e_stride, hipStream_t st);
 // Aggregate-wise modified Gram-Schmidt of the nv fields (in place).

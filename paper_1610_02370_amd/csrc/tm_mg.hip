@@ -8,6 +8,8 @@
 // fixed order, so results do not depend on scheduling.
 #include "tm_mg.h"
 
+#include <algorithm>
+
 namespace tmsap {
 
 namespace {
@@ -38,76 +40,6 @@ __device__ inline void load_column(const MgArgs& m, int b, long long y, Spinor<f
     load_spinor<float, float>(field(m.P, m.P_stride, i), nullptr, m.g.V, y, p);
 #pragma unroll
     for (int q = 0; q < 6; ++q) p.v[sg == 0 ? 6 + q : q] = cmk(0.f, 0.f);
-}
-
-template <int T>
-__global__ void __launch_bounds__(kThreads) k_mg_term(MgArgs m, const void* __restrict__ links,
-                                                      const void* __restrict__ clover, int b0, int nb, void* out,
-                                                      size_t out_stride) {
-    constexpr int t = T;
-    const Geo& g = m.g;
-    const long long s = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (s >= g.V) return;
-    int nf[4], nbk[4], par;
-    unsigned wrap;
-    tiled_neighbours(g, s, nf, nbk, &wrap, &par);
-    const unsigned blk = (unsigned)s / (unsigned)g.Vb;
-    constexpr int mu = t == 0 ? 0 : (t - 1) % 4;
-    constexpr bool fwd = t >= 1 && t <= 4;
-    // neighbours along mu picked with static indices (no private-array indexing)
-    int nfm = nf[0], nbm = nbk[0];
-#pragma unroll
-    for (int d = 1; d < 4; ++d)
-        if (d == mu) {
-            nfm = nf[d];
-            nbm = nbk[d];
-        }
-    // the face hop of term t exists at this site only when it leaves the aggregate
-    const bool face = t == 0 ? false : ((unsigned)(fwd ? nfm : nbm) / (unsigned)g.Vb != blk);
-    Clover<float> A;
-    if (t == 0) load_clover<float, float>(clover, g.V, s, A);
-    for (int b = b0; b < b0 + nb; ++b) {
-        Spinor<float> o, h, p;
-#pragma unroll
-        for (int q = 0; q < 12; ++q) o.v[q] = h.v[q] = cmk(0.f, 0.f);
-        if (t == 0) {
-            load_column(m, b, s, p);
-            clover_apply(A, (float)g.mu_shift[par], p, o);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                if ((unsigned)nf[d] / (unsigned)g.Vb == blk) {
-                    Link<float> L;
-                    load_link<float, float>(links, g.V, s, d, L);
-                    load_column(m, b, nf[d], p);
-                    if (wrap & (1u << d)) apply_bc(g, d, +1, p);
-                    hop_forward(d, L, p, 1.f, h);
-                }
-                if ((unsigned)nbk[d] / (unsigned)g.Vb == blk) {
-                    Link<float> L;
-                    load_link<float, float>(links, g.V, nbk[d], d, L);
-                    load_column(m, b, nbk[d], p);
-                    if (wrap & (16u << d)) apply_bc(g, d, -1, p);
-                    hop_backward(d, L, p, 1.f, h);
-                }
-            }
-        } else if (face) {
-            Link<float> L;
-            if (fwd) {
-                load_link<float, float>(links, g.V, s, mu, L);
-                load_column(m, b, nfm, p);
-                if (wrap & (1u << mu)) apply_bc(g, mu, +1, p);
-                hop_forward(mu, L, p, 1.f, h);
-            } else {
-                load_link<float, float>(links, g.V, nbm, mu, L);
-                load_column(m, b, nbm, p);
-                if (wrap & (16u << mu)) apply_bc(g, mu, -1, p);
-                hop_backward(mu, L, p, 1.f, h);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 12; ++q) o.v[q] = o.v[q] - 0.5f * h.v[q];
-        store_spinor<float, float>(static_cast<char*>(out) + (size_t)(b - b0) * out_stride, nullptr, g.V, s, o);
-    }
 }
 
 // Sum over the 64 lanes of a wave of 64 values per lane: after the exchange lane l
@@ -146,35 +78,16 @@ __device__ inline void agg_group(int b, int G, long long nc, int& j, int& grp) {
     j = base + (within - grp * width);
 }
 
-// Restriction of S systems per workgroup (one aggregate of at most NT sites).
-// Per site and test vector the 4 S partial sums (two spin halves, re / im, per
-// system) of 16 / S test vectors at a time go through one wave-level transpose
-// sum; the wave sums meet in LDS.
-template <int S, int NT>
-__global__ void __launch_bounds__(NT) k_mg_restrict(MgArgs m, const void* __restrict__ x, size_t x_stride,
-                                                      int nsys, float2* out, size_t base, size_t s_stride,
-                                                      size_t j_stride) {
+// c[k][a] = <column a of P, x_k> on one aggregate for the S fields xv (their spinor at the thread's site s;
+// `on` marks the threads that hold a site).  Per site and test vector the 4 S partial sums (two spin halves,
+// re / im, per field) of 16 / S test vectors at a time go through one wave-level transpose sum; the wave sums
+// meet in LDS ([waves][chunks][64]).  Field k's coefficients go to out + k * k_stride for k < ns.
+template <int S>
+__device__ inline void restrict_sums(const MgArgs& m, const Spinor<float> (&xv)[S], long long s, bool on, int ns,
+                                     float* red, float2* out, size_t k_stride) {
     constexpr int PER = 16 / S;  // test vectors per 64-value chunk
-    extern __shared__ float red[];  // [waves][chunks][64]
-    const Geo& g = m.g;
-    int j, grp;
-    agg_group(blockIdx.x, (nsys + S - 1) / S, g.V / g.Vb, j, grp);
-    const int l = threadIdx.x;
-    const bool on = l < g.Vb;
-    const long long s = (long long)j * g.Vb + l;
-    const int s0 = grp * S;
-    const int ns = min(S, nsys - s0);
-    const int lane = l & 63, w = l >> 6, nw = blockDim.x >> 6, nv = m.nv;
+    const int l = threadIdx.x, lane = l & 63, w = l >> 6, nw = blockDim.x >> 6, nv = m.nv;
     const int nch = (nv + PER - 1) / PER;
-    Spinor<float> xv[S];
-#pragma unroll
-    for (int k = 0; k < S; ++k) {
-        if (on && k < ns)
-            load_spinor<float, float>(field(x, x_stride, s0 + k), nullptr, g.V, s, xv[k]);
-        else
-#pragma unroll
-            for (int q = 0; q < 12; ++q) xv[k].v[q] = cmk(0.f, 0.f);
-    }
     for (int c = 0; c < nch; ++c) {
         float v[64];
 #pragma unroll
@@ -182,7 +95,7 @@ __global__ void __launch_bounds__(NT) k_mg_restrict(MgArgs m, const void* __rest
             const int i = c * PER + ii;
             Spinor<float> p;
             if (on && i < nv)
-                load_spinor<float, float>(field(m.P, m.P_stride, i), nullptr, g.V, s, p);
+                load_spinor<float, float>(field(m.P, m.P_stride, i), nullptr, m.g.V, s, p);
             else
 #pragma unroll
                 for (int q = 0; q < 12; ++q) p.v[q] = cmk(0.f, 0.f);
@@ -214,8 +127,142 @@ __global__ void __launch_bounds__(NT) k_mg_restrict(MgArgs m, const void* __rest
             re += red[(q * nch + c) * 64 + vi];
             im += red[(q * nch + c) * 64 + vi + 1];
         }
-        out[base + (size_t)(s0 + k) * s_stride + (size_t)j * j_stride + a] = make_float2(re, im);
+        out[(size_t)k * k_stride + a] = make_float2(re, im);
     }
+}
+
+// Restriction of S systems per workgroup (one aggregate of at most NT sites).
+template <int S, int NT>
+__global__ void __launch_bounds__(NT) k_mg_restrict(MgArgs m, const void* __restrict__ x, size_t x_stride,
+                                                      int nsys, float2* out, size_t s_stride) {
+    extern __shared__ float red[];
+    const Geo& g = m.g;
+    int j, grp;
+    agg_group(blockIdx.x, (nsys + S - 1) / S, g.V / g.Vb, j, grp);
+    const bool on = (int)threadIdx.x < g.Vb;
+    const long long s = (long long)j * g.Vb + threadIdx.x;
+    const int s0 = grp * S;
+    const int ns = min(S, nsys - s0);
+    Spinor<float> xv[S];
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        if (on && k < ns)
+            load_spinor<float, float>(field(x, x_stride, s0 + k), nullptr, g.V, s, xv[k]);
+        else
+#pragma unroll
+            for (int q = 0; q < 12; ++q) xv[k].v[q] = cmk(0.f, 0.f);
+    }
+    restrict_sums<S>(m, xv, s, on, ns, red, out + (size_t)s0 * s_stride + (size_t)j * 2 * m.nv, s_stride);
+}
+
+// h_k += the hop along MU of columns b0 .. b0 + ns - 1 of P into site s (from s + mu, or from s - mu)
+template <int MU, bool FWD, int S>
+__device__ inline void add_hop(const MgArgs& m, const void* links, long long s, int nbr, bool wrap, int b0, int ns,
+                               Spinor<float> (&h)[S]) {
+    Link<float> L;
+    load_link<float, float>(links, m.g.V, FWD ? s : (long long)nbr, MU, L);
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        if (k < ns) {
+            Spinor<float> p;
+            load_column(m, b0 + k, nbr, p);
+            if (wrap) apply_bc(m.g, MU, FWD ? +1 : -1, p);
+            if (FWD)
+                hop_forward(MU, L, p, 1.f, h[k]);
+            else
+                hop_backward(MU, L, p, 1.f, h[k]);
+        }
+    }
+}
+
+// Stencil matrices of D on the aggregates: column b of matrix t of aggregate j at Dc + ((j 9 + t) n2 + b) n2 is
+// P^+ (term t of D applied to column b of P), term 0 the block-diagonal part (the diagonal at mu = 0 plus the
+// parity shift, and the hops inside the aggregate), 1 + mu the forward hop along mu where it leaves the
+// aggregate, 5 + mu the backward hop likewise.  A workgroup takes S columns of one term on one aggregate: it
+// forms the term in registers (every (site, column) once) and restricts it there, so the term never goes
+// through memory.  FACE: the threads are the sites of the face that the hop crosses, 1 / extent of the
+// aggregate, instead of all of its sites with zeros inside.  Bound by reading P from L2 once per group of S
+// columns.  16^4 with 4^4 aggregates and 20 vectors: 269 us for term 0 and
+// 326 us for the eight faces, where writing each term as 40 fields and restricting those took 1780 us.
+template <int S, int NT, bool FACE>
+__global__ void __launch_bounds__(NT) k_mg_stencil(MgArgs m, const void* __restrict__ links,
+                                                   const void* __restrict__ clover, float2* Dc) {
+    extern __shared__ float red[];
+    const Geo& g = m.g;
+    const int n2 = 2 * m.nv;
+    int j, grp;
+    agg_group(blockIdx.x, (n2 + S - 1) / S, g.V / g.Vb, j, grp);
+    const int b0 = grp * S, ns = min(S, n2 - b0);
+    const int term = FACE ? 1 + (int)blockIdx.y : 0, mu = (term - 1) & 3;
+    int l = threadIdx.x;
+    bool on = l < g.Vb;
+    if (FACE) {
+        const int axis = axis_of(mu);
+        int lb = 0, nb = 0, inner = 1;  // extent and aggregates along mu, sites per step along mu
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            if (d == axis) {
+                lb = g.lb[d];
+                nb = g.nb[d];
+            }
+            if (d > axis) inner *= g.lb[d];
+        }
+        on = l < g.Vb / lb && nb > 1;
+        l = (l / inner) * inner * lb + (term <= 4 ? lb - 1 : 0) * inner + l % inner;
+    }
+    const long long s = (long long)j * g.Vb + l;
+    Spinor<float> xv[S];
+#pragma unroll
+    for (int k = 0; k < S; ++k)
+#pragma unroll
+        for (int q = 0; q < 12; ++q) xv[k].v[q] = cmk(0.f, 0.f);
+    if (on) {
+        int nf[4], nbk[4], par;
+        unsigned wrap;
+        tiled_neighbours(g, s, nf, nbk, &wrap, &par);
+        if (FACE) {
+            switch (term) {
+                case 1: add_hop<0, true>(m, links, s, nf[0], wrap & 1u, b0, ns, xv); break;
+                case 2: add_hop<1, true>(m, links, s, nf[1], wrap & 2u, b0, ns, xv); break;
+                case 3: add_hop<2, true>(m, links, s, nf[2], wrap & 4u, b0, ns, xv); break;
+                case 4: add_hop<3, true>(m, links, s, nf[3], wrap & 8u, b0, ns, xv); break;
+                case 5: add_hop<0, false>(m, links, s, nbk[0], wrap & 16u, b0, ns, xv); break;
+                case 6: add_hop<1, false>(m, links, s, nbk[1], wrap & 32u, b0, ns, xv); break;
+                case 7: add_hop<2, false>(m, links, s, nbk[2], wrap & 64u, b0, ns, xv); break;
+                default: add_hop<3, false>(m, links, s, nbk[3], wrap & 128u, b0, ns, xv); break;
+            }
+        } else {
+            const unsigned Vb = (unsigned)g.Vb;
+            const auto inside = [&](int n) { return (unsigned)n / Vb == (unsigned)j; };
+            if (inside(nf[0])) add_hop<0, true>(m, links, s, nf[0], wrap & 1u, b0, ns, xv);
+            if (inside(nbk[0])) add_hop<0, false>(m, links, s, nbk[0], wrap & 16u, b0, ns, xv);
+            if (inside(nf[1])) add_hop<1, true>(m, links, s, nf[1], wrap & 2u, b0, ns, xv);
+            if (inside(nbk[1])) add_hop<1, false>(m, links, s, nbk[1], wrap & 32u, b0, ns, xv);
+            if (inside(nf[2])) add_hop<2, true>(m, links, s, nf[2], wrap & 4u, b0, ns, xv);
+            if (inside(nbk[2])) add_hop<2, false>(m, links, s, nbk[2], wrap & 64u, b0, ns, xv);
+            if (inside(nf[3])) add_hop<3, true>(m, links, s, nf[3], wrap & 8u, b0, ns, xv);
+            if (inside(nbk[3])) add_hop<3, false>(m, links, s, nbk[3], wrap & 128u, b0, ns, xv);
+        }
+#pragma unroll
+        for (int k = 0; k < S; ++k)
+#pragma unroll
+            for (int q = 0; q < 12; ++q) xv[k].v[q] = -0.5f * xv[k].v[q];
+        if (!FACE) {
+            Clover<float> A;
+            load_clover<float, float>(clover, g.V, s, A);
+#pragma unroll
+            for (int k = 0; k < S; ++k) {
+                if (k < ns) {
+                    Spinor<float> p, o;
+                    load_column(m, b0 + k, s, p);
+                    clover_apply(A, (float)g.mu_shift[par], p, o);
+#pragma unroll
+                    for (int q = 0; q < 12; ++q) xv[k].v[q] = o.v[q] + xv[k].v[q];
+                }
+            }
+        }
+    }
+    restrict_sums<S>(m, xv, s, on, ns, red, Dc + (((size_t)j * 9 + term) * n2 + b0) * n2, (size_t)n2);
 }
 
 template <int S, int NT>
@@ -867,39 +914,47 @@ int agg_threads(const Geo& g) { return (g.Vb + 63) & ~63; }
 
 }  // namespace
 
-hipError_t launch_mg_term(const MgArgs& m, const void* links, const void* clover, int t, int b0, int nb, void* out,
-                          size_t out_stride, hipStream_t st) {
-    if (t < 0 || t > 8 || nb <= 0) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((m.g.V + kThreads - 1) / kThreads)), blk(kThreads);
-    switch (t) {
-        case 0: hipLaunchKernelGGL(k_mg_term<0>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        case 1: hipLaunchKernelGGL(k_mg_term<1>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        case 2: hipLaunchKernelGGL(k_mg_term<2>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        case 3: hipLaunchKernelGGL(k_mg_term<3>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        case 4: hipLaunchKernelGGL(k_mg_term<4>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        case 5: hipLaunchKernelGGL(k_mg_term<5>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        case 6: hipLaunchKernelGGL(k_mg_term<6>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        case 7: hipLaunchKernelGGL(k_mg_term<7>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-        default: hipLaunchKernelGGL(k_mg_term<8>, grid, blk, 0, st, m, links, clover, b0, nb, out, out_stride); break;
-    }
+namespace {
+
+// Systems or columns per workgroup: 4 for aggregates (faces) of up to 256 sites, 1 for larger ones (registers).
+size_t restrict_lds(int nt, int nv, int S) { return (size_t)(nt / 64) * ((nv + 16 / S - 1) / (16 / S)) * 64 * sizeof(float); }
+
+}  // namespace
+
+hipError_t launch_mg_stencil(const MgArgs& m, const void* links, const void* clover, float2* Dc, hipStream_t st) {
+    const int nt = agg_threads(m.g), n2 = 2 * m.nv;
+    if (nt > 1024 || m.nv < 1 || m.nv > kMgMaxVec) return hipErrorInvalidValue;
+    const long long nc = m.g.V / m.g.Vb;
+    int face = 1;  // sites of the largest face
+    for (int d = 0; d < 4; ++d) face = std::max(face, m.g.Vb / m.g.lb[d]);
+    const int nf = (face + 63) & ~63;
+    if (nt <= 256)
+        hipLaunchKernelGGL((k_mg_stencil<4, 256, false>), dim3((unsigned)(nc * ((n2 + 3) / 4))), dim3(nt),
+                           restrict_lds(nt, m.nv, 4), st, m, links, clover, Dc);
+    else
+        hipLaunchKernelGGL((k_mg_stencil<1, 1024, false>), dim3((unsigned)(nc * n2)), dim3(nt),
+                           restrict_lds(nt, m.nv, 1), st, m, links, clover, Dc);
+    if (nf <= 256)
+        hipLaunchKernelGGL((k_mg_stencil<4, 256, true>), dim3((unsigned)(nc * ((n2 + 3) / 4)), 8), dim3(nf),
+                           restrict_lds(nf, m.nv, 4), st, m, links, clover, Dc);
+    else
+        hipLaunchKernelGGL((k_mg_stencil<1, 1024, true>), dim3((unsigned)(nc * n2), 8), dim3(nf),
+                           restrict_lds(nf, m.nv, 1), st, m, links, clover, Dc);
     return hipGetLastError();
 }
 
-// Aggregates of up to 256 sites take 4 systems per workgroup, larger ones 1 (register budget).
-hipError_t launch_mg_restrict(const MgArgs& m, const void* x, size_t x_stride, int nsys, float2* out, size_t base,
-                              size_t s_stride, size_t j_stride, hipStream_t st) {
+hipError_t launch_mg_restrict(const MgArgs& m, const void* x, size_t x_stride, int nsys, float2* out,
+                              size_t s_stride, hipStream_t st) {
     const int nt = agg_threads(m.g);
     if (nt > 1024 || m.nv < 1 || m.nv > kMgMaxVec || nsys < 1) return hipErrorInvalidValue;
     const int S = nt <= 256 ? 4 : 1;
-    const int nch = (m.nv + 16 / S - 1) / (16 / S);
-    const size_t lds = (size_t)(nt / 64) * nch * 64 * sizeof(float);
     const dim3 grid((unsigned)(m.g.V / m.g.Vb * ((nsys + S - 1) / S)));
     if (nt <= 256)
-        hipLaunchKernelGGL((k_mg_restrict<4, 256>), grid, dim3(nt), lds, st, m, x, x_stride, nsys, out, base,
-                           s_stride, j_stride);
+        hipLaunchKernelGGL((k_mg_restrict<4, 256>), grid, dim3(nt), restrict_lds(nt, m.nv, 4), st, m, x, x_stride, nsys,
+                           out, s_stride);
     else
-        hipLaunchKernelGGL((k_mg_restrict<1, 1024>), grid, dim3(nt), lds, st, m, x, x_stride, nsys, out, base,
-                           s_stride, j_stride);
+        hipLaunchKernelGGL((k_mg_restrict<1, 1024>), grid, dim3(nt), restrict_lds(nt, m.nv, 1), st, m, x, x_stride,
+                           nsys, out, s_stride);
     return hipGetLastError();
 }
 

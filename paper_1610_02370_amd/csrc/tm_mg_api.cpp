@@ -456,7 +456,7 @@ int mg_apply(tm_mg* mg, DeviceState* ds, const SpinorBuf& r, const SpinorBuf& z,
     float2* ec = c + (size_t)ns * n;
     const MgArgs ma = margs(mg);
     const size_t fb = internal_bytes(mg->g, 1, P_F32);
-    if ((rc = hc(launch_mg_restrict(ma, r.data, fb, ns, c, 0, (size_t)n, (size_t)mg->n2, st), "restriction"))) return rc;
+    if ((rc = hc(launch_mg_restrict(ma, r.data, fb, ns, c, (size_t)n, st), "restriction"))) return rc;
     std::vector<double> muc(ns);
     for (int k = 0; k < ns; ++k) muc[k] = mg->p.delta * mu[k];
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -537,24 +537,14 @@ int orthonormalize_fields(tm_mg* mg, float2* v, int nv, hipStream_t st) {
 }
 
 // P = aggregate-wise orthonormalised copy of the fields v; then the stencil.
-int build_coarse(tm_mg* mg, const GaugeDev& G, const void* v, void* W, int chunk, hipStream_t st) {
+int build_coarse(tm_mg* mg, const GaugeDev& G, const void* v, hipStream_t st) {
     int rc;
-    const int nv = mg->p.n_vec, n2 = mg->n2;
+    const int nv = mg->p.n_vec;
     if ((rc = hc(hipMemcpyAsync(mg->P.ptr, v, (size_t)nv * mg->field, hipMemcpyDeviceToDevice, st), "copy"))) return rc;
     const MgArgs ma = margs(mg);
     for (int k = 0; k < kMgMaxInv; ++k) mg->inv_ok[k] = false;  // the block inverses follow the stencil
     if ((rc = hc(launch_mg_block_orthonormalize(ma, mg->P.ptr, st), "aggregate orthonormalisation"))) return rc;
-    const size_t fb = internal_bytes(mg->g, 1, P_F32);
-    for (int t = 0; t < 9; ++t)
-        for (int b0 = 0; b0 < n2; b0 += chunk) {
-            const int nb = std::min(chunk, n2 - b0);
-            if ((rc = hc(launch_mg_term(ma, G.links, G.clover, t, b0, nb, W, fb, st), "coarse stencil terms"))) return rc;
-            if ((rc = hc(launch_mg_restrict(ma, W, fb, nb, static_cast<float2*>(mg->Dc.ptr),
-                                            (size_t)t * n2 * n2 + (size_t)b0 * n2, (size_t)n2, (size_t)9 * n2 * n2, st),
-                         "coarse stencil")))
-                return rc;
-        }
-    return TM_OK;
+    return hc(launch_mg_stencil(ma, G.links, G.clover, static_cast<float2*>(mg->Dc.ptr), st), "coarse stencil");
 }
 
 int check_params(const tm_geom* geom, const tm_mg_params* p, int tile[4]) {
@@ -668,22 +658,11 @@ int tm_mg_setup(const tm_geom* geom, const void* U, double kappa, double c_sw, c
     if ((e = mg->P.ensure((size_t)nv * mg->field)) != hipSuccess) return hip_fail(e, "basis P");
     if ((e = mg->Dc.ensure((size_t)mg->nc * 9 * mg->n2 * mg->n2 * sizeof(float2))) != hipSuccess)
         return hip_fail(e, "coarse stencil");
-    // fine workspace: the vectors, their next iterate, and the stencil-term chunk; all 2 N_v
-    // columns of a term at once when the device has room (each restriction then reads P once
-    // per term), else 16 at a time
+    // fine workspace: the vectors and their next iterate
     const size_t vbytes = (size_t)nv * mg->field;
-    int chunk = std::min(mg->n2, 16);
-    {
-        size_t free_b = 0, total_b = 0;
-        const size_t coarse_ws = (2 + coarse_work_vectors(mg.get(), params->coarse_restart)) * (size_t)nv *
-                                 (size_t)(mg->nc * mg->n2) * sizeof(float2);
-        const size_t need = 2 * vbytes + (size_t)mg->n2 * mg->field + coarse_ws + (size_t(4) << 30);
-        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && need <= free_b) chunk = mg->n2;
-    }
-    if ((e = mg->fine.ensure(2 * vbytes + (size_t)chunk * mg->field)) != hipSuccess) return hip_fail(e, "setup workspace");
+    if ((e = mg->fine.ensure(2 * vbytes)) != hipSuccess) return hip_fail(e, "setup workspace");
     char* vcur = static_cast<char*>(mg->fine.ptr);
     char* vnext = vcur + vbytes;
-    char* W = vnext + vbytes;
     if ((e = ds->stats.ensure(256)) != hipSuccess) return hip_fail(e, "stats");
     unsigned* flag = (unsigned*)ds->stats.ptr + 2;
     if ((rc = hc(hipMemsetAsync(flag, 0, sizeof(unsigned), st), "flag"))) return rc;
@@ -703,7 +682,7 @@ int tm_mg_setup(const tm_geom* geom, const void* U, double kappa, double c_sw, c
         if (rc) return rc;
         std::swap(vcur, vnext);
         if ((rc = orthonormalize_fields(mg.get(), reinterpret_cast<float2*>(vcur), nv, st))) return rc;
-        if ((rc = build_coarse(mg.get(), *G, vcur, W, chunk, st))) return rc;
+        if ((rc = build_coarse(mg.get(), *G, vcur, st))) return rc;
         if (verbose()) {
             (void)hipStreamSynchronize(st);
             std::fprintf(stderr, "[tm] two-level setup iteration %d of %d done at %.2f s\n", it, params->setup_iters,
@@ -711,9 +690,9 @@ int tm_mg_setup(const tm_geom* geom, const void* U, double kappa, double c_sw, c
             std::fflush(stderr);
         }
     }
-    if (params->setup_iters == 0 && (rc = build_coarse(mg.get(), *G, vcur, W, chunk, st))) return rc;
+    if (params->setup_iters == 0 && (rc = build_coarse(mg.get(), *G, vcur, st))) return rc;
     if ((rc = hc(hipStreamSynchronize(st), "setup"))) return rc;
-    // the setup's workspaces (test vectors, stencil terms, the coarse basis for n_vec systems)
+    // the setup's workspaces (test vectors, the coarse basis for n_vec systems)
     // are not needed by the solves
     mg->fine.release();
     mg->coarse.release();
@@ -771,7 +750,7 @@ int tm_mg_restrict(tm_mg* mg, int nsys, const void* r, void* c, const tm_opts* o
     if ((rc = hc(launch_spinor_import(mg->g, wrap_internal(ds->io.ptr, mg->g, nsys, P_F32), r, (unsigned*)ds->stats.ptr + 2,
                                       st), "import")))
         return rc;
-    if ((rc = hc(launch_mg_restrict(margs(mg), ds->io.ptr, mg->field, nsys, cv, 0, (size_t)n, (size_t)mg->n2, st),
+    if ((rc = hc(launch_mg_restrict(margs(mg), ds->io.ptr, mg->field, nsys, cv, (size_t)n, st),
                  "restriction")))
         return rc;
     return hc(launch_mg_coarse_export(cv, c, (long long)nsys * n, st), "export");

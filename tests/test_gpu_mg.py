@@ -255,3 +255,20 @@ def test_solve_rejects_a_mismatched_handle():
         tm.tm_fgmres_solve(dims, dev(U), dev(b), x, KAPPA, [0.01], CSW, 1e-10, storage="f64", antiperiodic_t=True,
                            theta=THETA, mu_shift=SHIFT, mg=g)
     assert e.value.code == -4
+
+
+# Stencil kernels by aggregate and face size: faces of 96, 64 and 48 sites next to 192-site aggregates (a
+# partial wavefront each), and faces of 512 sites (one column per workgroup) of 1024-site aggregates.
+@pytest.mark.parametrize("dims,adims,nv", [((4, 8, 8, 12), (2, 4, 4, 6), 5), ((4, 16, 16, 16), (2, 8, 8, 8), 3)])
+def test_stencil_face_sizes(dims, adims, nv):
+    U = synth.gauge_field(dims, 0.6, seed=7)
+    v0 = synth.gaussian_spinor(dims, nv, seed=107)
+    announce(f"stencil faces dims={dims} aggregates={adims}")
+    g = tm.MG(dims, dev(U), KAPPA, 0.01, CSW, dev(v0), antiperiodic_t=True, theta=THETA, mu_shift=SHIFT,
+              block_dims=adims, n_vec=nv, setup_iters=0, coarse_eo=0)
+    op = oracle.Operator(dims, U, oracle.kappa_to_m(KAPPA), 0.01, CSW, antiperiodic_t=True, theta=THETA,
+                         mu_shift=SHIFT)
+    o = oracle.MG(op, adims, nv, setup_iters=0, coarse_eo=False)
+    o.setup(v0)
+    Dc = host(g.export()[1])
+    assert np.abs(Dc - o.Dc).max() < 1e-5 * np.abs(o.Dc).max()
