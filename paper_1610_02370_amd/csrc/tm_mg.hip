@@ -15,7 +15,10 @@ namespace tmsap {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kCoarseSys = 16;  // systems per coarse-operator workgroup
+// Coarse operator: up to this many <4, 1024> workgroups (4 per CU) that form runs.  20 test vectors, 3 / 8 / 16
+// systems, <4, 1024> against <16, 256>: 256 sites 13 / 19 / 33 us against 23 / 35 / 56, 512 sites 19 / 35 / 64
+// against 28 / 42 / 60, 1024 sites 34 / 63 / 119 against 34 / 48 / 115.
+constexpr int kCoarseFill = 1024;
 constexpr int kDots = 16;       // basis vectors per dot / axpy pass
 
 __device__ inline float wave_sum(float v) {
@@ -383,18 +386,22 @@ __device__ inline int coarse_parity(const Geo& g, long long j) {
     return sum & 1;
 }
 
-// One workgroup per coarse site and group of kCoarseSys systems.  The 9 stencil
+// One workgroup of NT threads per coarse site and group of KS systems.  The 9 stencil
 // matrices of the site are 9 * n2 columns of n2 complex numbers, stored one after
 // the other; thread t takes the row pair (2p, 2p + 1) with p = t % nv of the columns
-// c = t / nv, t / nv + G, ... (G = 256 / nv column groups), so a wavefront reads
+// c = t / nv, t / nv + G, ... (G = NT / nv column groups), so a wavefront reads
 // consecutive 16-byte pieces and every thread has its own stream of loads.  The
 // neighbours' x are staged in LDS; the column groups' partial sums meet there too.
+// <16, 256> reads the stencil once for up to 16 systems, the bound where the coarse lattice fills the device;
+// <4, 1024> is for the coarse lattices that do not, where a thread's 30 loads one batch after the other were
+// the time: 26 us on 128 sites, 13.4 now.
 // General form: y = add + (self term + i mu_c Gamma5c) x_self + hop_sign * (8 neighbour terms) x_hop
 // on the coarse sites of `parity` (all sites when parity < 0); a null input drops its terms, a
 // null mu_c the twist.  The other parity's sites get 0 when zero_other is set, else stay as they are.
 // With a parity the grid covers site pairs (2b, 2b + 1), one of each parity since the innermost
 // coarse extent is even: the workgroup computes its pair's site of `parity` (and zeroes the other).
-__global__ void __launch_bounds__(kThreads) k_mg_coarse_apply(Geo g, int nv, const float2* __restrict__ Dc,
+template <int KS, int NT>
+__global__ void __launch_bounds__(NT) k_mg_coarse_apply(Geo g, int nv, const float2* __restrict__ Dc,
                                                               const double* __restrict__ mu_c,
                                                               const float2* __restrict__ x_self,
                                                               const float2* __restrict__ x_hop, float hop_sign,
@@ -403,13 +410,13 @@ __global__ void __launch_bounds__(kThreads) k_mg_coarse_apply(Geo g, int nv, con
     // xs [9][ks][n2]; then [G][ks][n2] partial sums, ks = systems per workgroup (LDS sized by it)
     extern __shared__ float2 sh[];
     const int n2 = 2 * nv;
-    const int ks = min(kCoarseSys, nsys);
+    const int ks = min(KS, nsys);
     const long long nc = g.V / g.Vb;
-    const int s0 = blockIdx.y * kCoarseSys;
-    const int ns = min(kCoarseSys, nsys - s0);
+    const int s0 = blockIdx.y * KS;
+    const int ns = min(KS, nsys - s0);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // one (term, system) row per wavefront
-    constexpr int kWaves = kThreads / 64;
+    constexpr int kWaves = NT / 64;
     long long j = blockIdx.x;
     if (parity >= 0) {
         const long long j0 = 2 * (long long)blockIdx.x;
@@ -457,11 +464,11 @@ __global__ void __launch_bounds__(kThreads) k_mg_coarse_apply(Geo g, int nv, con
         }
     }
     __syncthreads();
-    const int G = kThreads / nv;
+    const int G = NT / nv;
     const int p = tid % nv, grp = tid / nv;
-    float2 acc0[kCoarseSys], acc1[kCoarseSys];
+    float2 acc0[KS], acc1[KS];
 #pragma unroll
-    for (int k = 0; k < kCoarseSys; ++k) acc0[k] = acc1[k] = make_float2(0.f, 0.f);
+    for (int k = 0; k < KS; ++k) acc0[k] = acc1[k] = make_float2(0.f, 0.f);
     if (grp < G) {
         const float4* A = reinterpret_cast<const float4*>(Dc + (size_t)j * 9 * n2 * n2);
         const int c_lo = x_self ? 0 : n2, c_hi = x_hop ? 9 * n2 : n2;
@@ -479,7 +486,7 @@ __global__ void __launch_bounds__(kThreads) k_mg_coarse_apply(Geo g, int nv, con
                 ++t;
             }
 #pragma unroll
-            for (int k = 0; k < kCoarseSys; ++k) {
+            for (int k = 0; k < KS; ++k) {
                 if (k < ns) {
                     const float2 xv = xs[k * n2];
                     // one product per statement: each becomes one fused multiply-add
@@ -498,7 +505,7 @@ __global__ void __launch_bounds__(kThreads) k_mg_coarse_apply(Geo g, int nv, con
     __syncthreads();
     if (grp < G)
 #pragma unroll
-        for (int k = 0; k < kCoarseSys; ++k)
+        for (int k = 0; k < KS; ++k)
             if (k < ns) {
                 sh[(grp * ks + k) * n2 + 2 * p] = acc0[k];
                 sh[(grp * ks + k) * n2 + 2 * p + 1] = acc1[k];
@@ -612,51 +619,65 @@ __global__ void __launch_bounds__(kThreads) k_mg_block_inverse(Geo g, int nv, co
 }
 
 // y_s = Minv_{sel[s]} x_s at the coarse sites of `parity` (the others get 0 when zero_other
-// is set, else stay as they are).  One 64-lane workgroup per site pair (2b, 2b + 1), whose
-// site of `parity` has inverse b; one lane per row; the systems of one inverse set go in
-// chunks of kBlockMulSys, so each inverse is read from memory once per call.
+// is set, else stay as they are).  One workgroup per site pair (2b, 2b + 1), whose site of
+// `parity` has inverse b, and run of up to kBlockMulSys systems of one inverse set.  Each of its four
+// wavefronts takes a quarter of the columns, one lane per row, and has all of its loads in flight before the
+// first product; the quarters meet in LDS.  One wavefront walking all columns waited for each load in turn:
+// 31 us for 128 sites of 40 components and up to 20 systems, 6 now.
 constexpr int kBlockMulSys = 8;
-__global__ void __launch_bounds__(64) k_mg_block_mul(BlockMulArgs a) {
+__global__ void __launch_bounds__(256) k_mg_block_mul(BlockMulArgs a) {
+    constexpr int kCols = kMgMaxVec / 2;  // columns of a wavefront, at most
     __shared__ float2 xs[kBlockMulSys][64];
+    __shared__ float2 part[4][kBlockMulSys][64];
     const Geo& g = a.g;
     const long long j0 = 2 * (long long)blockIdx.x;
     const long long j = coarse_parity(g, j0) == a.parity ? j0 : j0 + 1;
-    const int lane = threadIdx.x, n2 = 2 * a.nv;
+    const int lane = threadIdx.x & 63, n2 = 2 * a.nv;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long long nc = g.V / g.Vb;
-    if (a.zero_other && lane < n2) {
-        const long long jo = 2 * j0 + 1 - j;
-        for (int s = 0; s < a.nsys; ++s) a.y[((size_t)s * nc + jo) * n2 + lane] = make_float2(0.f, 0.f);
+    int set = 0, c0 = 0;  // this workgroup's inverse set and first system
+    for (int run = blockIdx.y;; ++set) {
+        const int runs = (a.start[set + 1] - a.start[set] + kBlockMulSys - 1) / kBlockMulSys;
+        if (run < runs) {
+            c0 = a.start[set] + run * kBlockMulSys;
+            break;
+        }
+        run -= runs;
     }
-    for (int q = 0; q < kMgMaxInv; ++q) {
-        if (a.start[q] == a.start[q + 1]) continue;
-        const float2* M = a.sets[q] + (size_t)blockIdx.x * n2 * n2 + lane;
-        for (int c0 = a.start[q]; c0 < a.start[q + 1]; c0 += kBlockMulSys) {
-            const int cn = min(kBlockMulSys, a.start[q + 1] - c0);
-            __syncthreads();
-            if (lane < n2)
-                for (int k = 0; k < cn; ++k) xs[k][lane] = a.x[((size_t)a.order[c0 + k] * nc + j) * n2 + lane];
-            __syncthreads();
-            if (lane < n2) {
-                float2 acc[kBlockMulSys];
+    const int cn = min(kBlockMulSys, a.start[set + 1] - c0);
+    const int per = (n2 + 3) / 4, b0 = w * per, nb = min(per, n2 - b0);
+    const float2* M = a.sets[set] + ((size_t)blockIdx.x * n2 + b0) * n2 + lane;
+    float2 m[kCols];
 #pragma unroll
-                for (int k = 0; k < kBlockMulSys; ++k) acc[k] = make_float2(0.f, 0.f);
-                for (int b = 0; b < n2; ++b) {
-                    const float2 m = M[(size_t)b * n2];
+    for (int b = 0; b < kCols; ++b) m[b] = b < nb && lane < n2 ? M[(size_t)b * n2] : make_float2(0.f, 0.f);
+    if (lane < n2)
+        for (int k = w; k < cn; k += 4) {
+            const size_t at = (size_t)a.order[c0 + k] * nc;
+            xs[k][lane] = a.x[(at + j) * n2 + lane];
+            if (a.zero_other) a.y[(at + (2 * j0 + 1 - j)) * n2 + lane] = make_float2(0.f, 0.f);
+        }
+    __syncthreads();
+    for (int k = 0; k < cn; ++k) {
+        float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
-                    for (int k = 0; k < kBlockMulSys; ++k) {
-                        const float2 v = xs[k][b];
-                        acc[k].x = acc[k].x + m.x * v.x;  // one fused multiply-add per product
-                        acc[k].x = acc[k].x - m.y * v.y;
-                        acc[k].y = acc[k].y + m.x * v.y;
-                        acc[k].y = acc[k].y + m.y * v.x;
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < kBlockMulSys; ++k)
-                    if (k < cn) a.y[((size_t)a.order[c0 + k] * nc + j) * n2 + lane] = acc[k];
+        for (int b = 0; b < kCols; ++b) {
+            if (b < nb) {
+                const float2 v = xs[k][b0 + b];
+                acc.x = acc.x + m[b].x * v.x;  // one fused multiply-add per product
+                acc.x = acc.x - m[b].y * v.y;
+                acc.y = acc.y + m[b].x * v.y;
+                acc.y = acc.y + m[b].y * v.x;
             }
         }
+        part[w][k][lane] = acc;
     }
+    __syncthreads();
+    if (lane < n2)
+        for (int k = w; k < cn; k += 4) {
+            const float2 p0 = part[0][k][lane], p1 = part[1][k][lane], p2 = part[2][k][lane], p3 = part[3][k][lane];
+            a.y[((size_t)a.order[c0 + k] * nc + j) * n2 + lane] =
+                make_float2((p0.x + p1.x) + (p2.x + p3.x), (p0.y + p1.y) + (p2.y + p3.y));
+        }
 }
 
 __global__ void k_mg_stencil_export(long long nc, int nv, const float2* __restrict__ Dc, double2* out) {
@@ -978,24 +999,38 @@ hipError_t launch_mg_block_orthonormalize(const MgArgs& m, void* P, hipStream_t 
     return hipGetLastError();
 }
 
+namespace {
+
+template <int KS, int NT>
+hipError_t coarse_part(const Geo& g, int nv, const float2* Dc, const double* mu_c, const float2* x_self,
+                       const float2* x_hop, double hop_sign, const float2* add, int parity, bool zero_other, float2* y,
+                       int nsys, hipStream_t st) {
+    const int n2 = 2 * nv, ks = nsys < KS ? nsys : KS;
+    const size_t xs = (size_t)9 * ks * n2, red = (size_t)(NT / nv) * ks * n2;
+    const size_t lds = (xs > red ? xs : red) * sizeof(float2);  // at most 9 * 16 * 64 * 8 = 72 KiB
+    if (lds > 65536) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mg_coarse_apply<KS, NT>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    const long long nc = g.V / g.Vb;
+    const dim3 grid((unsigned)(parity >= 0 ? nc / 2 : nc), (unsigned)((nsys + KS - 1) / KS));
+    hipLaunchKernelGGL((k_mg_coarse_apply<KS, NT>), grid, dim3(NT), lds, st, g, nv, Dc, mu_c, x_self, x_hop,
+                       (float)hop_sign, add, parity, (int)zero_other, y, nsys);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_mg_coarse_part(const Geo& g, int nv, const float2* Dc, const double* mu_c, const float2* x_self,
                                  const float2* x_hop, double hop_sign, const float2* add, int parity, bool zero_other,
                                  float2* y, int nsys, hipStream_t st) {
     if (nv < 1 || nv > kMgMaxVec || nsys < 1 || nsys > kMaxSys) return hipErrorInvalidValue;
-    const int n2 = 2 * nv, ks = nsys < kCoarseSys ? nsys : kCoarseSys;
-    const size_t xs = (size_t)9 * ks * n2, red = (size_t)(kThreads / nv) * ks * n2;
-    const size_t lds = (xs > red ? xs : red) * sizeof(float2);  // at most 9 * 16 * 64 * 8 = 72 KiB
-    if (lds > 65536) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mg_coarse_apply),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
     if (parity >= 0 && g.nb[3] % 2 != 0) return hipErrorInvalidValue;
-    const long long nc = g.V / g.Vb;
-    const dim3 grid((unsigned)(parity >= 0 ? nc / 2 : nc), (unsigned)((nsys + kCoarseSys - 1) / kCoarseSys));
-    hipLaunchKernelGGL(k_mg_coarse_apply, grid, dim3(kThreads), lds, st, g, nv, Dc, mu_c, x_self, x_hop,
-                       (float)hop_sign, add, parity, (int)zero_other, y, nsys);
-    return hipGetLastError();
+    const long long sites = parity >= 0 ? g.V / g.Vb / 2 : g.V / g.Vb;
+    if (sites * ((nsys + 3) / 4) <= kCoarseFill)
+        return coarse_part<4, 1024>(g, nv, Dc, mu_c, x_self, x_hop, hop_sign, add, parity, zero_other, y, nsys, st);
+    return coarse_part<16, 256>(g, nv, Dc, mu_c, x_self, x_hop, hop_sign, add, parity, zero_other, y, nsys, st);
 }
 
 hipError_t launch_mg_coarse_apply(const Geo& g, int nv, const float2* Dc, const double* mu_c, const float2* x,
@@ -1021,7 +1056,7 @@ hipError_t launch_mg_block_mul(const BlockMulArgs& a, hipStream_t st) {
     if (a.nv < 1 || a.nv > kMgMaxVec || a.nsys < 1 || a.nsys > kMaxSys || a.g.nb[3] % 2 != 0)
         return hipErrorInvalidValue;
     BlockMulArgs k = a;  // systems grouped by inverse set
-    int pos = 0;
+    int pos = 0, runs = 0;
     for (int q = 0; q < kMgMaxInv; ++q) {
         k.start[q] = pos;
         for (int s = 0; s < a.nsys; ++s)
@@ -1029,10 +1064,11 @@ hipError_t launch_mg_block_mul(const BlockMulArgs& a, hipStream_t st) {
                 if (!a.sets[q]) return hipErrorInvalidValue;
                 k.order[pos++] = (unsigned char)s;
             }
+        runs += (pos - k.start[q] + kBlockMulSys - 1) / kBlockMulSys;
     }
     k.start[kMgMaxInv] = pos;
     if (pos != a.nsys) return hipErrorInvalidValue;  // a selector outside 0 .. kMgMaxInv - 1
-    hipLaunchKernelGGL(k_mg_block_mul, dim3((unsigned)(a.g.V / a.g.Vb / 2)), dim3(64), 0, st, k);
+    hipLaunchKernelGGL(k_mg_block_mul, dim3((unsigned)(a.g.V / a.g.Vb / 2), runs), dim3(256), 0, st, k);
     return hipGetLastError();
 }
 

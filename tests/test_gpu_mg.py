@@ -272,3 +272,26 @@ def test_stencil_face_sizes(dims, adims, nv):
     o.setup(v0)
     Dc = host(g.export()[1])
     assert np.abs(Dc - o.Dc).max() < 1e-5 * np.abs(o.Dc).max()
+
+
+# The coarse operator's two forms by the number of sites times systems, at the edges of 4 and of 16 systems.
+@pytest.mark.parametrize("dims,nsys", [((8, 8, 8, 8), 5), ((16, 16, 16, 16), 16), ((16, 16, 16, 16), 17),
+                                       ((32, 16, 16, 16), 9)])
+def test_coarse_operator_by_systems(dims, nsys):
+    U = synth.gauge_field(dims, 0.6, seed=9)
+    nv, mus = 3, [0.001 * (k - 4) for k in range(nsys)]
+    announce(f"coarse operator dims={dims} nsys={nsys}")
+    g = tm.MG(dims, dev(U), KAPPA, 0.01, CSW, dev(synth.gaussian_spinor(dims, nv, seed=109)), n_vec=nv, setup_iters=0)
+    nc, n2 = U.size // (4 * 9 * 256), 2 * nv
+    Dc = host(g.export()[1]).reshape(nc, 9, n2, n2)
+    rng = np.random.default_rng(49)
+    x = rng.normal(size=(nsys, nc, n2)) + 1j * rng.normal(size=(nsys, nc, n2))
+    y = host(g.coarse_apply(dev(x), mus)).reshape(x.shape)
+    grid = np.arange(nc).reshape([d // 4 for d in dims])
+    ref = np.einsum("jab,sjb->sja", Dc[:, 0], x)
+    for mu, axis in enumerate((0, 3, 2, 1)):
+        for t, step in ((1 + mu, -1), (5 + mu, 1)):
+            ref += np.einsum("jab,sjb->sja", Dc[:, t], x[:, np.roll(grid, step, axis).ravel()])
+    ref += 1j * np.array(mus)[:, None, None] * np.where(np.arange(n2) < nv, 1, -1) * x
+    for k in range(nsys):
+        assert rel_err(y[k], ref[k]) < 1e-5
