@@ -4,6 +4,8 @@
 // fields.
 #include "tm_internal.h"
 
+#include <algorithm>
+
 namespace tmsap {
 
 namespace {
@@ -46,13 +48,6 @@ __device__ inline M3 mdag(const M3& a) {
     return c;
 }
 
-__device__ inline void madd(M3& a, const M3& b) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) a.m[i][j] = cadd(a.m[i][j], b.m[i][j]);
-}
-
 // Coordinates of tiled site s in 32-bit arithmetic (a lattice has at most 2^29 sites).
 __device__ inline void coords32(const Geo& g, unsigned s, int c[4]) {
     unsigned blk = s / (unsigned)g.Vb, l = s - blk * (unsigned)g.Vb;
@@ -69,11 +64,16 @@ __device__ inline void coords32(const Geo& g, unsigned s, int c[4]) {
 // The links of time slices t0 .. t0 + nt (wrapped), 64 sites per workgroup, one (site, direction) per
 // thread.  The canonical array is read in its own order through LDS: read link by link, 64 lanes
 // touch 64 separate cache lines per load.  Writes, as asked for: the internal two-row copy of the
-// slices t0 + k0 .. t0 + k0 + kn (with the SU(3) check), and all nine elements as a structure of arrays
-// `soa` [4 mu][9][nt S], S = sites of a slice, sites lexicographic.
+// slices t0 + k0 .. t0 + k0 + kn (with the SU(3) check), and all nine elements in the staged order `soa`
+// [4 mu][nt][z][y][x / 4][9][x % 4]: four neighbouring sites' elements side by side, a link within 640 bytes.
 // stats[0]: max deviation from SU(3) (float bits), stats[1]: nonfinite flag.
 // 32^3x64 with staging: 0.70 ms for 1.2 GB read and 2.0 GB written (0.51 without the staged copy).
 constexpr int kIngestSites = 64;
+
+// Element 0 of the staged link at x of a row (of all directions and slices); element e is at + 4 e.
+__device__ inline size_t staged_link(unsigned row, unsigned X, unsigned x) {
+    return ((size_t)row * ((X + 3) / 4) + x / 4) * 36 + x % 4;
+}
 
 template <class G>
 __global__ void __launch_bounds__(kThreads) k_link_ingest(Geo g, const double* __restrict__ U, int t0, int nt, int k0,
@@ -102,10 +102,10 @@ __global__ void __launch_bounds__(kThreads) k_link_ingest(Geo g, const double* _
         L.m[e / 3][e % 3] = {v.x, v.y};
     }
     if (soa && on) {
-        const size_t at = (size_t)k * S + first + n, plane = (size_t)nt * S;
+        const unsigned X = (unsigned)g.d[3], row = (first + n) / X, x = first + n - row * X, rows = S / X;
+        double2* o = soa + staged_link((unsigned)(mu * nt + k) * rows + row, X, x);
 #pragma unroll
-        for (int e = 0; e < 9; ++e)
-            soa[(size_t)(mu * 9 + e) * plane + at] = make_double2(L.m[e / 3][e % 3].re, L.m[e / 3][e % 3].im);
+        for (int e = 0; e < 9; ++e) o[4 * e] = make_double2(L.m[e / 3][e % 3].re, L.m[e / 3][e % 3].im);
     }
     if (!links || k < k0 || k >= k0 + kn) return;
     float dev = 0.f;
@@ -156,30 +156,32 @@ __global__ void __launch_bounds__(kThreads) k_link_ingest(Geo g, const double* _
 //   [ m+4 + f H_3        f (H_1 - i H_2) ]
 //   [ f (H_1 + i H_2)    m+4 - f H_3     ]
 //
-// One thread per (site, plane) sums the leaves; a workgroup holds 64 consecutive tiled sites (a
-// 4 x 4 x 4 cube on 4^4 tiles, whose neighbours share cache lines), wavefront p the plane p, so that the
-// directions are uniform.  F goes through LDS to one thread per site and chirality, which writes the block.
-// (One thread per site over all planes kept both 6x6 blocks in scratch memory and read links as 144-byte
-// records: 5.55 ms at 32^3x64 against 3.2 ms, from the slices that the ingest stages.  What is left is
-// traffic between L2 and L1: 16 links of 144 bytes per site and plane.)
+// A workgroup holds a box of up to 2 x 4 x 4 x 4 sites (half a 4^4 tile) and goes through the six planes with
+// one thread per plaquette: the box's own and those that reach into it from one step below in either direction
+// (240 and 200 for 128 sites).  A plaquette's four links give its value around each of its four corners,
+// and a corner's anti-Hermitian part, 9 reals, is added to that site's sum in LDS, one corner after the other so
+// that every site has one writer.  Two threads per site, one per chirality, then write the blocks.
+// 32^3x64: 1.95 ms for the field, 3.2 with one thread per (site, plane) reading the 16 links around its site, 5.55
+// with one thread per site.  Two wavefronts per SIMD wait on L2: 1.5 to 1.9 plaquettes of 4 links per site
+// and plane; the boxes in XCD order (0.42 GB instead of 0.82 GB from memory per 11 slices) and the staged
+// order of the links (one base address and two elements per cache line) are 2.0 of it, from 3.1 ms.
 
-// Where the links come from: the canonical array, or the structure of arrays of slices tb .. tb + nt.
-template <bool SOA> struct LinkSource {
-    static constexpr bool kSoa = SOA;
+// Where the links come from: the canonical array, or the staged slices tb .. tb + nt.
+template <bool STAGED> struct LinkSource {
+    static constexpr bool kStaged = STAGED;
     const double2* p;
-    int tb;
-    size_t plane;
+    int tb, nt;
     __device__ inline M3 get(const Geo& g, const int c[4], int mu) const {
         M3 r;
-        if constexpr (SOA) {
+        if constexpr (STAGED) {
             int k = c[0] - tb;
             if (k < 0) k += g.d[0];
             if (k >= g.d[0]) k -= g.d[0];
-            const size_t at = (size_t)mu * 9 * plane +
-                              (unsigned)(((k * g.d[1] + c[1]) * g.d[2] + c[2]) * g.d[3] + c[3]);
+            const double2* q = p + staged_link((unsigned)(((mu * nt + k) * g.d[1] + c[1]) * g.d[2] + c[2]),
+                                               (unsigned)g.d[3], (unsigned)c[3]);
 #pragma unroll
             for (int e = 0; e < 9; ++e) {
-                const double2 v = p[at + (size_t)e * plane];
+                const double2 v = q[4 * e];
                 r.m[e / 3][e % 3] = {v.x, v.y};
             }
         } else {
@@ -204,76 +206,126 @@ __device__ inline void shift(const Geo& g, const int c[4], int a, int dir, int o
     }
 }
 
-// The four leaves at c0: with a(y) = U_mu(y) U_nu(y+mu) and b(y) = U_nu(y) U_mu(y+nu), the two ways around the
-// plaquette at y, they are a b^+ at y = x, U_nu(y+mu) b^+ U_mu(y) at y = x - mu, b^+ a at y = x - mu - nu and
-// U_nu(y)^+ a U_mu(y+nu)^+ at y = x - nu.
-template <bool SOA>
-__device__ inline M3 leaf_sum(const Geo& g, const LinkSource<SOA>& src, const int c0[4], int mu, int nu) {
-    const int am = axis_of(mu), an = axis_of(nu);
-    int ym[4], yn[4], ymn[4], p[4];
-    shift(g, c0, am, -1, ym);
-    shift(g, c0, an, -1, yn);
-    shift(g, ym, an, -1, ymn);
-    M3 Q;
-    {
-        shift(g, c0, am, +1, p);
-        const M3 a = mmul(src.get(g, c0, mu), src.get(g, p, nu));
-        shift(g, c0, an, +1, p);
-        Q = mmul(a, mdag(mmul(src.get(g, c0, nu), src.get(g, p, mu))));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    {
-        shift(g, ym, an, +1, p);
-        const M3 b = mmul(src.get(g, ym, nu), src.get(g, p, mu));
-        madd(Q, mmul(src.get(g, c0, nu), mmul(mdag(b), src.get(g, ym, mu))));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    {
-        const M3 a = mmul(src.get(g, ymn, mu), src.get(g, yn, nu));
-        const M3 b = mmul(src.get(g, ymn, nu), src.get(g, ym, mu));
-        madd(Q, mmul(mdag(b), a));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    {
-        shift(g, yn, am, +1, p);
-        const M3 a = mmul(src.get(g, yn, mu), src.get(g, p, nu));
-        madd(Q, mmul(mdag(src.get(g, yn, nu)), mmul(a, mdag(src.get(g, c0, mu)))));
-    }
-    return Q;
-}
+constexpr int kCloverThreads = 256, kPlanes = 6, kBoxSites = 128;
 
-constexpr int kCloverSites = 64, kPlanes = 6;
+// The boxes of a build: extents p, boxes per axis, first and last + 1 coordinate.
+struct CloverBoxes {
+    int p[4], n[4], lo[4], hi[4];
+};
 
-// Sites s0 .. s0 + ns of the tiled layout.
-template <class C, bool SOA>
-__global__ void __launch_bounds__(kCloverSites * kPlanes) k_clover_build(Geo g, LinkSource<SOA> src, long long s0,
-                                                                         long long ns, double m4, double f,
-                                                                         void* clover) {
-    // F = i H, H Hermitian: H's diagonal (3 reals) and upper triangle 01, 02, 12 (complex), per plane
-    __shared__ double fh[kPlanes][9][kCloverSites];
-    const int pl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = threadIdx.x & 63;
-    const long long rel = (long long)blockIdx.x * kCloverSites + n;
-    const bool on = rel < ns;
-    const unsigned s = (unsigned)(s0 + (on ? rel : 0));
-    int c[4];
-    coords32(g, s, c);
-    const int mu = pl < 3 ? 0 : (pl < 5 ? 1 : 2), nu = pl < 3 ? pl + 1 : (pl < 5 ? pl - 1 : 3);
-    const M3 Q = leaf_sum(g, src, c, mu, nu);
-    // H = -i (Q - Q^+)
+// n / e for 0 <= n < 256, 1 <= e <= 8, with inv = ceil(65536 / e)
+__device__ inline int small_div(int n, int inv) { return (n * inv) >> 16; }
+
+// Add (or with FIRST, set) -i (Q - Q^+) to the sums of one plane at site n of the box: the diagonal (3 reals)
+// and the upper triangle 01, 02, 12 (complex) of the Hermitian matrix.
+template <bool FIRST>
+__device__ inline void add_corner(const M3& Q, double (*fh)[kBoxSites], int n) {
+    double h[9];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) fh[pl][i][n] = 2.0 * Q.m[i][i].im;
+    for (int i = 0; i < 3; ++i) h[i] = 2.0 * Q.m[i][i].im;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const int i = k == 2 ? 1 : 0, j = k == 0 ? 1 : 2;
         const C64 d = csub(Q.m[i][j], cconj(Q.m[j][i]));
-        fh[pl][3 + 2 * k][n] = d.im;
-        fh[pl][4 + 2 * k][n] = -d.re;
+        h[3 + 2 * k] = d.im;
+        h[4 + 2 * k] = -d.re;
+    }
+#pragma unroll
+    for (int e = 0; e < 9; ++e) fh[e][n] = FIRST ? h[e] : fh[e][n] + h[e];
+}
+
+// With a(y) = U_mu(y) U_nu(y+mu) and b(y) = U_nu(y) U_mu(y+nu), the plaquette at y seen from its corners is
+// a b^+ at y, U_nu(y+mu) b^+ U_mu(y) at y + mu, b^+ a at y + mu + nu and U_nu(y)^+ a U_mu(y+nu)^+ at y + nu:
+// the four leaves of F at those sites.
+template <class C, bool STAGED>
+__global__ void __launch_bounds__(kCloverThreads) __attribute__((amdgpu_waves_per_eu(2)))
+k_clover_build(Geo g, LinkSource<STAGED> src, CloverBoxes bx, double m4, double f, void* clover) {
+    __shared__ double fh[kPlanes][9][kBoxSites];
+    int org[4];
+    {
+        int b = (int)xcd_swizzle(blockIdx.x, gridDim.x);
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+            org[q] = bx.lo[q] + (b % bx.n[q]) * bx.p[q];
+            b /= bx.n[q];
+        }
+    }
+    // site n of the box (x fastest): strides of the box
+    const int st[4] = {bx.p[1] * bx.p[2] * bx.p[3], bx.p[2] * bx.p[3], bx.p[3], 1};
+#pragma unroll 1
+    for (int pl = 0; pl < kPlanes; ++pl) {
+        const int mu = pl < 3 ? 0 : (pl < 5 ? 1 : 2), nu = pl < 3 ? pl + 1 : (pl < 5 ? pl - 1 : 3);
+        const int am = axis_of(mu), an = axis_of(nu);
+        int l[4], y[4], n = threadIdx.x;
+        bool on = true;
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+            const int e = bx.p[q] + (q == am || q == an ? 1 : 0), m = small_div(n, (65535 + e) / e);
+            l[q] = n - m * e - (q == am || q == an ? 1 : 0);
+            y[q] = org[q] + l[q];
+            on = on && y[q] < bx.hi[q];
+            n = m;
+        }
+        on = on && n == 0;
+        int lm = 0, ln = 0, em = 0, en = 0, sm = 0, sn = 0, at = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (!on) y[q] = org[q];  // the spare threads load what others load
+            if (y[q] < 0) y[q] += g.d[q];
+            if (q == am) lm = l[q], em = min(bx.p[q], bx.hi[q] - org[q]), sm = st[q];
+            if (q == an) ln = l[q], en = min(bx.p[q], bx.hi[q] - org[q]), sn = st[q];
+            at += l[q] * st[q];
+        }
+        int ym[4], yn[4];
+        shift(g, y, am, +1, ym);
+        shift(g, y, an, +1, yn);
+        const bool m0 = on && lm >= 0, m1 = on && lm + 1 < em, n0 = ln >= 0, n1 = ln + 1 < en;
+        const M3 Un = src.get(g, y, nu), Vm = src.get(g, yn, mu);
+        const M3 Um = src.get(g, y, mu), Vn = src.get(g, ym, nu);
+        __builtin_amdgcn_sched_barrier(0);
+        const M3 b = mmul(Un, Vm);
+        M3 a;
+        {
+            const M3 Q = mmul(Vn, mmul(mdag(b), Um));
+            if (m1 && n0) add_corner<true>(Q, fh[pl], at + sm);
+            a = mmul(Um, Vn);
+        }
+        __syncthreads();
+        {
+            const M3 Q = mmul(a, mdag(b));
+            if (m0 && n0) add_corner<false>(Q, fh[pl], at);
+        }
+        __syncthreads();
+        asm volatile("" ::: "memory");  // the last corner reads its two links again instead of keeping 72 registers
+        {
+            const M3 Q = mmul(mdag(b), a);
+            if (m1 && n1) add_corner<false>(Q, fh[pl], at + sm + sn);
+        }
+        __syncthreads();
+        {
+            const M3 U2 = src.get(g, y, nu), V2 = src.get(g, yn, mu);
+            const M3 Q = mmul(mmul(mdag(U2), a), mdag(V2));
+            if (m0 && n1) add_corner<false>(Q, fh[pl], at + sn);
+        }
     }
     __syncthreads();
-    if (pl >= 2 || !on) return;
-    // chirality pl: H_l = i (F_jk -+ F_0l) = -(H_jk -+ H_0l); planes 0..2 are (0, l), 5, 4, 3 the jk of
+    // the box's sites: 128 threads per chirality
+    const int ch = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
+    const int n = threadIdx.x & (kBoxSites - 1);
+    int c[4], r = n;
+    bool on = true;
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+        const int m = small_div(r, (65535 + bx.p[q]) / bx.p[q]);
+        c[q] = org[q] + r - m * bx.p[q];
+        on = on && c[q] < bx.hi[q];
+        r = m;
+    }
+    if (!on || r != 0) return;
+    const long long s = coords_site(g, c);
+    // chirality ch: H_l = i (F_jk -+ F_0l) = -(H_jk -+ H_0l); planes 0..2 are (0, l), 5, 4, 3 the jk of
     // l = 1, 2, 3, plane 4 = (1, 3) with the sign of eps_132
-    const double sg = pl == 0 ? -1.0 : 1.0;
+    const double sg = ch == 0 ? -1.0 : 1.0;
     double h[3][9];
 #pragma unroll
     for (int l = 0; l < 3; ++l)
@@ -309,7 +361,7 @@ __global__ void __launch_bounds__(kCloverSites * kPlanes) k_clover_build(Geo g, 
             out[k++] = v.im;
         }
 #pragma unroll
-    for (int u = 0; u < 9; ++u) Unit<C>::store(clover, (size_t)(9 * pl + u) * g.V + s, out + 4 * u);
+    for (int u = 0; u < 9; ++u) Unit<C>::store(clover, (size_t)(9 * ch + u) * g.V + s, out + 4 * u);
 }
 
 // c_sw = 0: the mass term alone.
@@ -477,7 +529,7 @@ __global__ void __launch_bounds__(kThreads) k_eo_inverse(Geo g, const void* __re
     }
 
 size_t gauge_stage_bytes(const Geo& g, int slices) {
-    return (size_t)slices * (size_t)(g.V / g.d[0]) * 36 * sizeof(double2);
+    return (size_t)slices * (size_t)(g.d[1] * g.d[2]) * (size_t)((g.d[3] + 3) / 4 * 4) * 36 * sizeof(double2);
 }
 
 hipError_t launch_link_ingest(const Geo& g, Prec G, const void* Ucanon, void* links, unsigned* stats,
@@ -504,14 +556,25 @@ hipError_t launch_gauge_build(const Geo& g, Prec G, Prec C, const void* Ucanon, 
     const int T = g.d[0], lt = g.lb[0];
     const size_t slice = gauge_stage_bytes(g, 1);
     const int room = (int)(stage ? stage_bytes / slice : 0);
-    auto build = [&](auto src, long long s0, long long ns) {
-        const unsigned nwg = (unsigned)((ns + kCloverSites - 1) / kCloverSites);
-        TM_DISPATCH_PREC(C, Tc, hipLaunchKernelGGL((k_clover_build<Tc, decltype(src)::kSoa>), dim3(nwg),
-                                                   dim3(kCloverSites * kPlanes), 0, st, g, src, s0, ns, m4, f, clover));
+    CloverBoxes bx;
+    for (int q = 0; q < 4; ++q) {  // an axis in steps of 4, or of 3 where that pads less (2 and 1 in t)
+        const int big = q == 0 ? 2 : 4, small = q == 0 ? 1 : 3, d = g.d[q];
+        bx.p[q] = std::min(d, (d + big - 1) / big * big <= (d + small - 1) / small * small ? big : small);
+        bx.n[q] = (d + bx.p[q] - 1) / bx.p[q];
+        bx.lo[q] = 0;
+        bx.hi[q] = d;
+    }
+    auto build = [&](auto src, int t0, int nt) {  // slices t0 .. t0 + nt
+        bx.lo[0] = t0;
+        bx.hi[0] = t0 + nt;
+        bx.n[0] = (nt + bx.p[0] - 1) / bx.p[0];
+        const unsigned nwg = (unsigned)((long long)bx.n[0] * bx.n[1] * bx.n[2] * bx.n[3]);
+        TM_DISPATCH_PREC(C, Tc, hipLaunchKernelGGL((k_clover_build<Tc, decltype(src)::kStaged>), dim3(nwg),
+                                                   dim3(kCloverThreads), 0, st, g, src, bx, m4, f, clover));
     };
     if (room < T && room < lt + 2) {  // no room to stage one row of tiles with its neighbours
         if ((e = launch_link_ingest(g, G, Ucanon, links, stats, st)) != hipSuccess) return e;
-        build(LinkSource<false>{(const double2*)Ucanon, 0, 0}, 0, g.V);
+        build(LinkSource<false>{(const double2*)Ucanon, 0, 0}, 0, T);
         return hipGetLastError();
     }
     // whole rows of tiles (contiguous in the tiled layout) with one slice on either side, or everything at once
@@ -525,7 +588,7 @@ hipError_t launch_gauge_build(const Geo& g, Prec G, Prec C, const void* Ucanon, 
                                                    (const double*)Ucanon, tb, nt, k0, m, links, stats,
                                                    (double2*)stage));
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        build(LinkSource<true>{(const double2*)stage, tb, (size_t)nt * (size_t)S}, t * S, m * S);
+        build(LinkSource<true>{(const double2*)stage, tb, nt}, t, m);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

@@ -240,3 +240,13 @@ def test_canonical_application_matches_staged_one(dims, nsys):
     out = both[12:].view(p.shape)
     tm.tm_dirac_apply(dims, Ud, both[:p.numel()].view(p.shape), 0.14, mus, 1.2, out, **kw)
     assert rel_err(host(out), got) < 1e-13
+
+
+# Boxes of the clover build: steps of 4 and of 3, boxes cut off by the lattice's end, one and two slices.
+@pytest.mark.parametrize("dims", [(2, 6, 10, 7), (4, 9, 5, 3), (3, 11, 4, 6), (6, 2, 1, 14)])
+def test_clover_build_boxes(dims):
+    U, psi = synth.gauge_field(dims, 0.6, seed=83), synth.gaussian_spinor(dims, 1, seed=183)
+    ref = oracle.Operator(dims, U, oracle.kappa_to_m(0.14), 0.1, 1.3).apply(psi[0]).reshape(psi[0].shape)
+    announce(f"clover boxes dims={dims}")
+    got = host(tm.tm_dirac_apply(dims, dev(U), dev(psi), 0.14, [0.1], 1.3))
+    check_close(got[0], ref, "dirac", "f64", f"clover boxes {dims}")
