@@ -150,36 +150,48 @@ def _check(rc: int, allow_not_converged: bool = False) -> int:
 def _stream_handle(stream):
     """None: torch's current stream; False: the null stream (no torch call)."""
     if stream is False:
-        return ctypes.c_void_p(None)
+        return None
+    if stream is not None:
+        return stream.cuda_stream
     import torch
 
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    # the handle alone: building a Stream object around it takes 3 us of a small call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+_INT4, _DOUBLE4, _DOUBLE2 = ctypes.c_int * 4, ctypes.c_double * 4, ctypes.c_double * 2
+_DOUBLES = tuple(ctypes.c_double * n for n in range(MAX_SYS + 1))  # array types, which cost 1 us each to look up
+_opts_default = None
 
 
 def make_geom(dims: Sequence[int], mu, antiperiodic_t: bool = False, theta=None, mu_shift=None):
     """theta: twisted boundary phases (radians) for t, x, y, z; mu_shift: added to mu on even / odd sites."""
-    mus = [float(mu)] if isinstance(mu, (int, float)) else [float(m) for m in mu]
-    arr = (ctypes.c_double * len(mus))(*mus)
-    th = [float(t) for t in (theta or (0.0, 0.0, 0.0, 0.0))]
-    ms = [float(t) for t in (mu_shift or (0.0, 0.0))]
-    g = Geom((ctypes.c_int * 4)(*[int(d) for d in dims]), int(bool(antiperiodic_t)), len(mus),
-             ctypes.cast(arr, ctypes.POINTER(ctypes.c_double)), (ctypes.c_double * 4)(*th),
-             (ctypes.c_double * 2)(*ms))
+    mus = (float(mu),) if isinstance(mu, (int, float)) else tuple(map(float, mu))
+    n = len(mus)
+    arr = (_DOUBLES[n] if n <= MAX_SYS else ctypes.c_double * n)(*mus)
+    g = Geom(_INT4(*map(int, dims)), int(bool(antiperiodic_t)), n, arr)  # phases and shifts start as zero
+    if theta:
+        g.theta = _DOUBLE4(*map(float, theta))
+    if mu_shift:
+        g.mu_shift = _DOUBLE2(*map(float, mu_shift))
     g._keep = arr
     return g
 
 
 def make_opts(storage: str = "f64", compute: str | None = None, stream=None, io: str = "canonical",
               layout_block=None, gauge_tag: int = 0):
-    o = Opts()
-    lib().tm_opts_default(ctypes.byref(o))
+    global _opts_default
+    if _opts_default is None:
+        o = Opts()
+        lib().tm_opts_default(ctypes.byref(o))
+        _opts_default = bytes(o)
+    o = Opts.from_buffer_copy(_opts_default)
     o.storage = PREC[storage]
     o.compute = PREC[compute] if compute else (PREC["f64"] if storage == "f64" else PREC["f32"])
     o.stream = _stream_handle(stream)
     o.io = IO[io]
     if layout_block is not None:
-        o.layout_block = (ctypes.c_int * 4)(*[int(v) for v in layout_block])
+        o.layout_block = _INT4(*map(int, layout_block))
     o.gauge_tag = int(gauge_tag)
     return o
 
@@ -222,10 +234,10 @@ def _internal(t, nbytes: int, what: str) -> ctypes.c_void_p:
 def _volume(dims) -> int:
     """Sites of dims, or 0 when a dimension is not positive (the library reports that error itself)."""
     V = 1
-    for d in dims:
-        if int(d) <= 0:
+    for d in map(int, dims):
+        if d <= 0:
             return 0
-        V *= int(d)
+        V *= d
     return V
 
 
