@@ -48,9 +48,9 @@ __device__ inline void parity_dir(const ParityArgs& a, const FieldOf<double>& in
     cplx<double> uf[6], ub[6];
     FieldOf<double>::Raw pf, pb;
     in.read<MU>(nf[MU] >> 1, c, pf);
-    link_read<MU>(a.links, g.V, s, uf);
+    link_read<MU>(a.links, g.V, s, c, uf);
     in.read<MU>(nbk[MU] >> 1, c, pb);
-    link_read<MU>(a.links, g.V, nbk[MU], ub);
+    link_read<MU>(a.links, g.V, nbk[MU], c, ub);
     Col<double> p, q, h, t;
     FieldOf<double>::spins<MU>(pf, c, p, q);
     if (G5HOP) {

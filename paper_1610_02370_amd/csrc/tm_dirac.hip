@@ -297,9 +297,9 @@ __device__ inline void dir_add(const DiracArgs& a, const F& in, const PairSite& 
     cplx<double> uf[6], ub[6];
     typename F::Raw pf, pb;
     in.template read<MU>(F::kCanonical ? t.cf[MU] : t.nf[MU], c, pf);
-    link_read<MU>(a.links, a.g.V, t.s, uf);
+    link_read<MU>(a.links, a.g.V, t.s, c, uf);
     in.template read<MU>(F::kCanonical ? t.cb[MU] : t.nbk[MU], c, pb);
-    link_read<MU>(a.links, a.g.V, t.nbk[MU], ub);
+    link_read<MU>(a.links, a.g.V, t.nbk[MU], c, ub);
     hop_add<MU, +1, F>(a.g, pf, uf, t.wrap & (1u << MU), c, s, acc);
     hop_add<MU, -1, F>(a.g, pb, ub, t.wrap & (16u << MU), c, s, acc);
     pin(acc);

@@ -16,6 +16,7 @@
 #pragma once
 
 #include "tm_device.h"
+#include "tm_reduce.h"
 
 namespace tmsap {
 
@@ -236,15 +237,18 @@ template <class S> struct FieldOf {  // internal layout, units of four reals
     static constexpr bool kCanonical = false;
 };
 
-// The two rows of the FP64 link MU of a site.
+// The two rows of the FP64 link MU of a site, which both lanes of the pair need: each loads one complex number
+// of every unit, 1 KiB in a row per wavefront, and takes the other from its partner.  All lanes active.
 template <int MU>
-__device__ inline void link_read(const void* links, long long V, long long site, cplx<double> u[6]) {
+__device__ inline void link_read(const void* links, long long V, long long site, int c, cplx<double> u[6]) {
+    double2 w[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        w[q] = static_cast<const double2*>(plane<double>(links, 3 * MU + q, V))[2 * (size_t)site + c];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        double w[4];
-        Unit<double>::load(plane<double>(links, 3 * MU + q, V), (size_t)site, w);
-        u[2 * q] = cmk(w[0], w[1]);
-        u[2 * q + 1] = cmk(w[2], w[3]);
+        u[2 * q] = cmk(dpp_v<0xa0, 0xf>(w[q].x), dpp_v<0xa0, 0xf>(w[q].y));      // the even lane's
+        u[2 * q + 1] = cmk(dpp_v<0xf5, 0xf>(w[q].x), dpp_v<0xf5, 0xf>(w[q].y));  // the odd lane's
     }
 }
 
