@@ -45,10 +45,10 @@ hipError_t blas_dgs_coef(const double* d, int nb, int nsys, unsigned long long o
                          double* tri, hipStream_t st);
 int blas_dgs_tri_stride();
 // Update: y <- s (w - V a - h v_nb), formed from u, w and the stored vectors; out[sys] = ||y||^2 of
-// the stored values.
+// the stored values; with `copy` (p = P_F64), y also rounded to FP32 there ([nsys][6 units][V]).
 hipError_t blas_dgs_update(Prec p, const VecRef& basis, size_t vec_stride, int nb, const VecRef& u, const VecRef& w,
                            const VecRef& y, const double* coef, double* partials, double* out, int nsys, long long V,
-                           hipStream_t st);
+                           hipStream_t st, float* copy = nullptr);
 // y = a[sys] x
 hipError_t blas_scale(Prec pi, Prec po, const VecRef& x, const double* a, const VecRef& y, int nsys, long long V,
                       hipStream_t st);

@@ -82,6 +82,11 @@ __global__ void __launch_bounds__(kThreads) k_norm2(VecRef x, double* partials, 
 // Dots sweep over stored vectors [i0, i0 + n): per system 4 n values
 // (<u_i, u>, <u_i, w>) as complex pairs, and with `head` 4 more: <u, u>,
 // <u, w> (complex), <w, w>, for u = u_j.
+//
+// A thread takes one unit (4 reals) of a vector at a time instead of a site's 24: the registers go to the sums,
+// and a sweep covers 11 vectors (as many as the reduction's 2 kMaxVec values hold), so that u and w are read
+// once per 11 stored vectors.  32^3x64, 2 systems, FP64, 14 steps: 16.7 ms at 5.8 TB/s; with a site at a time and
+// 4 vectors per sweep 19.9 ms.
 template <class P, int NV>
 __global__ void __launch_bounds__(kThreads) k_dgs_dots(VecRef basis, size_t vec_stride, int i0, int n, VecRef u,
                                                        VecRef w, int head, double* partials, long long V) {
@@ -95,41 +100,40 @@ __global__ void __launch_bounds__(kThreads) k_dgs_dots(VecRef basis, size_t vec_
     const char* b0 = static_cast<const char*>(basis.data) + (size_t)sys * basis.sys_stride + (size_t)i0 * vec_stride;
     const char* u0 = static_cast<const char*>(u.data) + (size_t)sys * u.sys_stride;
     const char* w0 = static_cast<const char*>(w.data) + (size_t)sys * w.sys_stride;
-    for (long long s = (long long)blockIdx.x * kThreads + threadIdx.x; s < V; s += (long long)nblk * kThreads) {
-        Spinor<R> uv, wv;
-        load_spinor<R, P>(u0, nullptr, V, s, uv);
-        load_spinor<R, P>(w0, nullptr, V, s, wv);
+    // a + (re, im) of <x, y> over one unit
+    const auto dot = [](const R* x, const R* y, double* a) {
+        R re = x[0] * y[0], im = x[0] * y[1];
+        re += x[1] * y[1];
+        im -= x[1] * y[0];
+        re += x[2] * y[2];
+        im += x[2] * y[3];
+        re += x[3] * y[3];
+        im -= x[3] * y[2];
+        a[0] += (double)re;
+        a[1] += (double)im;
+    };
+    for (long long s = (long long)blockIdx.x * kThreads + threadIdx.x; s < 6 * V; s += (long long)nblk * kThreads) {
+        R uv[4], wv[4], v[NV][4];
+        Unit<P>::load(u0, (size_t)s, uv);
+        Unit<P>::load(w0, (size_t)s, wv);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
+        for (int i = 0; i < NV; ++i)
+            if (i < n) Unit<P>::load(b0 + i * vec_stride, (size_t)s, v[i]);
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
             if (i < n) {
-                Spinor<R> v;
-                load_spinor<R, P>(b0 + i * vec_stride, nullptr, V, s, v);
-                R cr = 0, ci = 0, ar = 0, ai = 0;
-#pragma unroll
-                for (int k = 0; k < 12; ++k) {
-                    cr += v.v[k].re * uv.v[k].re + v.v[k].im * uv.v[k].im;
-                    ci += v.v[k].re * uv.v[k].im - v.v[k].im * uv.v[k].re;
-                    ar += v.v[k].re * wv.v[k].re + v.v[k].im * wv.v[k].im;
-                    ai += v.v[k].re * wv.v[k].im - v.v[k].im * wv.v[k].re;
-                }
-                acc[4 * i] += (double)cr;
-                acc[4 * i + 1] += (double)ci;
-                acc[4 * i + 2] += (double)ar;
-                acc[4 * i + 3] += (double)ai;
+                dot(v[i], uv, acc + 4 * i);
+                dot(v[i], wv, acc + 4 * i + 2);
             }
-        }
         if (head) {
-            R uu = 0, uwr = 0, uwi = 0, ww = 0;
+            R uu = 0, ww = 0;
 #pragma unroll
-            for (int k = 0; k < 12; ++k) {
-                uu += uv.v[k].re * uv.v[k].re + uv.v[k].im * uv.v[k].im;
-                uwr += uv.v[k].re * wv.v[k].re + uv.v[k].im * wv.v[k].im;
-                uwi += uv.v[k].re * wv.v[k].im - uv.v[k].im * wv.v[k].re;
-                ww += wv.v[k].re * wv.v[k].re + wv.v[k].im * wv.v[k].im;
+            for (int k = 0; k < 4; ++k) {
+                uu += uv[k] * uv[k];
+                ww += wv[k] * wv[k];
             }
             acc[4 * NV] += (double)uu;
-            acc[4 * NV + 1] += (double)uwr;
-            acc[4 * NV + 2] += (double)uwi;
+            dot(uv, wv, acc + 4 * NV + 1);
             acc[4 * NV + 3] += (double)ww;
         }
     }
@@ -247,11 +251,15 @@ __global__ void k_dgs_coef(const double* d, int nb, int nsys, unsigned long long
 }
 
 // Update sweep with the coefficients of k_dgs_coef (per system at coef + sys * (4 + 2 nb)):
-//   y = s w - (s e) u_j - sum_i (s g_i) u_i   written to y; out = ||y||^2 of the stored values
+//   y = s w - (s e) u_j - sum_i (s g_i) u_i   written to y; out = ||y||^2 of the stored values.
+// With `copy` (FP64 vectors) y is also stored rounded to FP32, [nsys][6 units][V]: the smoother's input.  A
+// conversion reads all of y for it: 222 us a step for 2 systems on 32^3x64, against 75 here.  (A unit at a time,
+// as in the dots, gains nothing: reads and the write run at 5.0 TB/s either way.)
 template <class P, int NV>
 __global__ void __launch_bounds__(kThreads) k_dgs_update(VecRef basis, size_t vec_stride, int nb, VecRef u,
-                                                         VecRef w, VecRef y, const double* __restrict__ coef,
-                                                         double* partials, long long V) {
+                                                         VecRef w, VecRef y, float* copy,
+                                                         const double* __restrict__ coef, double* partials,
+                                                         long long V) {
     typedef typename std::conditional<std::is_same<P, double>::value, double, float>::type R;
     __shared__ double lds[(kThreads / 64) * 2 * kMaxVec];
     const int sys = blockIdx.y;
@@ -281,6 +289,14 @@ __global__ void __launch_bounds__(kThreads) k_dgs_update(VecRef basis, size_t ve
             }
         }
         store_spinor<R, P>(y0, nullptr, V, s, yv);
+        if constexpr (std::is_same<P, double>::value) {
+            if (copy) {
+                Spinor<float> f;
+#pragma unroll
+                for (int k = 0; k < 12; ++k) f.v[k] = cmk((float)yv.v[k].re, (float)yv.v[k].im);
+                store_spinor<float, float>(copy + (size_t)sys * 24 * V, nullptr, V, s, f);
+            }
+        }
         R n2 = 0;
 #pragma unroll
         for (int k = 0; k < 12; ++k) n2 += yv.v[k].re * yv.v[k].re + yv.v[k].im * yv.v[k].im;
@@ -464,18 +480,26 @@ hipError_t blas_dgs_dots(Prec p, const VecRef& basis, size_t vec_stride, int nb,
                         double* partials, double* out, int nsys, long long V, hipStream_t st) {
     if (nb < 0 || nb > kMaxVec - 1 || (p != P_F64 && p != P_F32)) return hipErrorInvalidValue;
     const int nblk = blas_blocks(V);
-    const int chunk = p == P_F32 ? 8 : 4;  // FP64 spinors take twice the registers
+    constexpr int chunk = 11;  // 4 chunk + 4 values per sweep
+    static_assert(4 * chunk + 4 <= 2 * kMaxVec, "reduction scratch");
     const int ds = 4 * nb + 4;
     dim3 grid(nblk, nsys);
     for (int i0 = 0;; i0 += chunk) {
         const int n = nb - i0 < chunk ? nb - i0 : chunk;
         const int head = i0 + n == nb;
-        if (p == P_F32)
-            hipLaunchKernelGGL((k_dgs_dots<float, 8>), grid, dim3(kThreads), 0, st, basis, vec_stride, i0, n, u, w,
-                               head, partials, V);
-        else
-            hipLaunchKernelGGL((k_dgs_dots<double, 4>), grid, dim3(kThreads), 0, st, basis, vec_stride, i0, n, u, w,
-                               head, partials, V);
+#define TM_DOTS_LAUNCH(T)                                                                                              \
+    if (n <= 4)                                                                                                        \
+        hipLaunchKernelGGL((k_dgs_dots<T, 4>), grid, dim3(kThreads), 0, st, basis, vec_stride, i0, n, u, w, head,       \
+                           partials, V);                                                                               \
+    else                                                                                                               \
+        hipLaunchKernelGGL((k_dgs_dots<T, chunk>), grid, dim3(kThreads), 0, st, basis, vec_stride, i0, n, u, w, head,   \
+                           partials, V)
+        if (p == P_F32) {
+            TM_DOTS_LAUNCH(float);
+        } else {
+            TM_DOTS_LAUNCH(double);
+        }
+#undef TM_DOTS_LAUNCH
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         const int nv = 4 * n + (head ? 4 : 0);
@@ -498,17 +522,18 @@ int blas_dgs_tri_stride() { return kTri; }
 
 hipError_t blas_dgs_update(Prec p, const VecRef& basis, size_t vec_stride, int nb, const VecRef& u, const VecRef& w,
                            const VecRef& y, const double* coef, double* partials, double* out, int nsys, long long V,
-                           hipStream_t st) {
+                           hipStream_t st, float* copy) {
+    if (copy && p != P_F64) return hipErrorInvalidValue;
     if (nb < 0 || nb > kMaxVec - 1 || (p != P_F64 && p != P_F32)) return hipErrorInvalidValue;
     const int nblk = blas_blocks(V);
     dim3 grid(nblk, nsys);
 #define TM_DGS_LAUNCH(NVT)                                                                                     \
     if (p == P_F32)                                                                                            \
         hipLaunchKernelGGL((k_dgs_update<float, NVT>), grid, dim3(kThreads), 0, st, basis, vec_stride, nb, u, \
-                           w, y, coef, partials, V);                                                           \
+                           w, y, copy, coef, partials, V);                                                     \
     else                                                                                                       \
         hipLaunchKernelGGL((k_dgs_update<double, NVT>), grid, dim3(kThreads), 0, st, basis, vec_stride, nb, u, \
-                           w, y, coef, partials, V)
+                           w, y, copy, coef, partials, V)
     if (nb <= 4) {
         TM_DGS_LAUNCH(4);
     } else if (nb <= 8) {

@@ -274,6 +274,7 @@ int fgmres_core(Ctx& c, Krylov& K, const SpinorBuf& rhs, const SpinorBuf& x, boo
             return rc;
         r_in_rhs = false;
         int jdone = 0;
+        const bool copied = K.convert && c.vp == P_F64 && K.vS.prec == P_F32;
         for (int j = 0; j < m && steps < max_iters; ++j) {
             // slot j: v_0 at the first step, afterwards the direction u_j of the previous step,
             // orthogonalised once; it becomes v_j in this step's update sweep
@@ -281,7 +282,8 @@ int fgmres_core(Ctx& c, Krylov& K, const SpinorBuf& rhs, const SpinorBuf& x, boo
             const SpinorBuf zj = K.Zb(c, j);
             SpinorBuf src = uj;
             if (K.convert) {
-                if ((rc = hcheck(launch_spinor_convert(c.g, uj, K.vS, c.st), "convert"))) return rc;
+                // from the second step on an FP32 copy comes with the update sweep
+                if ((j == 0 || !copied) && (rc = hcheck(launch_spinor_convert(c.g, uj, K.vS, c.st), "convert"))) return rc;
                 src = K.vS;
             }
             // z_j = SAP(u_j) from a zero guess; w = D z_j.  When the smoother and the operator
@@ -323,7 +325,8 @@ int fgmres_core(Ctx& c, Krylov& K, const SpinorBuf& rhs, const SpinorBuf& x, boo
             if ((rc = hcheck(blas_dgs_coef(c.sc.dots, j, ns, off, c.sc.coef, c.sc.rep, c.sc.tri, c.st), "gs")))
                 return rc;
             if ((rc = hcheck(blas_dgs_update(c.vp, basis, K.vstride, j, ur, wr, vec_ref(un, V), c.sc.coef,
-                                             c.sc.partials, c.sc.nrm2, ns, V, c.st),
+                                             c.sc.partials, c.sc.nrm2, ns, V, c.st,
+                                             copied ? (float*)K.vS.data : nullptr),
                              "gs")))
                 return rc;
             const size_t rstride = 4 + 4 * (size_t)blas_dgs_tri_stride();
