@@ -269,9 +269,9 @@ def sap_sweep_phase(wl, Ud, mus, torch, tm, reps, storage=None):
 
 def sap_kernel_name(storage: str, eo: bool = False) -> str:
     if eo:
-        return "k_sap_half_eo"
+        return "k_sap_pair_eo" if tuple(BLOCK) == (4, 4, 4, 4) else "k_sap_half_eo"
     if storage == "f64":
-        return "k_sap_half"
+        return "k_sap_pair" if tuple(BLOCK) == (4, 4, 4, 4) else "k_sap_half"
     return "k_sap_half_44" if tuple(BLOCK) == (4, 4, 4, 4) else "k_sap_half_v2"
 
 

@@ -202,10 +202,10 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
 // neighbours one hop at a time.  A pair's lanes each read the two spins of a neighbour that their
 // half spinor needs, and both hops of a direction are read before either is used.
 //
-// Measured, with the calls' canonical buffers: 6x10x7x9, 3 systems, 26.6 -> 13.3 us; 4^4, 2 systems, 19.6 ->
-// 13.2; 32^3x64, one system, 1170 -> 830, six systems 5060 -> 3980; FP32 in and FP64 out, 32^3x64, two
-// systems, 1740 -> 1180.  Large lattices are bound by the neighbours' reads from L2 (about 3 KB per
-// site and system, 8 TB/s).
+// Measured, with the calls' canonical buffers: 6x10x7x9, 3 systems, 26.6 -> 13.3 us a call; 4^4, 2 systems, 19.6
+// -> 13.2 (7.9 and 6.0 us of it the kernel); 32^3x64, one system, 1170 -> 800, six systems 5060 -> 3980 (before
+// the halved link loads); FP32 in and FP64 out, 32^3x64, two systems, 1740 -> 1056.  Large lattices are bound by
+// the neighbours' reads from L2 (about 3 KB per site and system, 8 to 9 TB/s).
 
 // The canonical layout as a field (FieldOf, tm_pair.h, is the internal one).
 struct Canonical {
