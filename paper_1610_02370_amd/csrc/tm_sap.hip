@@ -954,9 +954,11 @@ __device__ inline void s44_stage_forward(const Geo& g, const Spinor<float>& p, b
 // w stages axis w's halo: the backward product of the site below the lower face
 // into the slot of its column's upper-face site, and, once the in-block hops
 // have read xs, the projected half spinor of the site above the upper face into
-// xs.  The diagonal comes first, which frees e, and the spinor above the upper face is on
-// its way during the in-block hops: fetched where it is staged, every system waited for it
-// (10.3 against 9.75 ms for 12 systems on 48^3x96, 40.8 GB at 4.2 TB/s).  Starts by writing LDS (the caller must have passed a barrier since the
+// xs.  The spinor above the upper face is on its way during the in-block hops, in the registers of e, which
+// is read again for the diagonal at the end: fetched where it is staged, every system waited for it
+// (10.3 against 9.8 ms for 12 systems on 48^3x96, 40.8 GB).  Taking the diagonal first would spare
+// the second read, 9.65 ms, but add the hops to the larger sum: 1.1e-7 from the exact result instead of 9.8e-8;
+// keeping e spills (10.2).  Starts by writing LDS (the caller must have passed a barrier since the
 // last reads of xs and gb) and ends after the last reads, without a barrier.
 // k_sap_half_44 takes the same steps written out in its residual: called there,
 // the compiler allocates that kernel's registers differently and spills one
@@ -985,8 +987,7 @@ __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, 
         }
     }
 #pragma unroll
-    for (int i = 0; i < 12; ++i) acc.v[i] = cmk(-0.f, -0.f);  // -0 + t = t: the first term is stored
-    clover_acc(A, twist, e, acc);
+    for (int i = 0; i < 12; ++i) acc.v[i] = cmk(-0.f, -0.f);  // -0 + t = t: the first hop is stored
     Spinor<float> hu;
     load_spinor<float, S>(xx, xsc, g.V, up_site, hu);
     __syncthreads();
@@ -1014,6 +1015,10 @@ __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, 
             default: s44_stage_forward<1>(g, hu, up_wrap, sm.xs, l); break;
         }
     }
+    Spinor<float> again;  // x at the own site
+    int own = (int)hx.s;
+    asm volatile("" : "+v"(own));
+    load_spinor<float, S>(xx, xsc, g.V, own, again);
     __syncthreads();
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -1024,6 +1029,7 @@ __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, 
             forward_accumulate(mu, gg, acc);
         }
     }
+    clover_acc(A, twist, again, acc);
 }
 
 // ---------------------------------------------------------------------------
