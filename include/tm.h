@@ -44,7 +44,11 @@
  * Errors: negative return values are errors and leave outputs unspecified;
  * tm_last_error() returns a thread-local message for the last failure.
  * Calls are not re-entrant on one stream: two calls that overlap on the same
- * device share the library's scratch buffers and race.
+ * device share the library's scratch buffers and race.  tm_dirac_apply and
+ * tm_sap_smooth use them with canonical buffers only, so that on internal
+ * buffers they may overlap a call on another stream.  That holds when they
+ * build a gauge copy as well (its scratch is its own, and free again on
+ * return), unless it replaces a copy that the other call reads.
  */
 #ifndef TM_H
 #define TM_H

@@ -170,6 +170,10 @@ Geo make_geo(const tm_geom* geom, const int tile[4]) {
 
 Prec clover_prec_for(Prec link_p) { return (link_p == P_F16 || link_p == P_BF16) ? P_F32 : link_p; }
 
+// Staged links of a gauge build: what a build asks for (more where a row of tiles needs more), and what is kept
+// from one build to the next (a row of 4^4 tiles up to 64^3 slices)
+constexpr size_t kGaugeStage = (size_t)256 << 20, kGaugeStageKept = (size_t)1 << 30;
+
 // Links + clover derived from U at (link precision, tile).  A nonzero tag
 // reuses a copy made for the same (U, tag, dims, tile, kappa, c_sw,
 // precision); tag 0 rebuilds into a reusable tag-0 slot of matching size.
@@ -251,20 +255,21 @@ int get_gauge(DeviceState* ds, const Geo& g, const void* U, double kappa, double
         if ((h = launch_clover_to_f32(g, c64->dev.clover, slot->dev.clover, st)) != hipSuccess)
             return hip_fail(h, "clover conversion");
     } else {
-        // the links are staged in the canonical-buffer workspace: as much of it as there is, at least
-        // 256 MiB of slices (or the lattice, or one row of tiles, if that is less / more); without the memory
-        // the build reads the canonical links
+        // the links are staged in a workspace of their own (ds->io may be in use by a call on another stream):
+        // kGaugeStage bytes of slices (or the lattice, or one row of tiles, if that is less / more); without the
+        // memory the build reads the canonical links
         const size_t whole = gauge_stage_bytes(g, g.d[0]), row = gauge_stage_bytes(g, std::min(g.d[0], g.lb[0] + 2));
-        const size_t want = std::min(whole, std::max(row, (size_t)256 << 20));
-        if (csw != 0.0 && ds->io.ensure(want) != hipSuccess) (void)hipGetLastError();
-        if ((h = launch_gauge_build(g, link_p, cl_p, U, m4, csw, slot->dev.links, slot->dev.clover, stats, ds->io.ptr,
-                                    ds->io.bytes, st)) != hipSuccess)
+        const size_t want = std::min(whole, std::max(row, kGaugeStage));
+        if (csw != 0.0 && ds->links.ensure(want) != hipSuccess) (void)hipGetLastError();
+        if ((h = launch_gauge_build(g, link_p, cl_p, U, m4, csw, slot->dev.links, slot->dev.clover, stats, ds->links.ptr,
+                                    ds->links.bytes, st)) != hipSuccess)
             return hip_fail(h, "gauge build");
     }
     unsigned host[2];
     if ((h = hipMemcpyAsync(host, stats, sizeof host, hipMemcpyDeviceToHost, st)) != hipSuccess)
         return hip_fail(h, "stats copy");
     if ((h = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(h, "gauge ingest");
+    if (ds->links.bytes > kGaugeStageKept) ds->links.release();  // the stream is done with it
     if (host[1]) return fail(TM_ERR_NONFINITE, "gauge field holds NaN or Inf");
     float dev;
     std::memcpy(&dev, &host[0], sizeof dev);

@@ -39,6 +39,7 @@ struct DeviceState {
     std::vector<std::unique_ptr<GaugeEntry>> gauge;
     DeviceBuffer stats;   // small flags / reductions
     DeviceBuffer io;      // canonical <-> internal staging
+    DeviceBuffer links;   // time slices of the links while a gauge copy is built; idle once get_gauge returns
     DeviceBuffer solver;  // Krylov bases and solver vectors
     DeviceBuffer red;     // reduction partials
 };
