@@ -15,7 +15,8 @@ namespace {
 
 constexpr int kThreads = 256;
 // Up to here (sites times systems) the FP64 operator splits the directions over wavefronts: below, one
-// workgroup of the unsplit kernel or less falls on each compute unit.
+// workgroup of the unsplit kernel or less falls on each compute unit.  All FP64 kernels form the same products and
+// add them in the same order: a system's result is the same bits whatever the number of systems selects.
 constexpr long long kSplitSites = 32768;
 
 // Link from its first two rows, stored as 12 reals (row-major, re/im pairs); third row rebuilt.
@@ -107,15 +108,57 @@ __global__ void __launch_bounds__(kThreads) k_dirac(DiracArgs a) {
     }
 }
 
-// FP64 links on 4^4 tiles (one tile per workgroup): the kernel above reloads the eight links of
-// a site for every system, since at FP64 holding them leaves no registers, and those reloads are
-// most of its HBM traffic (80 GB per 6-system application at 48^3x96 against 22 GB of fields).
-// Here the workgroup stages its tile's own links (two rows each, 96 KiB) in LDS once, and every
-// system takes its forward links there.  The backward links U_mu(x - mu) stay loads from memory:
-// inside the tile they are the links just staged, still in L2, and read from LDS as well they
-// made the compiler spill a kilobyte per lane.  Kept for several FP64 systems in the internal layout: 32^3x64 in
-// 820 us for one system and 490 per system for six, against 800 and 700 with two lanes per site, whose
-// neighbour reads all go to L2.
+// FP64 links on 4^4 tiles (one tile per workgroup), one lane per site, for several systems in the internal layout:
+// the workgroup stages its tile's own links (two rows each, 96 KiB) in LDS once, and every system takes its
+// forward links there.  The backward links U_mu(x - mu) stay loads from memory: inside the tile they are the
+// links just staged, still in L2, and read from LDS as well they made the compiler spill a kilobyte per lane.
+// 32^3x64 in 820 us for one system and 465 per system for six, against 800 and 700 with two lanes per site
+// (k_dirac_pair), whose neighbour reads all go to L2.  Products and sums are those of the pair's two lanes, in
+// their order; the phase after the projection, on 6 numbers instead of 12, took 2 to 5 % off.
+template <int MU, int DIR>
+__device__ inline void site_hop(const Geo& g, const Spinor<double>& psi, const cplx<double> u[6], bool wrap,
+                                PairAcc<double> acc[2]) {
+    // boundary phase (1 for hops inside the lattice), branch-free: fewer registers
+    const cplx<double> ph = cmk(wrap ? g.bcr[MU] : 1.0, wrap ? (DIR > 0 ? g.bci[MU] : -g.bci[MU]) : 0.0);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const double s = c != 0 ? 1.0 : -1.0;
+        Col<double> p, q, h, t;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            p.v[k] = psi.v[3 * c + k];
+            q.v[k] = psi.v[3 * (pair_cross(MU) ? 3 - c : 2 + c) + k];
+        }
+        pair_project<MU, DIR>(p, q, s, h);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) h.v[k] = mul_fixed(ph, h.v[k]);
+        if constexpr (DIR > 0)
+            pair_mul_fixed(u, h, t);
+        else
+            pair_dag_mul_fixed(u, h, t);
+        pair_accumulate<MU, DIR>(t, s, acc[c]);
+    }
+}
+
+// Both hops of direction MU into the site; `fwd` its own link.
+template <int MU>
+__device__ inline void site_dir(const DiracArgs& a, const void* in, const cplx<double> fwd[6], const int nf[4],
+                                const int nbk[4], unsigned wrap, PairAcc<double> acc[2]) {
+    Spinor<double> p;
+    load_spinor<double, double>(in, nullptr, a.g.V, nf[MU], p);
+    site_hop<MU, +1>(a.g, p, fwd, wrap & (1u << MU), acc);
+    cplx<double> u[6];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        double w[4];
+        Unit<double>::load(a.links, (size_t)(3 * MU + q) * a.g.V + nbk[MU], w);
+        u[2 * q] = cmk(w[0], w[1]);
+        u[2 * q + 1] = cmk(w[2], w[3]);
+    }
+    load_spinor<double, double>(in, nullptr, a.g.V, nbk[MU], p);
+    site_hop<MU, -1>(a.g, p, u, wrap & (16u << MU), acc);
+}
+
 __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
     __shared__ double2 lk[4][6][kThreads];  // [mu][row-major pair][site in tile]
     const Geo& g = a.g;
@@ -137,60 +180,48 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
     Clover<double> A;
     load_clover<double, double>(a.clover, g.V, s, A);
     __syncthreads();
-    const size_t in_stride = (size_t)6 * g.V * Unit<double>::bytes;
-    const size_t out_stride = (size_t)6 * g.V * Unit<double>::bytes;
+    const size_t stride = (size_t)6 * g.V * Unit<double>::bytes;
     const int sys_begin = blockIdx.y * a.sys_tile;
     const int sys_end = min(a.nsys, sys_begin + a.sys_tile);
     for (int sys = sys_begin; sys < sys_end; ++sys) {
-        const void* in = reinterpret_cast<const char*>(a.in) + sys * in_stride;
-        const float* isc = a.in_scale ? a.in_scale + (size_t)sys * g.V : nullptr;
+        const void* in = reinterpret_cast<const char*>(a.in) + sys * stride;
         // the thread index again through a barrier the compiler cannot see through: the LDS reads
         // of the links do not depend on the system, and hoisted out of this loop they would be
         // held in registers
         int lx = l;
         asm volatile("" : "+v"(lx));
-        Spinor<double> acc;
+        const auto own = [&](int mu, cplx<double> u[6]) {
 #pragma unroll
-        for (int i = 0; i < 12; ++i) acc.v[i] = cmk(0.0, 0.0);
-#pragma unroll
-        for (int mu = 0; mu < 4; ++mu) {
-            Link<double> L;
-            Spinor<double> p;
-            {
-                double u[12];
-#pragma unroll
-                for (int k = 0; k < 6; ++k) {
-                    const double2 t = lk[mu][k][lx];
-                    u[2 * k] = t.x;
-                    u[2 * k + 1] = t.y;
-                }
-                link_from_rows(u, L);
+            for (int k = 0; k < 6; ++k) {
+                const double2 v = lk[mu][k][lx];
+                u[k] = cmk(v.x, v.y);
             }
-            load_spinor<double, double>(in, isc, g.V, nf[mu], p);
-            {  // boundary phase (1 for hops inside the lattice)
-                const bool w = wrap & (1u << mu);
-                const double re = w ? g.bcr[mu] : 1.0, im = w ? g.bci[mu] : 0.0;
+        };
+        PairAcc<double> acc[2];
+        pair_zero(acc[0]);
+        pair_zero(acc[1]);
+        cplx<double> u[6];
+        own(0, u);
+        site_dir<0>(a, in, u, nf, nbk, wrap, acc);
+        own(1, u);
+        site_dir<1>(a, in, u, nf, nbk, wrap, acc);
+        own(2, u);
+        site_dir<2>(a, in, u, nf, nbk, wrap, acc);
+        own(3, u);
+        site_dir<3>(a, in, u, nf, nbk, wrap, acc);
+        Spinor<double> self, hop, out;
 #pragma unroll
-                for (int i = 0; i < 12; ++i) p.v[i] = cmk(re * p.v[i].re - im * p.v[i].im, re * p.v[i].im + im * p.v[i].re);
-            }
-            hop_forward(mu, L, p, 1.0, acc);
-            load_link<double, double>(a.links, g.V, nbk[mu], mu, L);
-            load_spinor<double, double>(in, isc, g.V, nbk[mu], p);
-            {
-                const bool w = wrap & (16u << mu);
-                const double re = w ? g.bcr[mu] : 1.0, im = w ? -g.bci[mu] : 0.0;
-#pragma unroll
-                for (int i = 0; i < 12; ++i) p.v[i] = cmk(re * p.v[i].re - im * p.v[i].im, re * p.v[i].im + im * p.v[i].re);
-            }
-            hop_backward(mu, L, p, 1.0, acc);
+        for (int k = 0; k < 3; ++k) {  // as pair_finish
+            hop.v[k] = acc[0].up.v[k];
+            hop.v[3 + k] = acc[1].up.v[k];
+            hop.v[6 + k] = acc[0].same.v[k] + acc[1].cross.v[k];
+            hop.v[9 + k] = acc[0].cross.v[k] + acc[1].same.v[k];
         }
-        Spinor<double> self, out;
-        load_spinor<double, double>(in, isc, g.V, s, self);
+        load_spinor<double, double>(in, nullptr, g.V, s, self);
         clover_apply(A, a.mu[sys] + g.mu_shift[par], self, out);
 #pragma unroll
-        for (int i = 0; i < 12; ++i) out.v[i] = out.v[i] - 0.5 * acc.v[i];
-        store_spinor<double, double>(reinterpret_cast<char*>(a.out) + sys * out_stride,
-                                 a.out_scale ? a.out_scale + (size_t)sys * g.V : nullptr, g.V, s, out);
+        for (int i = 0; i < 12; ++i) out.v[i] = out.v[i] - 0.5 * hop.v[i];
+        store_spinor<double, double>(reinterpret_cast<char*>(a.out) + sys * stride, nullptr, g.V, s, out);
     }
 }
 
@@ -236,22 +267,22 @@ struct Canonical {
     static constexpr bool kCanonical = true;
 };
 
+// The product that one hop adds (pair_accumulate).
 template <int MU, int DIR, class F>
-__device__ inline void hop_add(const Geo& g, const typename F::Raw& psi, const cplx<double> u[6], bool wrap, int c,
-                               double s, PairAcc<double>& acc) {
-    Col<double> p, q, h, t;
+__device__ inline void hop_term(const Geo& g, const typename F::Raw& psi, const cplx<double> u[6], bool wrap, int c,
+                                double s, Col<double>& t) {
+    Col<double> p, q, h;
     F::template spins<MU>(psi, c, p, q);
     pair_project<MU, DIR>(p, q, s, h);
     if (wrap) {  // boundary phase
         const cplx<double> ph = cmk(g.bcr[MU], DIR > 0 ? g.bci[MU] : -g.bci[MU]);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) h.v[k] = ph * h.v[k];
+        for (int k = 0; k < 3; ++k) h.v[k] = mul_fixed(ph, h.v[k]);
     }
     if constexpr (DIR > 0)
-        pair_mul(u, h, t);
+        pair_mul_fixed(u, h, t);
     else
-        pair_dag_mul(u, h, t);
-    pair_accumulate<MU, DIR>(t, s, acc);
+        pair_dag_mul_fixed(u, h, t);
 }
 
 // The site's neighbours: tiled (links) and, for canonical fields, lexicographic.
@@ -289,19 +320,31 @@ template <bool CANON> __device__ inline void pair_site(const Geo& g, long long s
     }
 }
 
+// What both hops of direction MU need from memory.
+template <class F> struct DirOperands {
+    cplx<double> uf[6], ub[6];
+    typename F::Raw pf, pb;
+};
+template <int MU, class F>
+__device__ inline void dir_read(const DiracArgs& a, const F& in, const PairSite& t, int c, DirOperands<F>& d) {
+    in.template read<MU>(F::kCanonical ? t.cf[MU] : t.nf[MU], c, d.pf);
+    link_read<MU>(a.links, a.g.V, t.s, c, d.uf);
+    in.template read<MU>(F::kCanonical ? t.cb[MU] : t.nbk[MU], c, d.pb);
+    link_read<MU>(a.links, a.g.V, t.nbk[MU], c, d.ub);
+}
+
 // Both hops of direction MU.
 template <int MU, class F>
 __device__ inline void dir_add(const DiracArgs& a, const F& in, const PairSite& t, int c, double s,
                                PairAcc<double>& acc) {
     __builtin_amdgcn_sched_barrier(0);  // one direction's operands live at a time
-    cplx<double> uf[6], ub[6];
-    typename F::Raw pf, pb;
-    in.template read<MU>(F::kCanonical ? t.cf[MU] : t.nf[MU], c, pf);
-    link_read<MU>(a.links, a.g.V, t.s, c, uf);
-    in.template read<MU>(F::kCanonical ? t.cb[MU] : t.nbk[MU], c, pb);
-    link_read<MU>(a.links, a.g.V, t.nbk[MU], c, ub);
-    hop_add<MU, +1, F>(a.g, pf, uf, t.wrap & (1u << MU), c, s, acc);
-    hop_add<MU, -1, F>(a.g, pb, ub, t.wrap & (16u << MU), c, s, acc);
+    DirOperands<F> d;
+    dir_read<MU>(a, in, t, c, d);
+    Col<double> v;
+    hop_term<MU, +1, F>(a.g, d.pf, d.uf, t.wrap & (1u << MU), c, s, v);
+    pair_accumulate<MU, +1>(v, s, acc);
+    hop_term<MU, -1, F>(a.g, d.pb, d.ub, t.wrap & (16u << MU), c, s, v);
+    pair_accumulate<MU, -1>(v, s, acc);
     pin(acc);
     __builtin_amdgcn_sched_barrier(0);
 }
@@ -363,10 +406,30 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
     site_finish<F, So>(a, sys, t, c, A, on, acc);
 }
 
-// 32 sites of one system per workgroup, wavefront w on direction w, summed through LDS.
+// 32 sites of one system per workgroup, wavefront w on direction w; the products meet in LDS, and the first
+// wavefront adds them up in k_dirac_pair's order.
+template <int MU, class F>
+__device__ inline void dir_terms(const DiracArgs& a, const F& in, const PairSite& t, int c, double s, Col<double>& f,
+                                 Col<double>& b) {
+    DirOperands<F> d;
+    dir_read<MU>(a, in, t, c, d);
+    hop_term<MU, +1, F>(a.g, d.pf, d.uf, t.wrap & (1u << MU), c, s, f);
+    hop_term<MU, -1, F>(a.g, d.pb, d.ub, t.wrap & (16u << MU), c, s, b);
+}
+template <int MU>
+__device__ inline void dir_sum(const double2 (&part)[3][6][64], int lane, double s, PairAcc<double>& acc) {
+    Col<double> v;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v.v[k] = cmk(part[MU - 1][k][lane].x, part[MU - 1][k][lane].y);
+    pair_accumulate<MU, +1>(v, s, acc);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v.v[k] = cmk(part[MU - 1][3 + k][lane].x, part[MU - 1][3 + k][lane].y);
+    pair_accumulate<MU, -1>(v, s, acc);
+}
+
 template <class F, class So>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) k_dirac_pair_split(DiracArgs a) {
-    __shared__ double2 part[3][9][64];
+    __shared__ double2 part[3][6][64];
     const Geo& g = a.g;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 1;
     const double s = c != 0 ? 1.0 : -1.0;
@@ -378,29 +441,29 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
     double A[36];
     if (w == 0) clover_read(a, (size_t)t.s, c, A);
     const F in(a.in, a.in_scale, sys, g);
-    PairAcc<double> acc;
-    pair_zero(acc);
+    Col<double> f, b;
     switch (w) {
-        case 0: dir_add<0>(a, in, t, c, s, acc); break;
-        case 1: dir_add<1>(a, in, t, c, s, acc); break;
-        case 2: dir_add<2>(a, in, t, c, s, acc); break;
-        default: dir_add<3>(a, in, t, c, s, acc); break;
+        case 0: dir_terms<0>(a, in, t, c, s, f, b); break;
+        case 1: dir_terms<1>(a, in, t, c, s, f, b); break;
+        case 2: dir_terms<2>(a, in, t, c, s, f, b); break;
+        default: dir_terms<3>(a, in, t, c, s, f, b); break;
     }
-    cplx<double>* v[9] = {&acc.up.v[0],   &acc.up.v[1],    &acc.up.v[2],    &acc.same.v[0], &acc.same.v[1],
-                          &acc.same.v[2], &acc.cross.v[0], &acc.cross.v[1], &acc.cross.v[2]};
     if (w > 0) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) part[w - 1][i][lane] = make_double2(v[i]->re, v[i]->im);
+        for (int k = 0; k < 3; ++k) {
+            part[w - 1][k][lane] = make_double2(f.v[k].re, f.v[k].im);
+            part[w - 1][3 + k][lane] = make_double2(b.v[k].re, b.v[k].im);
+        }
     }
     __syncthreads();
     if (w > 0) return;
-#pragma unroll
-    for (int i = 0; i < 9; ++i)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const double2 p = part[q][i][lane];
-            *v[i] = *v[i] + cmk(p.x, p.y);
-        }
+    PairAcc<double> acc;
+    pair_zero(acc);
+    pair_accumulate<0, +1>(f, s, acc);
+    pair_accumulate<0, -1>(b, s, acc);
+    dir_sum<1>(part, lane, s, acc);
+    dir_sum<2>(part, lane, s, acc);
+    dir_sum<3>(part, lane, s, acc);
     site_finish<F, So>(a, sys, t, c, A, on, acc);
 }
 

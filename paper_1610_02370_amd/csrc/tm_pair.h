@@ -139,6 +139,25 @@ __device__ inline void pair_spins(const Chir<R>& v, bool lower, Col<R>& p, Col<R
     }
 }
 
+// Complex products in FP64 as fused multiply-adds written out: where a product could be fused with either of two
+// sums the compiler chooses by what surrounds it, and two kernels would round one system's result differently.
+__device__ inline double fuse(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline cplx<double> mul_fixed(cplx<double> a, cplx<double> b) {  // a b
+    return cmk(fuse(-a.im, b.im, a.re * b.re), fuse(a.im, b.re, a.re * b.im));
+}
+__device__ inline cplx<double> dag_fixed(cplx<double> a, cplx<double> b) {  // conj(a) b
+    return cmk(fuse(a.im, b.im, a.re * b.re), fuse(-a.im, b.re, a.re * b.im));
+}
+__device__ inline cplx<double> mad_fixed(cplx<double> a, cplx<double> b, cplx<double> c) {  // a b + c
+    return cmk(fuse(-a.im, b.im, fuse(a.re, b.re, c.re)), fuse(a.im, b.re, fuse(a.re, b.im, c.im)));
+}
+__device__ inline cplx<double> dagmad_fixed(cplx<double> a, cplx<double> b, cplx<double> c) {  // conj(a) b + c
+    return cmk(fuse(a.im, b.im, fuse(a.re, b.re, c.re)), fuse(-a.im, b.re, fuse(a.re, b.im, c.im)));
+}
+__device__ inline cplx<double> cross_fixed(cplx<double> a, cplx<double> b, cplx<double> c, cplx<double> d) {
+    return conj(mad_fixed(-c, d, mul_fixed(a, b)));  // conj(a b - c d)
+}
+
 // g = U h and g = U^+ h for one colour vector; U from its first two rows u (row-major).
 template <class R> __device__ inline void pair_mul(const cplx<R> u[6], const Col<R>& h, Col<R>& g) {
     const cplx<R> a = conj(u[1] * u[5] - u[2] * u[4]), b = conj(u[2] * u[3] - u[0] * u[5]),
@@ -153,6 +172,21 @@ template <class R> __device__ inline void pair_dag_mul(const cplx<R> u[6], const
 #pragma unroll
     for (int i = 0; i < 3; ++i)
         g.v[i] = cjmad(r[i], h.v[2], cjmad(u[3 + i], h.v[1], conj(u[i]) * h.v[0]));
+}
+// The same in FP64 with a fixed rounding.
+__device__ inline void pair_mul_fixed(const cplx<double> u[6], const Col<double>& h, Col<double>& g) {
+    const cplx<double> r[9] = {u[0], u[1], u[2], u[3], u[4], u[5], cross_fixed(u[1], u[5], u[2], u[4]),
+                               cross_fixed(u[2], u[3], u[0], u[5]), cross_fixed(u[0], u[4], u[1], u[3])};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        g.v[i] = mad_fixed(r[3 * i + 2], h.v[2], mad_fixed(r[3 * i + 1], h.v[1], mul_fixed(r[3 * i], h.v[0])));
+}
+__device__ inline void pair_dag_mul_fixed(const cplx<double> u[6], const Col<double>& h, Col<double>& g) {
+    const cplx<double> r[3] = {cross_fixed(u[1], u[5], u[2], u[4]), cross_fixed(u[2], u[3], u[0], u[5]),
+                               cross_fixed(u[0], u[4], u[1], u[3])};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        g.v[i] = dagmad_fixed(r[i], h.v[2], dagmad_fixed(u[3 + i], h.v[1], dag_fixed(u[i], h.v[0])));
 }
 
 // Plane k of a field of V units per plane: the same address for every lane, so that the planes of one

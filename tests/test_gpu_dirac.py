@@ -250,3 +250,50 @@ def test_clover_build_boxes(dims):
     announce(f"clover boxes dims={dims}")
     got = host(tm.tm_dirac_apply(dims, dev(U), dev(psi), 0.14, [0.1], 1.3))
     check_close(got[0], ref, "dirac", "f64", f"clover boxes {dims}")
+
+
+# 20480 (4^4 tiles) and 20160 sites: one system alone has its directions split over wavefronts, several together have
+# not, and in internal buffers on 4^4 tiles they take the kernel with one lane per site.  One order of sums for all.
+@pytest.mark.parametrize("dims", [(8, 8, 16, 20), (7, 9, 16, 20)])
+def test_system_of_a_batch_is_bit_identical_to_it_alone(dims):
+    import torch
+
+    mus = [0.1, -0.02, 0.3]
+    U, psi = dev(synth.gauge_field(dims, 0.6, seed=93)), dev(synth.gaussian_spinor(dims, len(mus), seed=193))
+    kw = dict(antiperiodic_t=True, theta=(0.2, 0.3, -0.9, 0.5), mu_shift=(0.03, -0.02), gauge_tag=9)
+    announce(f"batch and single applications dims={dims}")
+
+    def internal(p, m):
+        n = tm.tm_spinor_bytes(dims, len(m), "f64")
+        a, b = (torch.zeros(n // 8, dtype=torch.float64, device="cuda") for _ in range(2))
+        tm.tm_spinor_import(dims, p, a, storage="f64")
+        tm.tm_dirac_apply(dims, U, a, 0.14, m, 1.2, b, io="internal", **kw)
+        return tm.tm_spinor_export(dims, b, torch.empty_like(p), storage="f64")
+
+    batch = tm.tm_dirac_apply(dims, U, psi, 0.14, mus, 1.2, **kw)
+    assert torch.equal(internal(psi, mus), batch)
+    for k, m in enumerate(mus):
+        p = psi[k:k + 1].contiguous()
+        assert torch.equal(tm.tm_dirac_apply(dims, U, p, 0.14, [m], 1.2, **kw), batch[k:k + 1])
+        assert torch.equal(internal(p, [m]), batch[k:k + 1])
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16"])
+def test_flexible_steps_of_a_batch_are_bit_identical_to_single_ones(storage):
+    # the FP64 operator on vectors of the smoother's precision, split over wavefronts for one system and not for two
+    import torch
+
+    dims, mus = (8, 8, 16, 24), [0.001, -0.002]
+    U, b = dev(synth.gauge_field(dims, 0.5, seed=94)), dev(synth.gaussian_spinor(dims, 2, seed=194))
+    announce(f"flexible steps, batch and single, {storage}")
+
+    def solve(k0, k1):
+        x = torch.zeros_like(b[k0:k1])
+        tm.tm_fgmres_solve(dims, U, b[k0:k1].contiguous(), x, 0.1373, mus[k0:k1], 1.5, 1e-12, storage=storage,
+                           form="flexible", restart=10, n_cycles=2, mr_iters=3, block_dims=(4, 4, 4, 4), x_in=False,
+                           max_iters=6, gauge_tag=11)
+        return x
+
+    both = solve(0, 2)
+    for k in range(2):
+        assert torch.equal(solve(k, k + 1), both[k:k + 1])
