@@ -108,9 +108,9 @@ __global__ void __launch_bounds__(kThreads) k_dirac(DiracArgs a) {
     }
 }
 
-// FP64 links on 4^4 tiles (one tile per workgroup), one lane per site, for several systems in the internal layout:
-// the workgroup stages its tile's own links (two rows each, 96 KiB) in LDS once, and every system takes its
-// forward links there.  The backward links U_mu(x - mu) stay loads from memory: inside the tile they are the
+// FP64, one lane per site, for several systems in the internal layout.  STAGED (4^4 tiles, one per workgroup): the
+// workgroup stages its tile's own links (two rows each, 96 KiB) in LDS once, and every system takes its
+// forward links there; on other tiles they too come from memory per system.  The backward links U_mu(x - mu) stay loads from memory: inside the tile they are the
 // links just staged, still in L2, and read from LDS as well they made the compiler spill a kilobyte per lane.
 // 32^3x64 in 820 us for one system and 465 per system for six, against 800 and 700 with two lanes per site
 // (k_dirac_pair), whose neighbour reads all go to L2.  Products and sums are those of the pair's two lanes, in
@@ -159,41 +159,49 @@ __device__ inline void site_dir(const DiracArgs& a, const void* in, const cplx<d
     site_hop<MU, -1>(a.g, p, u, wrap & (16u << MU), acc);
 }
 
+template <bool STAGED>
 __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
-    __shared__ double2 lk[4][6][kThreads];  // [mu][row-major pair][site in tile]
+    __shared__ double2 lk[STAGED ? 4 : 1][6][STAGED ? kThreads : 1];  // [mu][row-major pair][site in tile]
     const Geo& g = a.g;
     const long long tile = xcd_swizzle(blockIdx.x, gridDim.x);
     const int l = threadIdx.x;
-    const long long s = tile * kThreads + l;  // V is a multiple of the tile size
+    const long long s = tile * kThreads + l;  // staged: V is a multiple of the tile size
     const double2* src = reinterpret_cast<const double2*>(a.links);
+    if constexpr (STAGED) {
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu)
+        for (int mu = 0; mu < 4; ++mu)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {  // unit q of a link holds 4 reals: pairs 2q and 2q+1
-            const size_t u = ((size_t)mu * 3 + q) * g.V + s;
-            lk[mu][2 * q][l] = src[2 * u];
-            lk[mu][2 * q + 1][l] = src[2 * u + 1];
-        }
+            for (int q = 0; q < 3; ++q) {  // unit q of a link holds 4 reals: pairs 2q and 2q+1
+                const size_t u = ((size_t)mu * 3 + q) * g.V + s;
+                lk[mu][2 * q][l] = src[2 * u];
+                lk[mu][2 * q + 1][l] = src[2 * u + 1];
+            }
+    } else if (s >= g.V) {
+        return;
+    }
     int nf[4], nbk[4], par;
     unsigned wrap;
     tiled_neighbours(g, s, nf, nbk, &wrap, &par);
     Clover<double> A;
     load_clover<double, double>(a.clover, g.V, s, A);
-    __syncthreads();
+    if constexpr (STAGED) __syncthreads();
     const size_t stride = (size_t)6 * g.V * Unit<double>::bytes;
     const int sys_begin = blockIdx.y * a.sys_tile;
     const int sys_end = min(a.nsys, sys_begin + a.sys_tile);
     for (int sys = sys_begin; sys < sys_end; ++sys) {
         const void* in = reinterpret_cast<const char*>(a.in) + sys * stride;
-        // the thread index again through a barrier the compiler cannot see through: the LDS reads
-        // of the links do not depend on the system, and hoisted out of this loop they would be
-        // held in registers
-        int lx = l;
-        asm volatile("" : "+v"(lx));
+        // the thread index again through a barrier the compiler cannot see through: the reads of the
+        // links do not depend on the system, and hoisted out of this loop they would be held in
+        // registers
+        const int lx = opaque(l);
         const auto own = [&](int mu, cplx<double> u[6]) {
 #pragma unroll
             for (int k = 0; k < 6; ++k) {
-                const double2 v = lk[mu][k][lx];
+                double2 v;
+                if constexpr (STAGED)
+                    v = lk[mu][k][lx];
+                else
+                    v = src[2 * (((size_t)mu * 3 + k / 2) * g.V + tile * kThreads + lx) + k % 2];
                 u[k] = cmk(v.x, v.y);
             }
         };
@@ -516,13 +524,21 @@ hipError_t launch_dirac(const DiracArgs& a, Prec in_p, Prec out_p, Prec link_p, 
 #undef TM_CASE
     if (out_p == P_F64 && link_p == P_F64 && clover_p == P_F64 && compute == P_F64) {
         const int* lb = a.g.lb;
-        if (in_p == P_F64 && a.nsys > 1 && lb[0] == 4 && lb[1] == 4 && lb[2] == 4 && lb[3] == 4 &&
-            a.g.V * a.nsys > kSplitSites) {
+        const bool is44 = lb[0] == 4 && lb[1] == 4 && lb[2] == 4 && lb[3] == 4;
+        // Other tiles (their links stay in memory): from about two workgroups per compute unit on, sooner the more
+        // systems share a site's clover.  One lane per site against two, 2 / 6 / 12 systems: 18^4 59 / 153 / 309 us
+        // against 53 / 156 / 330, 20^2x22^2 105 / 295 / 573 against 117 / 350 / 672, 30^4 474 / 1167 / 2306 against
+        // 532 / 1480 / 2816; below, 15^4 29 / 69 / 128 against 30 / 70 / 126.
+        if (in_p == P_F64 && a.nsys > 1 &&
+            (is44 ? a.g.V * a.nsys > kSplitSites : a.g.V >= (a.nsys < 6 ? 131072 : 98304))) {
             DiracArgs t = a;
-            const unsigned nwg = (unsigned)(a.g.V / kThreads);  // a tile has kThreads sites
+            const unsigned nwg = (unsigned)((a.g.V + kThreads - 1) / kThreads);
             t.sys_tile = pick_sys_tile(nwg, a.nsys, kCUs, 0.4, true);
-            hipLaunchKernelGGL(k_dirac_lk, dim3(nwg, (unsigned)((a.nsys + t.sys_tile - 1) / t.sys_tile)), dim3(kThreads), 0,
-                               st, t);
+            const dim3 grid(nwg, (unsigned)((a.nsys + t.sys_tile - 1) / t.sys_tile));
+            if (is44)
+                hipLaunchKernelGGL(k_dirac_lk<true>, grid, dim3(kThreads), 0, st, t);
+            else
+                hipLaunchKernelGGL(k_dirac_lk<false>, grid, dim3(kThreads), 0, st, t);
             return hipGetLastError();
         }
         if (in_p == P_F64) return run_pair<FieldOf<double>, double>(a, st);
