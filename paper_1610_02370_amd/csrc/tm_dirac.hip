@@ -525,14 +525,17 @@ hipError_t launch_dirac(const DiracArgs& a, Prec in_p, Prec out_p, Prec link_p, 
     if (out_p == P_F64 && link_p == P_F64 && clover_p == P_F64 && compute == P_F64) {
         const int* lb = a.g.lb;
         const bool is44 = lb[0] == 4 && lb[1] == 4 && lb[2] == 4 && lb[3] == 4;
-        // Other tiles (their links stay in memory): from about two workgroups per compute unit on, sooner the more
-        // systems share a site's clover.  One lane per site against two, 2 / 6 / 12 systems: 18^4 59 / 153 / 309 us
-        // against 53 / 156 / 330, 20^2x22^2 105 / 295 / 573 against 117 / 350 / 672, 30^4 474 / 1167 / 2306 against
-        // 532 / 1480 / 2816; below, 15^4 29 / 69 / 128 against 30 / 70 / 126.
+        const unsigned nwg = (unsigned)((a.g.V + kThreads - 1) / kThreads), rounds = (nwg + kCUs - 1) / kCUs;
+        // Other tiles (their links stay in memory): one lane per site reads a site's clover once for all systems,
+        // but holds one workgroup per compute unit, so its time goes in rounds of 256 of them.  It is taken where
+        // these are at least 3/4 full, from 640 workgroups on or with six or more systems.  One lane against two,
+        // 2 / 6 / 12 systems: 16^4 (256 workgroups) 37 / 83 / 162 us against 34 / 92 / 191, 18^3x14 (319) 54 / 135 / 275
+        // against 40 / 107 / 230, 18^4 (411) 59 / 153 / 309 against 53 / 156 / 330, 20x22^2x20 (757) 105 / 295 / 573
+        // against 117 / 350 / 672, 30^4 474 / 1167 / 2306 against 532 / 1480 / 2816.
+        const bool full = nwg >= (unsigned)kCUs && 4 * nwg >= 3 * kCUs * rounds;
         if (in_p == P_F64 && a.nsys > 1 &&
-            (is44 ? a.g.V * a.nsys > kSplitSites : a.g.V >= (a.nsys < 6 ? 131072 : 98304))) {
+            (is44 ? a.g.V * a.nsys > kSplitSites : full && (nwg >= 640 || a.nsys >= 6))) {
             DiracArgs t = a;
-            const unsigned nwg = (unsigned)((a.g.V + kThreads - 1) / kThreads);
             t.sys_tile = pick_sys_tile(nwg, a.nsys, kCUs, 0.4, true);
             const dim3 grid(nwg, (unsigned)((a.nsys + t.sys_tile - 1) / t.sys_tile));
             if (is44)

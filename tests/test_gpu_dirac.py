@@ -253,9 +253,9 @@ def test_clover_build_boxes(dims):
 
 
 # 20480 (4^4 tiles) and 20160 sites: one system alone has its directions split over wavefronts, several together have
-# not, and in internal buffers on 4^4 tiles, or on other tiles from 131072 sites on, they take the kernel with one lane
-# per site (the last workgroup partly filled).  One order of sums for all.
-@pytest.mark.parametrize("dims", [(8, 8, 16, 20), (7, 9, 16, 20), (18, 18, 20, 22)])
+# not, and in internal buffers on 4^4 tiles, or on other tiles where these fill the device (23^2x19^2, the last workgroup
+# partly filled), they take the kernel with one lane per site.  One order of sums for all.
+@pytest.mark.parametrize("dims", [(8, 8, 16, 20), (7, 9, 16, 20), (23, 19, 19, 23)])
 def test_system_of_a_batch_is_bit_identical_to_it_alone(dims):
     import torch
 
