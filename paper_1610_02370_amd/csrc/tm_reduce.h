@@ -54,12 +54,22 @@ __device__ constexpr R min_normal() {
     return sizeof(R) == 8 ? (R)2.2250738585072014e-308 : (R)1.17549435e-38f;
 }
 
-// Sum of three values over the workgroup; every thread gets the result.
+// The same by lane exchanges, for the FP64 kernel on blocks of up to 256 sites other than 4^4, which is 2 to 4 %
+// faster with it (2^4 blocks on 16x12^3, 6 systems: 1195 us against 1240; the other FP64 kernels, on 8x4^3 blocks, are
+// 10 to 18 % slower).
 template <class R>
+__device__ inline R wave_sum_xor(R v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Sum of three values over the workgroup; every thread gets the result.
+template <bool XOR = false, class R>
 __device__ inline void block_sum3(R* red, R& a, R& b, R& c) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    c = wave_sum(c);
+    a = XOR ? wave_sum_xor(a) : wave_sum(a);
+    b = XOR ? wave_sum_xor(b) : wave_sum(b);
+    c = XOR ? wave_sum_xor(c) : wave_sum(c);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
     if (lane == 0) {
         red[4 * w] = a;

@@ -344,7 +344,7 @@ __global__ void __launch_bounds__(MAXT) k_sap_half(SapArgs a) {
                 gen_block_hops_add<G, R, LC>(a, t, sh, nt, l, (R)-0.5, q, lk);
                 mr_dots(q, rho, qr_re, qr_im, qq);
             }
-            block_sum3(red, qr_re, qr_im, qq);
+            block_sum3<sizeof(R) == 8 && MAXT == 256>(red, qr_re, qr_im, qq);
             if (active && qq >= min_normal<R>()) {
                 const cplx<R> alpha = cmk(qr_re / qq, qr_im / qq);
 #pragma unroll
