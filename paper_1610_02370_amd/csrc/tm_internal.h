@@ -35,9 +35,10 @@ inline size_t spinor_scale_bytes(long long V, int nsys, Prec p) {
 // as the tiles fill the device; with fewer tiles than slots most of the chip idles while each
 // workgroup runs through every system.  The split with the least ceil(workgroups / slots) x
 // (systems + load) is taken, unless a coarser one is within 10 % of it (24^3x32 with 2 FP64 systems,
-// estimated 5 % better, ran 6 % worse).  Results do not depend on the split.  Measured at 16^4 with 12 FP32 systems (128 blocks of a colour, 512 slots): the half-sweep
-// 230 us unsplit, the whole defect-correction solve 31.1 -> 13.4 ms with the split; a 6x10x7x9 FP64
-// application of 3 systems 44 -> 27 us.  At 48^3x96 (20736 blocks) no split is taken.
+// estimated 5 % better, ran 6 % worse).  Results do not depend on the split.  Measured at 16^4 with 12
+// FP32 systems (128 blocks of a colour, 512 slots): the half-sweep 230 us unsplit, the whole
+// defect-correction solve 31.1 -> 13.4 ms with the split; a 6x10x7x9 FP64 application of 3 systems
+// 44 -> 27 us.  At 48^3x96 (20736 blocks) no split is taken.
 //
 // fill_only (the operator kernels, bound by memory): no split once the tiles fill the slots.  Their last,
 // partly filled wave of workgroups runs faster than a full one, so splitting to even it out lost 10 %
@@ -58,6 +59,17 @@ inline int pick_sys_tile(long long blocks, int nsys, int slots, double load, boo
     return best;
 }
 constexpr int kCUs = 256;  // compute units of the MI355X
+
+// Systems per workgroup of the half-sweeps with one thread per site (tm_sap.hip), nt threads per block.  Workgroups
+// per CU: FP32 on up to 256 sites two (LDS of k_sap_half_v2, registers of k_sap_half_44), FP64 there one wavefront
+// per SIMD, one of the others.  The block's links and clover cost about 0.15 of one system's residual and MR
+// steps, 0.4 in FP32 on more than 256 sites.  With one FP64 workgroup per CU and 0.15 throughout, systems were
+// split where the blocks fill the device: 6 systems on 864 blocks of a colour, FP64 4^3x2 2575 us unsplit and 2807
+// split, BF16 8x4^3 19.3 and 20.6 ms.
+inline int sap_sys_tile(long long blocks, int nsys, int nt, bool fp64, bool eo) {
+    const int per_cu = eo || nt > 256 ? 1 : fp64 ? 256 / nt : 2;
+    return pick_sys_tile(blocks, nsys, per_cu * kCUs, nt > 256 && !fp64 && !eo ? 0.4 : 0.15, false);
+}
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 

@@ -1336,13 +1336,7 @@ hipError_t run(const SapArgs& args, hipStream_t st) {
     SapArgs a = args;
     const int nt = (a.g.Vb + 63) & ~63;
     const long long nblocks = (long long)a.g.nb[0] * a.g.nb[1] * a.g.nb[2] * a.g.nb[3];
-    if (a.sys_tile <= 0) {
-        // two workgroups per CU with FP32 arithmetic (of 256 threads; smaller blocks allow more, but
-        // not to count on), one with FP64; the block's links and clover cost about 0.15 of one
-        // system's residual and MR steps
-        const int per_cu = sizeof(R) == 4 && nt <= 256 && !a.eo ? 2 : 1;
-        a.sys_tile = pick_sys_tile(nblocks / 2, a.nsys, per_cu * kCUs, 0.15, false);
-    }
+    if (a.sys_tile <= 0) a.sys_tile = sap_sys_tile(nblocks / 2, a.nsys, nt, sizeof(R) == 8, a.eo);
     dim3 grid((unsigned)(nblocks / 2), (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
     const size_t lds = sap_lds_bytes(a.g.Vb, sizeof(R) == 8 ? P_F64 : P_F32);
     int dev = 0, max_lds = 0;
