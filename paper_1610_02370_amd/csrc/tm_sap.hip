@@ -954,16 +954,17 @@ __device__ inline void s44_stage_forward(const Geo& g, const Spinor<float>& p, b
 // w stages axis w's halo: the backward product of the site below the lower face
 // into the slot of its column's upper-face site, and, once the in-block hops
 // have read xs, the projected half spinor of the site above the upper face into
-// xs.  The spinor above the upper face is on its way during the in-block hops, in the registers of e, which
-// is read again for the diagonal at the end: fetched where it is staged, every system waited for it
-// (10.3 against 9.8 ms for 12 systems on 48^3x96, 40.8 GB).  Taking the diagonal first would spare
+// xs.  AHEAD: the spinor above the upper face is on its way during the in-block hops, in the registers of e,
+// which is read again for the diagonal at the end: fetched where it is staged, every system waited for it
+// (10.3 against 9.8 ms for 12 FP32 systems on 48^3x96, 40.8 GB).  Taking the diagonal first would spare
 // the second read, 9.65 ms, but add the hops to the larger sum: 1.1e-7 from the exact result instead of 9.8e-8;
-// keeping e spills (10.2).  Starts by writing LDS (the caller must have passed a barrier since the
+// keeping e spills (10.2).  Not AHEAD has the same result (run_dirac_44 says where it is taken).
+// Starts by writing LDS (the caller must have passed a barrier since the
 // last reads of xs and gb) and ends after the last reads, without a barrier.
 // k_sap_half_44 takes the same steps written out in its residual: called there,
 // the compiler allocates that kernel's registers differently and spills one
 // more address per system, which cost 3 % of its time.
-template <class S, class G>
+template <bool AHEAD, class S, class G>
 __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, const Geo& g, const void* links, const void* xx, const float* xsc,
                                    int l, const Link<float> Uo[4], const bool fin[4], const int str[4],
                                    const S44Site& hx, int wax, int wmu, const Clover<float>& A, float twist,
@@ -989,7 +990,7 @@ __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, 
 #pragma unroll
     for (int i = 0; i < 12; ++i) acc.v[i] = cmk(-0.f, -0.f);  // -0 + t = t: the first hop is stored
     Spinor<float> hu;
-    load_spinor<float, S>(xx, xsc, g.V, up_site, hu);
+    if constexpr (AHEAD) load_spinor<float, S>(xx, xsc, g.V, up_site, hu);
     __syncthreads();
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -1008,6 +1009,7 @@ __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, 
     __syncthreads();
     // pass 2: the upper-face halo, staged in xs
     {
+        if constexpr (!AHEAD) load_spinor<float, S>(xx, xsc, g.V, up_site, hu);
         switch (wax) {
             case 0: s44_stage_forward<0>(g, hu, up_wrap, sm.xs, l); break;
             case 1: s44_stage_forward<3>(g, hu, up_wrap, sm.xs, l); break;
@@ -1016,9 +1018,11 @@ __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, 
         }
     }
     Spinor<float> again;  // x at the own site
-    int own = (int)hx.s;
-    asm volatile("" : "+v"(own));
-    load_spinor<float, S>(xx, xsc, g.V, own, again);
+    if constexpr (AHEAD) {
+        int own = (int)hx.s;
+        asm volatile("" : "+v"(own));
+        load_spinor<float, S>(xx, xsc, g.V, own, again);
+    }
     __syncthreads();
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -1029,7 +1033,7 @@ __device__ __attribute__((always_inline)) inline void s44_stencil(V2Shared& sm, 
             forward_accumulate(mu, gg, acc);
         }
     }
-    clover_acc(A, twist, again, acc);
+    clover_acc(A, twist, AHEAD ? again : e, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1250,7 +1254,7 @@ __global__ void __launch_bounds__(kV2) __attribute__((amdgpu_waves_per_eu(2, 2))
 // workgroups per compute unit.  The generic k_dirac gathers its eight
 // neighbours per thread from memory and holds its links at one wavefront per
 // SIMD.
-template <class Si, class So, class G, class C>
+template <class Si, class So, class G, class C, bool AHEAD>
 __global__ void __launch_bounds__(kV2) __attribute__((amdgpu_waves_per_eu(2, 2))) k_dirac_44(DiracArgs a) {
     __shared__ V2Shared sm;
     const Geo& g = a.g;
@@ -1309,7 +1313,7 @@ __global__ void __launch_bounds__(kV2) __attribute__((amdgpu_waves_per_eu(2, 2))
 
         Spinor<float> e, acc;
         load_spinor<float, Si>(in, isc, g.V, s, e);
-        s44_stencil<Si, G>(sm, g, a.links, in, isc, l, Uo, fin, str, hx, wax, wmu, A, -2.f * mu_tw, e, acc);
+        s44_stencil<AHEAD, Si, G>(sm, g, a.links, in, isc, l, Uo, fin, str, hx, wax, wmu, A, -2.f * mu_tw, e, acc);
         // out = (A + twist) x - acc / 2, from acc - 2 (A + twist) x
 #pragma unroll
         for (int i = 0; i < 12; ++i) acc.v[i] = -0.5f * acc.v[i];
@@ -1327,7 +1331,17 @@ hipError_t run_dirac_44(const DiracArgs& args, hipStream_t st) {
     // two workgroups per CU; the tile's links and clover cost about 0.4 of one system's stencil
     a.sys_tile = pick_sys_tile(n, a.nsys, 2 * kCUs, 0.4, true);
     const dim3 grid((unsigned)n, (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile));
-    hipLaunchKernelGGL((k_dirac_44<Si, So, G, C>), grid, dim3(kV2), 0, st, a);
+    if constexpr (std::is_same<Si, float>::value) {
+        // Six or more FP32 systems in one workgroup, where the second read of the own spinor finds it in no cache: one
+        // colour's tiles, whose neighbours are no other workgroup's own (12 systems on 32^3x64 1180 us ahead, 1138
+        // not; two systems 276 and 282), or no more tiles than run at once (16^3x32, 12 / 6 / 3 systems 121.5 / 60.3 /
+        // 35.4 us ahead, 117.3 / 59.6 / 37.5 not).  Elsewhere ahead is 1 to 13 % faster.
+        if (a.nsys >= 6 && a.sys_tile == a.nsys && (a.colour >= 0 || n <= 2 * kCUs)) {
+            hipLaunchKernelGGL((k_dirac_44<Si, So, G, C, false>), grid, dim3(kV2), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_dirac_44<Si, So, G, C, true>), grid, dim3(kV2), 0, st, a);
     return hipGetLastError();
 }
 

@@ -298,3 +298,37 @@ def test_flexible_steps_of_a_batch_are_bit_identical_to_single_ones(storage):
     both = solve(0, 2)
     for k in range(2):
         assert torch.equal(solve(k, k + 1), both[k:k + 1])
+
+
+def test_fp32_application_of_one_round_of_tiles():
+    # 512 tiles, as many as run at once, with seven systems in each workgroup: the operator that reads the upper halo
+    # where it is staged; every system alone takes the other one.  The same sums in both.
+    import torch
+
+    dims, mus = (32, 16, 16, 16), [0.01 * (k - 3) for k in range(7)]
+    U, psi = dev(synth.gauge_field(dims, 0.6, seed=95)), dev(synth.gaussian_spinor(dims, len(mus), seed=195))
+    announce("FP32 application, 512 tiles, seven systems")
+    kw = dict(storage="f32", theta=(0.2, 0.3, -0.9, 0.5), gauge_tag=13)
+    batch = tm.tm_dirac_apply(dims, U, psi, 0.14, mus, 1.2, **kw)
+    for k, m in enumerate(mus):
+        assert torch.equal(tm.tm_dirac_apply(dims, U, psi[k:k + 1].contiguous(), 0.14, [m], 1.2, **kw), batch[k:k + 1])
+
+
+def test_defect_correction_steps_of_a_batch_are_bit_identical_to_single_ones():
+    # six systems on 512 tiles of a colour: D z on one colour's tiles from the same operator, two ways as above
+    import torch
+
+    dims, mus = (32, 32, 16, 16), [0.001 * (k - 2) for k in range(6)]
+    U, b = dev(synth.gauge_field(dims, 0.5, seed=96)), dev(synth.gaussian_spinor(dims, len(mus), seed=196))
+    announce("defect-correction steps, batch and single")
+
+    def solve(k0, k1):
+        x = torch.zeros_like(b[k0:k1])
+        tm.tm_fgmres_solve(dims, U, b[k0:k1].contiguous(), x, 0.1373, mus[k0:k1], 1.5, 1e-12, storage="f32",
+                           form="defect_correction", restart=8, n_cycles=2, mr_iters=3, block_dims=(4, 4, 4, 4),
+                           x_in=False, max_iters=4, gauge_tag=15)
+        return x
+
+    batch = solve(0, len(mus))
+    for k in range(len(mus)):
+        assert torch.equal(solve(k, k + 1), batch[k:k + 1])
