@@ -83,11 +83,12 @@ __global__ void __launch_bounds__(kThreads) k_norm2(VecRef x, double* partials, 
 // (<u_i, u>, <u_i, w>) as complex pairs, and with `head` 4 more: <u, u>,
 // <u, w> (complex), <w, w>, for u = u_j.
 //
-// A thread takes one unit (4 reals) of a vector at a time instead of a site's 24: the registers go to the sums,
+// UNIT: a thread takes one unit (4 reals) of a vector at a time instead of a site's 24: the registers go to the sums,
 // and a sweep covers 11 vectors (as many as the reduction's 2 kMaxVec values hold), so that u and w are read
-// once per 11 stored vectors.  32^3x64, 2 systems, FP64, 14 steps: 16.7 ms at 5.8 TB/s; with a site at a time and
-// 4 vectors per sweep 19.9 ms.
-template <class P, int NV>
+// once per 11 stored vectors.  32^3x64, FP64, 2 systems, 14 steps: 16.7 ms at 5.8 TB/s; with a site at a time and
+// 4 vectors per sweep 19.9 ms.  In FP32 it converts and adds to the FP64 sums six times as often as a site at a
+// time with 8 vectors per sweep, which the larger lattices take (kSiteDots).
+template <class P, int NV, bool UNIT>
 __global__ void __launch_bounds__(kThreads) k_dgs_dots(VecRef basis, size_t vec_stride, int i0, int n, VecRef u,
                                                        VecRef w, int head, double* partials, long long V) {
     typedef typename std::conditional<std::is_same<P, double>::value, double, float>::type R;
@@ -100,41 +101,79 @@ __global__ void __launch_bounds__(kThreads) k_dgs_dots(VecRef basis, size_t vec_
     const char* b0 = static_cast<const char*>(basis.data) + (size_t)sys * basis.sys_stride + (size_t)i0 * vec_stride;
     const char* u0 = static_cast<const char*>(u.data) + (size_t)sys * u.sys_stride;
     const char* w0 = static_cast<const char*>(w.data) + (size_t)sys * w.sys_stride;
-    // a + (re, im) of <x, y> over one unit
-    const auto dot = [](const R* x, const R* y, double* a) {
-        R re = x[0] * y[0], im = x[0] * y[1];
-        re += x[1] * y[1];
-        im -= x[1] * y[0];
-        re += x[2] * y[2];
-        im += x[2] * y[3];
-        re += x[3] * y[3];
-        im -= x[3] * y[2];
-        a[0] += (double)re;
-        a[1] += (double)im;
-    };
-    for (long long s = (long long)blockIdx.x * kThreads + threadIdx.x; s < 6 * V; s += (long long)nblk * kThreads) {
-        R uv[4], wv[4], v[NV][4];
-        Unit<P>::load(u0, (size_t)s, uv);
-        Unit<P>::load(w0, (size_t)s, wv);
+    if constexpr (UNIT) {
+        // a + (re, im) of <x, y> over one unit
+        const auto dot = [](const R* x, const R* y, double* a) {
+            R re = x[0] * y[0], im = x[0] * y[1];
+            re += x[1] * y[1];
+            im -= x[1] * y[0];
+            re += x[2] * y[2];
+            im += x[2] * y[3];
+            re += x[3] * y[3];
+            im -= x[3] * y[2];
+            a[0] += (double)re;
+            a[1] += (double)im;
+        };
+        for (long long s = (long long)blockIdx.x * kThreads + threadIdx.x; s < 6 * V; s += (long long)nblk * kThreads) {
+            R uv[4], wv[4], v[NV][4];
+            Unit<P>::load(u0, (size_t)s, uv);
+            Unit<P>::load(w0, (size_t)s, wv);
 #pragma unroll
-        for (int i = 0; i < NV; ++i)
-            if (i < n) Unit<P>::load(b0 + i * vec_stride, (size_t)s, v[i]);
+            for (int i = 0; i < NV; ++i)
+                if (i < n) Unit<P>::load(b0 + i * vec_stride, (size_t)s, v[i]);
 #pragma unroll
-        for (int i = 0; i < NV; ++i)
-            if (i < n) {
-                dot(v[i], uv, acc + 4 * i);
-                dot(v[i], wv, acc + 4 * i + 2);
+            for (int i = 0; i < NV; ++i)
+                if (i < n) {
+                    dot(v[i], uv, acc + 4 * i);
+                    dot(v[i], wv, acc + 4 * i + 2);
+                }
+            if (head) {
+                R uu = 0, ww = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    uu += uv[k] * uv[k];
+                    ww += wv[k] * wv[k];
+                }
+                acc[4 * NV] += (double)uu;
+                dot(uv, wv, acc + 4 * NV + 1);
+                acc[4 * NV + 3] += (double)ww;
             }
-        if (head) {
-            R uu = 0, ww = 0;
+        }
+    } else {
+        for (long long s = (long long)blockIdx.x * kThreads + threadIdx.x; s < V; s += (long long)nblk * kThreads) {
+            // (re, im) of <x, y> over the site, added to a
+            const auto dot = [](const Spinor<R>& x, const Spinor<R>& y, double* a) {
+                R re = 0, im = 0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                uu += uv[k] * uv[k];
-                ww += wv[k] * wv[k];
+                for (int k = 0; k < 12; ++k) {
+                    re += x.v[k].re * y.v[k].re + x.v[k].im * y.v[k].im;
+                    im += x.v[k].re * y.v[k].im - x.v[k].im * y.v[k].re;
+                }
+                a[0] += (double)re;
+                a[1] += (double)im;
+            };
+            Spinor<R> uv, wv;
+            load_spinor<R, P>(u0, nullptr, V, s, uv);
+            load_spinor<R, P>(w0, nullptr, V, s, wv);
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+                if (i < n) {
+                    Spinor<R> v;
+                    load_spinor<R, P>(b0 + i * vec_stride, nullptr, V, s, v);
+                    dot(v, uv, acc + 4 * i);
+                    dot(v, wv, acc + 4 * i + 2);
+                }
+            if (head) {
+                R uu = 0, ww = 0;
+#pragma unroll
+                for (int k = 0; k < 12; ++k) {
+                    uu += uv.v[k].re * uv.v[k].re + uv.v[k].im * uv.v[k].im;
+                    ww += wv.v[k].re * wv.v[k].re + wv.v[k].im * wv.v[k].im;
+                }
+                acc[4 * NV] += (double)uu;
+                dot(uv, wv, acc + 4 * NV + 1);
+                acc[4 * NV + 3] += (double)ww;
             }
-            acc[4 * NV] += (double)uu;
-            dot(uv, wv, acc + 4 * NV + 1);
-            acc[4 * NV + 3] += (double)ww;
         }
     }
     // the head values follow the n dot pairs
@@ -480,25 +519,32 @@ hipError_t blas_dgs_dots(Prec p, const VecRef& basis, size_t vec_stride, int nb,
                         double* partials, double* out, int nsys, long long V, hipStream_t st) {
     if (nb < 0 || nb > kMaxVec - 1 || (p != P_F64 && p != P_F32)) return hipErrorInvalidValue;
     const int nblk = blas_blocks(V);
-    constexpr int chunk = 11;  // 4 chunk + 4 values per sweep
-    static_assert(4 * chunk + 4 <= 2 * kMaxVec, "reduction scratch");
+    // FP32 sites from here on: by V alone, so that a system's sums do not depend on how many there are.  Sites against
+    // units: 48^3x96, 12 systems, 13 steps 124 against 132 ms; 32^3x64, 9 steps, 12 systems 33.1 against 33.8, one
+    // system 3.16 against 3.03; 24^3x48, 12 systems 21.2 against 21.5; 16^3x32, 3 systems 1.63 against 1.51.
+    constexpr long long kSiteDots = 1 << 19;
+    constexpr int units = 11, sites = 8;  // vectors, 4 values each and 4 more, per sweep
+    static_assert(4 * units + 4 <= 2 * kMaxVec, "reduction scratch");
+    const bool by_site = p == P_F32 && V >= kSiteDots;
+    const int chunk = by_site ? sites : units;
     const int ds = 4 * nb + 4;
     dim3 grid(nblk, nsys);
     for (int i0 = 0;; i0 += chunk) {
         const int n = nb - i0 < chunk ? nb - i0 : chunk;
         const int head = i0 + n == nb;
-#define TM_DOTS_LAUNCH(T)                                                                                              \
-    if (n <= 4)                                                                                                        \
-        hipLaunchKernelGGL((k_dgs_dots<T, 4>), grid, dim3(kThreads), 0, st, basis, vec_stride, i0, n, u, w, head,       \
-                           partials, V);                                                                               \
-    else                                                                                                               \
-        hipLaunchKernelGGL((k_dgs_dots<T, chunk>), grid, dim3(kThreads), 0, st, basis, vec_stride, i0, n, u, w, head,   \
-                           partials, V)
-        if (p == P_F32) {
-            TM_DOTS_LAUNCH(float);
-        } else {
-            TM_DOTS_LAUNCH(double);
-        }
+#define TM_DOTS_LAUNCH(T, NV, UNIT)                                                                                    \
+    hipLaunchKernelGGL((k_dgs_dots<T, NV, UNIT>), grid, dim3(kThreads), 0, st, basis, vec_stride, i0, n, u, w, head,    \
+                       partials, V)
+        if (by_site)
+            TM_DOTS_LAUNCH(float, sites, false);
+        else if (p == P_F32 && n <= 4)
+            TM_DOTS_LAUNCH(float, 4, true);
+        else if (p == P_F32)
+            TM_DOTS_LAUNCH(float, units, true);
+        else if (n <= 4)
+            TM_DOTS_LAUNCH(double, 4, true);
+        else
+            TM_DOTS_LAUNCH(double, units, true);
 #undef TM_DOTS_LAUNCH
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -14,7 +14,7 @@ import oracle
 import paper_1610_02370_amd as tm
 from paper_1610_02370_amd import synth
 
-from gpu_util import announce, dev, host, log_solve
+from gpu_util import announce, dev, host, log_solve, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -299,3 +299,19 @@ def test_defect_correction_tolerance_per_system(cfg_8888):
     assert rep["iters"] == rep_alone["iters"] and rep["outer"] == rep_alone["outer"], (rep, rep_alone)
     assert np.abs(got[1] - host(alone)[0]).max() <= 1e-12 * np.abs(got[1]).max()
     check_solutions(op, dims, b, got, mus, TOL)
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 16, 16), (32, 32, 32, 16)])
+def test_fp32_arnoldi_steps_follow_the_fp64_ones(dims):
+    # ten steps without a restart in FP32 and in FP64 vectors, the same smoother: the Gram-Schmidt dots of FP32 vectors
+    # by units and, from 524288 sites on, by sites with 8 vectors per sweep (a full sweep and a remainder).  FP32
+    # rounding (6e-8) of ten vectors, times at most 100 for the projected matrix' condition.
+    U, b = dev(synth.gauge_field(dims, 0.5, seed=97)), dev(synth.gaussian_spinor(dims, 1, seed=197))
+    announce(f"FP32 Arnoldi steps {dims}")
+    x = {}
+    for form in ("flexible", "defect_correction"):
+        x[form] = dev(np.zeros((1, U.numel() // 36, 4, 3)))
+        _, rep = tm.tm_fgmres_solve(dims, U, b, x[form], 0.1373, [0.01], 1.5, 1e-13, storage="f32", form=form, restart=12,
+                                    n_cycles=1, mr_iters=2, block_dims=(4, 4, 4, 4), x_in=False, max_iters=10, gauge_tag=1)
+        assert rep["iters"] == 10
+    assert rel_err(host(x["defect_correction"]), host(x["flexible"])) < 1e-4
