@@ -15,10 +15,12 @@ namespace tmsap {
 namespace {
 
 constexpr int kThreads = 256;
-// Coarse operator: up to this many <4, 1024> workgroups (4 per CU) that form runs.  20 test vectors, 3 / 8 / 16
-// systems, <4, 1024> against <16, 256>: 256 sites 13 / 19 / 33 us against 23 / 35 / 56, 512 sites 19 / 35 / 64
-// against 28 / 42 / 60, 1024 sites 34 / 63 / 119 against 34 / 48 / 115.
-constexpr int kCoarseFill = 1024;
+// Coarse operator on up to this many sites (the lattice's, or one parity's): <4, 1024>, on more <16, 256>.  By the
+// sites and the handle's vectors alone: the forms sum the columns in different groups, and a system's result must not
+// depend on how many there are.  20 test vectors, 3 / 8 / 16 systems, <4, 1024> against <16, 256>: 256 sites 13 / 19 /
+// 33 us against 23 / 35 / 56, 512 sites 19 / 35 / 64 against 28 / 42 / 60, 1024 sites 34 / 63 / 119 against 34 / 48 / 115.
+// 8 test vectors, 512 sites, whole calls: 34 / 43 / 60 against 37 / 44 / 57.
+constexpr long long coarse_fill(int nv) { return nv >= 16 ? 512 : 384; }
 constexpr int kDots = 16;       // basis vectors per dot / axpy pass
 
 __device__ inline float wave_sum(float v) {
@@ -1028,7 +1030,7 @@ hipError_t launch_mg_coarse_part(const Geo& g, int nv, const float2* Dc, const d
     if (nv < 1 || nv > kMgMaxVec || nsys < 1 || nsys > kMaxSys) return hipErrorInvalidValue;
     if (parity >= 0 && g.nb[3] % 2 != 0) return hipErrorInvalidValue;
     const long long sites = parity >= 0 ? g.V / g.Vb / 2 : g.V / g.Vb;
-    if (sites * ((nsys + 3) / 4) <= kCoarseFill)
+    if (sites <= coarse_fill(nv))
         return coarse_part<4, 1024>(g, nv, Dc, mu_c, x_self, x_hop, hop_sign, add, parity, zero_other, y, nsys, st);
     return coarse_part<16, 256>(g, nv, Dc, mu_c, x_self, x_hop, hop_sign, add, parity, zero_other, y, nsys, st);
 }

@@ -295,3 +295,33 @@ def test_coarse_operator_by_systems(dims, nsys):
     ref += 1j * np.array(mus)[:, None, None] * np.where(np.arange(n2) < nv, 1, -1) * x
     for k in range(nsys):
         assert rel_err(y[k], ref[k]) < 1e-5
+
+
+# Up to 512 sites one form of the coarse operator, above the other, whatever the number of systems.
+@pytest.mark.parametrize("dims,coarse_eo", [((16, 16, 16, 16), 0), ((32, 16, 16, 16), 0), ((32, 32, 16, 16), 1)])
+def test_coarse_operator_of_a_batch_is_bit_identical_to_single_ones(dims, coarse_eo):
+    import torch
+
+    U = dev(synth.gauge_field(dims, 0.6, seed=10))
+    nv, mus = 17, [0.001 * (k - 8) for k in range(18)]
+    announce(f"coarse operator, batch and single, dims={dims}")
+    g = tm.MG(dims, U, KAPPA, 0.01, CSW, dev(synth.gaussian_spinor(dims, nv, seed=110)), n_vec=nv, setup_iters=0,
+              coarse_eo=coarse_eo)
+    x = torch.randn((len(mus), U.numel() // (36 * 256), 2 * nv), dtype=torch.complex128, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(50))
+    y = g.coarse_apply(x, mus)
+    for k in (0, 4, 5, 17):
+        assert torch.equal(g.coarse_apply(x[k:k + 1].contiguous(), mus[k:k + 1]), y[k:k + 1])
+
+
+def test_preconditioner_of_a_batch_is_bit_identical_to_single_ones():
+    import torch
+
+    dims, mus = (16, 16, 16, 16), [0.001 * (k - 9) for k in range(20)]
+    U = dev(synth.gauge_field(dims, 0.6, seed=10))
+    announce("two-level preconditioner, batch and single")
+    g = tm.MG(dims, U, KAPPA, 0.01, CSW, dev(synth.gaussian_spinor(dims, 6, seed=111)), n_vec=6, setup_iters=1)
+    r = dev(synth.gaussian_spinor(dims, len(mus), seed=112))
+    z = g.precond(r, mus)
+    for k in (0, 7, 19):
+        assert torch.equal(g.precond(r[k:k + 1].contiguous(), mus[k:k + 1]), z[k:k + 1])
