@@ -31,13 +31,22 @@ __device__ inline int site_parity_tiled(const Geo& g, unsigned s) {
     return sum & 1;
 }
 
+// A chunk's sum from its parts, pairwise.
+template <int PARTS>
+__device__ inline double sum_parts(const double* v) {
+    return PARTS == 4 ? (v[0] + v[1]) + (v[2] + v[3]) : (PARTS == 2 ? v[0] + v[1] : v[0]);
+}
+
 // out_p = (D_pp^-1)? [ hop_sign * H in_hop + D_pp in_diag + add_sign * in_add ], H = -1/2 sum of hops
 // between the parities, D_pp = (m+4) + clover + i mu Gamma5 on parity p; the Gamma5 flags multiply
 // the hop input, the diagonal input and the output.  With `partials`, also ||out||^2 per workgroup and
-// system at partials[sys * gridDim.x + blockIdx.x].
+// system.
 //
-// Two lanes per site (tm_pair.h), 32 sites of one system per wavefront, the four wavefronts of a workgroup on
-// `sys_tile` (1, 2 or 4) systems of the same sites.  Bound by the links and the site matrices: on 16^3x32,
+// Two lanes per site (tm_pair.h), a run of 32 sites of one system per wavefront, the four wavefronts of a workgroup
+// on `sys_tile` (1, 2 or 4) systems of the same sites.  Four runs make a chunk, whose sites stay together
+// whatever the tile: a workgroup of tile 1 takes the four runs of chunks b, b + blocks, ..., one of tile 2 or 4 its
+// part of them, two runs or one.  A system's sums therefore are the same bits in any number of systems: over a
+// wavefront's runs first, then pairwise over the four wavefronts, in LDS or (sum_partials) from the parts.  Bound by the links and the site matrices: on 16^3x32,
 // 126 MB (diagonal) to 150 MB (site inverse) per launch in 31-32 us, 4.0-4.8 TB/s, where a copy reaches 4.7;
 // one lane per site kept that half lattice at one wavefront per SIMD and took 36 us.
 template <int MU, bool G5HOP>
@@ -80,7 +89,7 @@ __device__ inline void parity_dir(const ParityArgs& a, const FieldOf<double>& in
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <bool HOP, bool DIAG, bool INV, bool G5HOP>
+template <bool HOP, bool DIAG, bool INV, bool G5HOP, int TILE>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) k_parity_op(ParityArgs a) {
     __shared__ double nrm[4];
     const Geo& g = a.g;
@@ -88,10 +97,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 1;
     const bool lower = c != 0;
     const double sg = lower ? 1.0 : -1.0;
-    const int groups = 4 / a.sys_tile, sys = blockIdx.y * a.sys_tile + w / groups;
+    constexpr int runs = 4 / TILE;  // of a chunk, per system
+    const int sys = blockIdx.y * TILE + w / runs;
+    // block and part; a chunk's parts on one XCD (blocks is a multiple of 8)
+    const int blocks = gridDim.x / TILE, row = blockIdx.x / 8u;
+    const int part = row % TILE, first = blockIdx.x % 8u + 8 * (row / TILE);
     double n2 = 0;
-    for (int vb = blockIdx.x; vb < a.chunks && sys < a.nsys; vb += gridDim.x) {
-        const long long at = (xcd_swizzle(vb, a.chunks) * groups + w % groups) * 32 + (lane >> 1);
+    for (int vb = first; vb < a.chunks && sys < a.nsys; vb += blocks) {
+        const long long at = (xcd_swizzle(vb, a.chunks) * 4 + part * runs + w % runs) * 32 + (lane >> 1);
         const bool on = at < half;
         const long long h = on ? at : 0;
         unsigned s = 2u * (unsigned)h;
@@ -172,11 +185,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
         if (lane == 0) nrm[w] = n2;
         __syncthreads();
         const int k = threadIdx.x;
-        if (k < a.sys_tile && (int)blockIdx.y * a.sys_tile + k < a.nsys) {
-            double t = 0;
-            for (int i = 0; i < groups; ++i) t += nrm[k * groups + i];
-            a.partials[(size_t)(blockIdx.y * a.sys_tile + k) * gridDim.x + blockIdx.x] = t;
-        }
+        if (k < TILE && (int)blockIdx.y * TILE + k < a.nsys)
+            a.partials[((size_t)(blockIdx.y * TILE + k) * blocks + first) * TILE + part] = sum_parts<runs>(nrm + k * runs);
     }
 }
 
@@ -235,10 +245,11 @@ __global__ void __launch_bounds__(kThreads) k_axpby(const double* __restrict__ x
         ys[i] = fa * xs[i] + fb * ys[i];
 }
 
-// Sum of n partials, in the same order in every workgroup that forms it.
+// Sum of n partials of PARTS parts each, in the same order in every workgroup that forms it.
+template <int PARTS>
 __device__ inline double sum_partials(const double* p, int n, double* lds) {
     double t = 0;
-    for (int i = threadIdx.x; i < n; i += kThreads) t += p[i];
+    for (int i = threadIdx.x; i < n; i += kThreads) t += sum_parts<PARTS>(p + (size_t)PARTS * i);
     t = wave_sum(t);
     __syncthreads();  // earlier reads of lds
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = t;
@@ -254,10 +265,11 @@ __device__ inline double sum_partials(const double* p, int n, double* lds) {
 //   first:  alpha = gamma / <q,q>;  r -= alpha q, partials of <r,r>
 //   second: beta = <s,s> / gamma;  x += alpha p;  p = s + beta p;  gamma' = <s,s>;  frozen' once
 //           ||r|| <= limit;  <r,r> to rr
+template <int PARTS>
 __global__ void __launch_bounds__(kThreads) k_cg_first(CgStep a) {
     __shared__ double lds[4];
     const int sys = blockIdx.y;
-    const double qq = sum_partials(a.qq + (size_t)sys * a.n_qq, a.n_qq, lds);
+    const double qq = sum_partials<PARTS>(a.qq + (size_t)sys * a.n_op * PARTS, a.n_op, lds);
     const double al = (a.frozen[sys] != 0 || !(qq > 0)) ? 0.0 : a.gamma[sys] / qq;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.alpha[sys] = al;
     const double2* q = reinterpret_cast<const double2*>(a.q + (size_t)sys * a.n);
@@ -279,14 +291,15 @@ __global__ void __launch_bounds__(kThreads) k_cg_first(CgStep a) {
     if (threadIdx.x == 0) a.rr_part[(size_t)sys * gridDim.x + blockIdx.x] = (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
+template <int PARTS>
 __global__ void __launch_bounds__(kThreads) k_cg_second(CgStep a) {
     __shared__ double lds[4];
     const int sys = blockIdx.y;
-    const double ss = sum_partials(a.ss + (size_t)sys * a.n_ss, a.n_ss, lds);
+    const double ss = sum_partials<PARTS>(a.ss + (size_t)sys * a.n_op * PARTS, a.n_op, lds);
     const bool off = a.frozen[sys] != 0;
     const double gam = a.gamma[sys], al = a.alpha[sys], be = (off || !(gam > 0)) ? 0.0 : ss / gam;
     if (blockIdx.x == 0) {
-        const double rr = sum_partials(a.rr_part + (size_t)sys * a.n_rr, a.n_rr, lds);
+        const double rr = sum_partials<1>(a.rr_part + (size_t)sys * a.n_rr, a.n_rr, lds);
         if (threadIdx.x == 0) {
             a.gamma_next[sys] = off ? gam : ss;
             a.frozen_next[sys] = (off || sqrt(fmax(0.0, rr)) <= a.limit[sys]) ? 1.0 : 0.0;
@@ -311,39 +324,53 @@ __global__ void __launch_bounds__(kThreads) k_cg_second(CgStep a) {
 
 }  // namespace
 
-static int parity_sys_tile(int nsys) { return nsys > 2 ? 4 : nsys; }
+int parity_parts(int nsys) { return nsys > 2 ? 4 : nsys; }
 
-static int parity_chunks(const Geo& g, int nsys) {
-    const long long per = 128 / parity_sys_tile(nsys);  // sites of a workgroup
-    return (int)((g.V / 2 + per - 1) / per);
-}
+// One statement for PARTS = 1, 2 or 4 (parity_parts).
+#define TM_PARTS_DISPATCH(n, ...)           \
+    do {                                    \
+        if ((n) == 1) {                     \
+            constexpr int PARTS = 1;        \
+            __VA_ARGS__;                    \
+        } else if ((n) == 2) {              \
+            constexpr int PARTS = 2;        \
+            __VA_ARGS__;                    \
+        } else {                            \
+            constexpr int PARTS = 4;        \
+            __VA_ARGS__;                    \
+        }                                   \
+    } while (0)
 
-// At most 2048 workgroups (a multiple of the 8 XCDs, so that a workgroup stays with its XCD's sites): every
-// workgroup of the update kernels adds up their partial sums.
-int parity_blocks(const Geo& g, int nsys) {
-    const int n = parity_chunks(g, nsys);
+static int parity_chunks(const Geo& g) { return (int)((g.V / 2 + 127) / 128); }
+
+// At most 2048 (every workgroup of the update kernels adds up the partial sums, up to four per block), a multiple of
+// the 8 XCDs, so that a workgroup stays with its XCD's sites; by V alone.
+int parity_blocks(const Geo& g) {
+    const int n = (parity_chunks(g) + 7) / 8 * 8;
     return n < 2048 ? n : 2048;
 }
 
 hipError_t launch_parity_op(const ParityArgs& args, hipStream_t st) {
     ParityArgs a = args;
-    a.sys_tile = parity_sys_tile(a.nsys);
-    a.chunks = parity_chunks(a.g, a.nsys);
-    const dim3 grid((unsigned)parity_blocks(a.g, a.nsys), (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile)),
+    a.sys_tile = parity_parts(a.nsys);
+    a.chunks = parity_chunks(a.g);
+    const dim3 grid((unsigned)(parity_blocks(a.g) * a.sys_tile), (unsigned)((a.nsys + a.sys_tile - 1) / a.sys_tile)),
         blk(kThreads);
     const bool hop = a.in_hop != nullptr, diag = a.in_diag != nullptr, inv = a.do_inv != 0;
+#define TM_PARITY_LAUNCH(...) TM_PARTS_DISPATCH(a.sys_tile, hipLaunchKernelGGL((k_parity_op<__VA_ARGS__, PARTS>), grid, blk, 0, st, a))
     if (hop && !diag && inv && a.g5_hop)
-        hipLaunchKernelGGL((k_parity_op<true, false, true, true>), grid, blk, 0, st, a);
+        TM_PARITY_LAUNCH(true, false, true, true);
     else if (hop && !diag && inv)
-        hipLaunchKernelGGL((k_parity_op<true, false, true, false>), grid, blk, 0, st, a);
+        TM_PARITY_LAUNCH(true, false, true, false);
     else if (hop && diag && !inv && !a.g5_hop)
-        hipLaunchKernelGGL((k_parity_op<true, true, false, false>), grid, blk, 0, st, a);
+        TM_PARITY_LAUNCH(true, true, false, false);
     else if (hop && !diag && !inv && !a.g5_hop)
-        hipLaunchKernelGGL((k_parity_op<true, false, false, false>), grid, blk, 0, st, a);
+        TM_PARITY_LAUNCH(true, false, false, false);
     else if (!hop && !diag && inv)
-        hipLaunchKernelGGL((k_parity_op<false, false, true, false>), grid, blk, 0, st, a);
+        TM_PARITY_LAUNCH(false, false, true, false);
     else
         return hipErrorInvalidValue;
+#undef TM_PARITY_LAUNCH
     return hipGetLastError();
 }
 
@@ -377,12 +404,12 @@ int cg_blocks(long long n) {
 }
 
 hipError_t launch_cg_first(const CgStep& a, int nsys, hipStream_t st) {
-    hipLaunchKernelGGL(k_cg_first, dim3((unsigned)cg_blocks(a.n), nsys), dim3(kThreads), 0, st, a);
+    TM_PARTS_DISPATCH(a.parts, hipLaunchKernelGGL(k_cg_first<PARTS>, dim3((unsigned)cg_blocks(a.n), nsys), dim3(kThreads), 0, st, a));
     return hipGetLastError();
 }
 
 hipError_t launch_cg_second(const CgStep& a, int nsys, hipStream_t st) {
-    hipLaunchKernelGGL(k_cg_second, dim3((unsigned)cg_blocks(a.n), nsys), dim3(kThreads), 0, st, a);
+    TM_PARTS_DISPATCH(a.parts, hipLaunchKernelGGL(k_cg_second<PARTS>, dim3((unsigned)cg_blocks(a.n), nsys), dim3(kThreads), 0, st, a));
     return hipGetLastError();
 }
 

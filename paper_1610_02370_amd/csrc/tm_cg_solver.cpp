@@ -189,7 +189,7 @@ int tm_cg_solve(const tm_geom* geom, const void* U, const void* b, void* x, doub
         // ||r||, constants, b-norms; then the partial sums
         const int nblk = blas_blocks(half);
         const int nblk_full = blas_blocks(g.V);
-        const int nop = parity_blocks(g, ns), nup = cg_blocks((long long)fd / ns);
+        const int nop = parity_blocks(g) * parity_parts(ns), nup = cg_blocks((long long)fd / ns);
         const size_t nred = 2 * (size_t)kMaxSys * std::max(nblk, nblk_full) + 64;
         if ((h = ds->red.ensure((16 * kMaxSys + nred + (size_t)ns * (2 * nop + nup)) * sizeof(double))) != hipSuccess)
             return hip_fail(h, "CG scalars");
@@ -280,7 +280,8 @@ int tm_cg_solve(const tm_geom* geom, const void* U, const void* b, void* x, doub
             u.qq = pqq;
             u.ss = pss;
             u.rr_part = prr;
-            u.n_qq = u.n_ss = nop;
+            u.n_op = parity_blocks(g);
+            u.parts = parity_parts(ns);
             u.n_rr = nup;
             u.limit = limit;
             u.alpha = alpha;

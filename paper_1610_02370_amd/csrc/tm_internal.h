@@ -157,8 +157,8 @@ struct ParityArgs {
     double mu_sign;
     double* out;
     int nsys;
-    int sys_tile, chunks;  // systems per workgroup and runs of sites per system, set by the launcher
-    double* partials;    // ||out||^2 per system and workgroup ([nsys][parity_blocks]), or null
+    int sys_tile, chunks;  // systems per workgroup and chunks of 128 sites, set by the launcher
+    double* partials;    // parts of ||out||^2 ([nsys][parity_blocks][parity_parts]), or null
     double mu[kMaxSys];
 };
 
@@ -169,7 +169,7 @@ struct CgStep {
     const double *q, *s;
     double *r, *p, *x;
     const double *qq, *ss;
-    int n_qq, n_ss, n_rr;
+    int n_op, parts, n_rr;  // parity_blocks and parity_parts (qq, ss), cg_blocks (rr_part)
     double* rr_part;
     const double *gamma, *frozen, *limit;
     double *alpha, *gamma_next, *frozen_next, *rr;
@@ -184,7 +184,8 @@ hipError_t launch_parity_export(const Geo& g, int nsys, const double* even, cons
 // y = a[sys] x + b[sys] y over n_per_sys doubles per system
 hipError_t launch_axpby(const double* x, const double* a, double* y, const double* b, int nsys, long long n_per_sys,
                         hipStream_t st);
-int parity_blocks(const Geo& g, int nsys);  // workgroups (partial sums per system) of launch_parity_op
+int parity_blocks(const Geo& g);            // partial sums per system of launch_parity_op ...
+int parity_parts(int nsys);                 // ... and their parts
 int cg_blocks(long long n);                 // the same of launch_cg_first
 hipError_t launch_cg_first(const CgStep& a, int nsys, hipStream_t st);
 hipError_t launch_cg_second(const CgStep& a, int nsys, hipStream_t st);

@@ -90,3 +90,23 @@ def test_cg_steps_of_joint_systems_match_single_ones(dims, mus):
         tm.tm_cg_solve(dims, U, dev(b[k:k + 1]), y, kappa, [m], csw, 1e-13, max_iters=5)
         y = host(y)[0]
         assert np.linalg.norm(x[k] - y) <= 1e-12 * np.linalg.norm(y)
+
+
+# The sums of a system go over the same sites in the same order with one, two or more systems: partly filled runs and
+# chunks, one round of chunks, and several (half lattice above 1024 x 128 sites).
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 2, 10, 4), (8, 16, 16, 16), (20, 24, 24, 24)])
+def test_cg_steps_of_joint_systems_are_bit_identical_to_single_ones(dims):
+    mus = [0.01, -0.02, 0.03, 0.02, 0.01]
+    U, b = dev(synth.gauge_field(dims, 0.4, seed=4)), dev(synth.gaussian_spinor(dims, len(mus), seed=6))
+    announce(f"cg steps, joint and single, {dims}")
+
+    def solve(k0, k1):
+        x = dev(np.zeros((k1 - k0,) + tuple(b.shape[1:])))
+        tm.tm_cg_solve(dims, U, b[k0:k1].contiguous(), x, 0.13, mus[k0:k1], 1.2, 1e-13, max_iters=5, gauge_tag=1)
+        return host(x)
+
+    single = [solve(k, k + 1)[0] for k in range(len(mus))]
+    for k0, k1 in ((0, 2), (0, 3), (0, 5)):
+        joint = solve(k0, k1)
+        for k in range(k0, k1):
+            assert np.array_equal(joint[k - k0], single[k])
