@@ -63,6 +63,15 @@ void drop_gauge(DeviceState* ds, const GaugeDev* G);
 // SAP tuning cache: the stored (block shape, systems per workgroup) for this
 // problem, if any; returns false when nothing is stored.
 bool tune_lookup(const tm_geom* geom, int storage, int n_cycles, int mr_iters, int eo, int block[4], int* sys_tile);
+// Systems per workgroup that the tuner times for the best shape, from all in one workgroup to a sixth.
+inline std::vector<int> tune_tiles(int nsys) {
+    std::vector<int> tiles;
+    for (int split : {1, 2, 3, 4, 6}) {
+        const int tile = (nsys + split - 1) / split;
+        if (tiles.empty() || tile < tiles.back()) tiles.push_back(tile);
+    }
+    return tiles;
+}
 SpinorBuf wrap_internal(void* base, const Geo& g, int nsys, Prec p);
 size_t internal_bytes(const Geo& g, int nsys, Prec p);
 void fill_mu(const tm_geom* geom, double* mu);

@@ -215,7 +215,8 @@ int tm_autotune_sap(const tm_geom* geom, const void* U, double kappa, double c_s
     if (!ds) return rc;
     hipStream_t st = (hipStream_t)opts->stream;
 
-    // stage 1: block shape with the launch's own choice of systems per workgroup; stage 2: other splits for that shape
+    // stage 1: block shape with the launch's own choice of systems per workgroup; stage 2: explicit ones for that
+    // shape, unsplit included
     double best = 0;
     int bb[4] = {0, 0, 0, 0}, btile = 0;
     for (auto& c : cand) {
@@ -228,11 +229,7 @@ int tm_autotune_sap(const tm_geom* geom, const void* U, double kappa, double c_s
         }
     }
     if (bb[0] == 0) return fail(TM_ERR_BLOCKS, "no candidate block shape could be launched");
-    std::vector<int> tried{geom->nsys};
-    for (int split : {2, 3, 4, 6}) {
-        const int tile = (geom->nsys + split - 1) / split;
-        if (std::find(tried.begin(), tried.end(), tile) != tried.end()) continue;
-        tried.push_back(tile);
+    for (int tile : tune_tiles(geom->nsys)) {
         Timing t = time_config(ds, geom, U, kappa, c_sw, n_cycles, mr_iters, sp, eo, opts->gauge_tag, st, bb, tile);
         if (t.rc) return t.rc;
         if (t.seconds < best) {

@@ -2,6 +2,7 @@
 // measured.  Built for the host only and run on the CPU by tests/test_launch_rules.py; prints "ALL OK".
 #include <cstdio>
 
+#include "../paper_1610_02370_amd/csrc/tm_api_internal.h"
 #include "../paper_1610_02370_amd/csrc/tm_internal.h"
 
 using namespace tmsap;
@@ -32,6 +33,14 @@ int main() {
                     const int tile = sap_sys_tile(blocks, nsys, nt, k & 1, k & 2);
                     if (tile < 1 || tile > nsys) expect("tile in 1..nsys", tile, nsys);
                 }
+    // the tuner times all systems in one workgroup too, whatever the launch would choose, and no tile twice
+    for (int nsys = 1; nsys <= kMaxSys; ++nsys) {
+        const std::vector<int> tiles = tune_tiles(nsys);
+        expect("first tile", tiles.front(), nsys);
+        for (size_t k = 1; k < tiles.size(); ++k)
+            if (tiles[k] >= tiles[k - 1] || tiles[k] < 1) expect("tiles fall", tiles[k], tiles[k - 1] - 1);
+    }
+    expect("tiles of 12 systems", (int)tune_tiles(12).size(), 5);
     if (failures) return 1;
     std::printf("ALL OK\n");
     return 0;
