@@ -155,8 +155,10 @@ def _stream_handle(stream):
         return stream.cuda_stream
     import torch
 
-    # the handle alone: building a Stream object around it takes 3 us of a small call
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the handle alone: building a Stream object around it takes 3 us of a small call; torch keeps the function
+    # that gives it to itself, so a version without it goes through the object
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw is not None else torch.cuda.current_stream().cuda_stream
 
 
 _INT4, _DOUBLE4, _DOUBLE2 = ctypes.c_int * 4, ctypes.c_double * 4, ctypes.c_double * 2

@@ -162,3 +162,18 @@ def test_binding_checks_buffer_sizes_before_any_library_call():
     with pytest.raises(ValueError, match="live on the GPU"):
         tm.tm_spinor_import(dims, psi, torch.zeros(need, dtype=torch.uint8), storage="f16",
                             layout_block=(2, 2, 2, 2), stream=False)
+
+
+def test_stream_handle_without_torchs_own_function(monkeypatch):
+    # the handle of the current stream where torch does not offer the short way to it, and of a given or no stream
+    import types
+
+    import torch
+
+    stream = types.SimpleNamespace(cuda_stream=4242)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: stream)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert tm._stream_handle(None) == 4242
+    assert tm._stream_handle(types.SimpleNamespace(cuda_stream=7)) == 7
+    assert tm._stream_handle(False) is None
+    assert tm.make_opts("f32", stream=None).stream == 4242
