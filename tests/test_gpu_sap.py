@@ -141,3 +141,47 @@ def test_sap_without_mr_steps_leaves_x(prec):
     bound = 1e-6 if prec == "f32" else 1e-3
     for i in range(len(mus)):
         assert rel_err(outs[0][i], x0[i]) < bound, i
+
+
+# Squares below the smallest normal number in the FP64 and the even-odd kernels, on 4^4 blocks (two lanes per site) and
+# others: 1e-160 squared for FP64, 1e-21 for FP32 (1e-40: fields that are FP32 subnormals themselves).
+@pytest.mark.parametrize("prec,eo,bd,tiny", [("f64", False, (4, 4, 4, 4), 1e-160), ("f64", True, (4, 4, 4, 4), 1e-160),
+                                             ("f32", True, (4, 4, 4, 4), 1e-21), ("f32", True, (4, 4, 4, 4), 1e-40),
+                                             ("bf16", True, (4, 4, 4, 4), 1e-21), ("f64", False, (4, 4, 4, 2), 1e-160),
+                                             ("f64", False, (4, 4, 4, 8), 1e-160), ("f64", True, (2, 2, 2, 2), 1e-160),
+                                             ("f32", True, (4, 4, 4, 8), 1e-21)])
+def test_sap_kernels_with_vanishing_residual(prec, eo, bd, tiny):
+    dims, kappa, mu, csw = (8, 8, 8, 16), 0.1373, 0.0009, 1.5
+    U = synth.gauge_field(dims, 0.6, seed=22)
+    b = tiny * synth.gaussian_spinor(dims, 1, seed=122)
+    b[0, 0, 0, 0] = 1.0
+    announce(f"sap vanishing residual prec={prec} eo={eo} block={bd} tiny={tiny}")
+    x = dev(np.zeros_like(b))
+    tm.tm_sap_smooth(dims, dev(U), dev(b), x, kappa, [mu], csw, bd, 2, 4, storage=prec, eo=eo)
+    got = host(x)[0]
+    assert np.isfinite(got).all()
+    ref = oracle.Operator(dims, U, oracle.kappa_to_m(kappa), mu, csw).sap(b[0], bd, 2, 4, eo=eo).reshape(-1, 4, 3)
+    check_close(got, ref, "sap", prec, f"vanishing residual eo {eo} block {bd} tiny {tiny}")
+
+
+# All systems of a call in one workgroup, with no MR step or a few between one system's residual and the next one's:
+# each kernel's own system loop, against one system per call.
+@pytest.mark.parametrize("mr", [0, 3])
+@pytest.mark.parametrize("bd", [(2, 2, 2, 2), (4, 4, 4, 2), (4, 4, 4, 4), (4, 4, 4, 8)])
+@pytest.mark.parametrize("prec,eo", [("f64", False), ("f32", False), ("bf16", False), ("f64", True), ("f32", True)])
+def test_systems_in_one_workgroup_match_single_calls(prec, eo, bd, mr):
+    dims, mus = (8, 8, 8, 16), [0.003, -0.003, 0.02, -0.02]
+    U, b = dev(synth.gauge_field(dims, 0.5, seed=42)), synth.gaussian_spinor(dims, len(mus), seed=142)
+    announce(f"systems in one workgroup prec={prec} eo={eo} block={bd} mr={mr}")
+
+    def smooth(k0, k1):
+        x = dev(0.1 * b[k0:k1])
+        tm.tm_sap_smooth(dims, U, dev(b[k0:k1]), x, 0.1373, mus[k0:k1], 1.5, bd, 2, mr, storage=prec, eo=eo,
+                         sys_tile=k1 - k0, gauge_tag=3)
+        return host(x)
+
+    together = smooth(0, len(mus))
+    for k in range(len(mus)):
+        assert np.array_equal(together[k], smooth(k, k + 1)[0]), k
+    if mr == 0 and not eo:  # no correction: x as stored
+        assert rel_err(together, 0.1 * b) < {"f64": 1e-15, "f32": 1e-7, "bf16": 4e-3}[prec]
