@@ -279,7 +279,7 @@ def test_system_of_a_batch_is_bit_identical_to_it_alone(dims):
         assert torch.equal(internal(p, [m]), batch[k:k + 1])
 
 
-@pytest.mark.parametrize("storage", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16", "bf16"])
 def test_flexible_steps_of_a_batch_are_bit_identical_to_single_ones(storage):
     # the FP64 operator on vectors of the smoother's precision, split over wavefronts for one system and not for two
     import torch
@@ -332,3 +332,21 @@ def test_defect_correction_steps_of_a_batch_are_bit_identical_to_single_ones():
     batch = solve(0, len(mus))
     for k in range(len(mus)):
         assert torch.equal(solve(k, k + 1), batch[k:k + 1])
+
+
+# Many systems on few tiles: several stay in each workgroup of the generic kernel (15 workgroups, 40 systems) and of the
+# one for 4^4 tiles (32 tiles, 64 systems), whose loops over systems then run more than once.
+@pytest.mark.parametrize("prec", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("dims,nsys", [((6, 10, 7, 9), 40), ((8, 8, 8, 16), 64)])
+def test_system_loop_of_the_application(dims, nsys, prec):
+    mus = [0.002 * (k - 20) for k in range(nsys)]
+    U, psi = synth.gauge_field(dims, 0.5, seed=98), synth.gaussian_spinor(dims, nsys, seed=198)
+    announce(f"application of {nsys} systems dims={dims} prec={prec}")
+    Ud = dev(U)
+    got = host(tm.tm_dirac_apply(dims, Ud, dev(psi), 0.15, mus, 1.2, storage=prec, gauge_tag=17))
+    op = oracle.Operator(dims, U, oracle.kappa_to_m(0.15), 0.0, 1.2)
+    for k in (0, 1, 2, 3, nsys // 2, nsys - 2, nsys - 1):
+        one = tm.tm_dirac_apply(dims, Ud, dev(psi[k:k + 1]), 0.15, [mus[k]], 1.2, storage=prec, gauge_tag=17)
+        assert np.array_equal(got[k], host(one)[0]), k
+    for k in (2, nsys - 1):
+        check_close(got[k], op.with_mu(mus[k]).apply(psi[k]).reshape(-1, 4, 3), "dirac", prec, f"{nsys} systems {dims} {k}")
