@@ -315,3 +315,18 @@ def test_fp32_arnoldi_steps_follow_the_fp64_ones(dims):
                                     n_cycles=1, mr_iters=2, block_dims=(4, 4, 4, 4), x_in=False, max_iters=10, gauge_tag=1)
         assert rep["iters"] == 10
     assert rel_err(host(x["defect_correction"]), host(x["flexible"])) < 1e-4
+
+
+@pytest.mark.parametrize("storage,bd", [("bf16", (4, 4, 4, 4)), ("f16", (4, 4, 4, 4)), ("bf16", (2, 2, 2, 2))])
+def test_flexible_solve_with_a_16_bit_smoother(storage, bd):
+    # the FP64 operator on 16-bit vectors
+    dims, kappa, mu, csw = (8, 8, 8, 8), 0.15, 0.01, 1.0
+    U, b = synth.gauge_field(dims, 0.4, seed=98), synth.gaussian_spinor(dims, 1, seed=198)
+    announce(f"flexible solve, {storage} smoother, blocks {bd}")
+    x = dev(np.zeros_like(b))
+    rc, rep = tm.tm_fgmres_solve(dims, dev(U), dev(b), x, kappa, [mu], csw, TOL, storage=storage, form="flexible",
+                                 restart=20, n_cycles=3, mr_iters=4, block_dims=bd)
+    assert rc == 0 and rep["converged"] == 1, rep
+    op = oracle.Operator(dims, U, oracle.kappa_to_m(kappa), mu, csw)
+    r = b[0].ravel() - op.apply(host(x)[0].ravel())
+    assert np.linalg.norm(r) / np.linalg.norm(b) <= TOL * RES_SLACK

@@ -81,3 +81,13 @@ def test_noalloc_refuses_problems_beyond_its_scratch():
     with pytest.raises(tm.TMError) as e:
         tm.tm_sap_smooth_noalloc(dims, U, b[:1], x[:1], 0.15, [0.1], 1.0, (4, 4, 4, 4), 1, 1, storage="f64")
     assert e.value.code == -1
+
+
+# The clover term built from the canonical links, with no staged copy (tm_sap_smooth stages them): boxes of the build
+# cut off by the lattice's end, extents in steps of 3 and of 4.
+@pytest.mark.parametrize("dims,block", [((6, 10, 6, 14), (3, 5, 3, 7)), ((2, 6, 10, 6), (1, 3, 5, 3)), ((10, 2, 6, 14), (5, 1, 3, 7))])
+def test_noalloc_builds_the_clover_term_without_staging(dims, block):
+    announce(f"no-alloc clover build dims={dims} block={block}")
+    a, b, ref = run_both(dims, block, "f64", [0.002], 1, 2, "canonical", 61)
+    assert np.array_equal(a, b)
+    check_close(b[0], ref[0], "sap", "f64", f"no-alloc clover build {dims}")
