@@ -36,6 +36,10 @@
  * pointer's older copy of the same shape in place (no new allocation).
  * tm_finalize() frees everything the library allocated.
  *
+ * Batches: a system's result is the same bits alone and among others, whatever
+ * kernels the number of systems selects (tm_dirac_apply, tm_sap_smooth, the
+ * CG's and FGMRES's steps, the two-level coarse operator).
+ *
  * Streams: all work is enqueued on opts->stream (NULL = the null stream).
  * tm_dirac_apply and tm_sap_smooth return after enqueueing (the caller
  * synchronises); tm_fgmres_solve synchronises once per Arnoldi step to read

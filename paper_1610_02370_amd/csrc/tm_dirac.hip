@@ -43,8 +43,8 @@ __global__ void __launch_bounds__(kThreads) k_dirac(DiracArgs a) {
     Clover<R> A;
     load_clover<R, C>(a.clover, g.V, s, A);
     // FP32 spinors and links: the 8 links of the site's hops (two rows each) are loaded once
-    // for all systems.  The other forms reload them per system: holding them takes the FP64
-    // and the FP16 / BF16 kernels to one wavefront per SIMD, which costs more than the loads.
+    // for all systems.  The FP16 / BF16 forms reload them per system: holding them takes these
+    // kernels to one wavefront per SIMD, which costs more than the loads.
     constexpr bool kHold = std::is_same<Si, float>::value && std::is_same<G, float>::value &&
                            std::is_same<R, float>::value;
     R lr[kHold ? 8 : 1][12];
@@ -242,9 +242,11 @@ __global__ void __launch_bounds__(kThreads) k_dirac_lk(DiracArgs a) {
 // half spinor needs, and both hops of a direction are read before either is used.
 //
 // Measured, with the calls' canonical buffers: 6x10x7x9, 3 systems, 26.6 -> 13.3 us a call; 4^4, 2 systems, 19.6
-// -> 13.2 (7.9 and 6.0 us of it the kernel); 32^3x64, one system, 1170 -> 800, six systems 5060 -> 3980 (before
-// the halved link loads); FP32 in and FP64 out, 32^3x64, two systems, 1740 -> 1056.  Large lattices are bound by
-// the neighbours' reads from L2 (about 3 KB per site and system, 8 to 9 TB/s).
+// -> 13.2 (7.9 and 6.0 us of it the kernel); 32^3x64, one, two and twelve systems 1150 -> 790, 1914 -> 1335 and
+// 9900 -> 6970.  FP32 in and FP64 out (any number of systems: the halved reads leave nothing to the one-lane
+// kernel), 32^3x64, 2 / 3 / 6 / 12 systems 1736 / 2471 / 4872 / 9810 -> 1068 / 1509 / 2885 / 5515; 24^4 in 4^3x2 tiles, 12
+// systems 1666 -> 817, BF16 in 1288 -> 725.  Large lattices are bound by the neighbours' reads from L2 (about 3 KB
+// per site and system, 8 to 9 TB/s).
 
 // The canonical layout as a field (FieldOf, tm_pair.h, is the internal one).
 struct Canonical {

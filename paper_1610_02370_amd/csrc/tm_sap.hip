@@ -1388,7 +1388,7 @@ hipError_t run(const SapArgs& args, hipStream_t st) {
         }
     }
     if constexpr (sizeof(R) == 8) {
-        // FP64: one workgroup per CU either way (registers), so the block's links fit in LDS
+        // FP64: registers leave one wavefront per SIMD either way, so the block's links fit in LDS
         // beside the exchange buffer for blocks of up to 256 sites
         const size_t lds_lc = lds + (size_t)48 * nt * sizeof(R);
         if (nt <= 256 && lds_lc <= (size_t)max_lds) {

@@ -311,11 +311,11 @@ enum { kFromZero = 0, kHaloOnly = 1, kFull = 2 };
 // ---------------------------------------------------------------------------
 // FP64 half-sweep: 512 threads per block, two wavefronts per SIMD, one
 // workgroup per compute unit (146 KiB of LDS: links 96, exchange 50).
-// 32^3x64, one system: 760 us per half-sweep against 1176 with one lane per
-// site (376 bytes per lane of scratch, one wavefront per SIMD).  75 us of it per
-// MR step (4.7 us per block, 2 wavefronts x 1084 vector instructions per SIMD);
-// the other 460 us read 516 KB per block, which no second workgroup overlaps:
-// 2.1 GB per half-sweep, 4.6 TB/s while it lasts.
+// 32^3x64, one system: 770 us per half-sweep (825 in bench.py's sweeps) against
+// 1176 with one lane per site (376 bytes per lane of scratch, one wavefront per
+// SIMD).  75 us of it per MR step (4.7 us per block, 2 wavefronts x 1084 vector
+// instructions per SIMD); the other 470 us read 516 KB per block, which no second
+// workgroup overlaps: 2.1 GB per half-sweep, 4.5 TB/s while it lasts.
 constexpr int kPlain = 2 * kSites;
 
 template <class S, class G, class C, class R, int MODE>
@@ -436,7 +436,7 @@ __global__ void __launch_bounds__(kPlain) __attribute__((amdgpu_waves_per_eu(2, 
 //   e_e = D_ee^-1 (r_e - D_eo e_o).
 // The odd site's clover stays in registers, the even site's inverse through a
 // system's MR steps.  75 KiB of LDS in FP32: two workgroups per compute unit.
-// 32^3x64, +-mu in FP32: 860 us per half-sweep against 3690 with one lane per
+// 32^3x64, +-mu in FP32: 890 us per half-sweep against 3690 with one lane per
 // site; bound by vector issue (an MR step is 2100 instructions per wavefront, a
 // fifth of them rebuilding third link rows).  Putting the links' reads, the
 // first system's and the clover's in flight together, as the FP64 kernel does,
