@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(kThreads) k_dirac(DiracArgs a) {
     }
 }
 
-// FP64, one lane per site, for several systems in the internal layout.  STAGED (4^4 tiles, one per workgroup): the
+// FP64, one lane per site, in the internal layout, mostly for several systems.  STAGED (4^4 tiles, one per workgroup): the
 // workgroup stages its tile's own links (two rows each, 96 KiB) in LDS once, and every system takes its
 // forward links there; on other tiles they too come from memory per system.  The backward links U_mu(x - mu) stay loads from memory: inside the tile they are the
 // links just staged, still in L2, and read from LDS as well they made the compiler spill a kilobyte per lane.
@@ -534,9 +534,13 @@ hipError_t launch_dirac(const DiracArgs& a, Prec in_p, Prec out_p, Prec link_p, 
         // 2 / 6 / 12 systems: 16^4 (256 workgroups) 37 / 83 / 162 us against 34 / 92 / 191, 18^3x14 (319) 54 / 135 / 275
         // against 40 / 107 / 230, 18^4 (411) 59 / 153 / 309 against 53 / 156 / 330, 20x22^2x20 (757) 105 / 295 / 573
         // against 117 / 350 / 672, 30^4 474 / 1167 / 2306 against 532 / 1480 / 2816.
-        const bool full = nwg >= (unsigned)kCUs && 4 * nwg >= 3 * kCUs * rounds;
-        if (in_p == P_F64 && a.nsys > 1 &&
-            (is44 ? a.g.V * a.nsys > kSplitSites : full && (nwg >= 640 || a.nsys >= 6))) {
+        // One system gains nothing from the shared clover and takes it from 896 workgroups on with rounds 7/8 full: 20x22x24x26
+        // (1073) 106 us against 103, 22^4 (916) 87 against 92, 30^4 314 against 320, 34^4 502 against 526.
+        const unsigned slots = kCUs * rounds;
+        const bool one_lane = is44            ? a.nsys > 1 && a.g.V * a.nsys > kSplitSites
+                              : a.nsys == 1 ? nwg >= 896 && 8 * nwg >= 7 * slots
+                                            : nwg >= kCUs && 4 * nwg >= 3 * slots && (nwg >= 640 || a.nsys >= 6);
+        if (in_p == P_F64 && one_lane) {
             DiracArgs t = a;
             t.sys_tile = pick_sys_tile(nwg, a.nsys, kCUs, 0.4, true);
             const dim3 grid(nwg, (unsigned)((a.nsys + t.sys_tile - 1) / t.sys_tile));
