@@ -87,6 +87,11 @@ __device__ inline void agg_group(int b, int G, long long nc, int& j, int& grp) {
 // `on` marks the threads that hold a site).  Per site and test vector the 4 S partial sums (two spin halves,
 // re / im, per field) of 16 / S test vectors at a time go through one wave-level transpose sum; the wave sums
 // meet in LDS ([waves][chunks][64]).  Field k's coefficients go to out + k * k_stride for k < ns.
+// S = 1 sums inside the branch that loads: summed after it, the loads of all 16 vectors were held at once in the
+// 128 registers of a 1024-thread workgroup, 1.2 KB per lane of it in scratch memory.  24^4 with 6x4^3 aggregates, 16
+// vectors, 12 systems: 3.22 ms, 0.46 now; the block-diagonal stencil there 8.4 ms, 1.43 now.  S > 1 holds four
+// vectors at once and sums after the branch: inside it, 12^4 with 3^4 aggregates, 9 vectors and 12 systems took
+// 0.907 ms a call instead of 0.895.
 template <int S>
 __device__ inline void restrict_sums(const MgArgs& m, const Spinor<float> (&xv)[S], long long s, bool on, int ns,
                                      float* red, float2* out, size_t k_stride) {
@@ -99,26 +104,33 @@ __device__ inline void restrict_sums(const MgArgs& m, const Spinor<float> (&xv)[
         for (int ii = 0; ii < PER; ++ii) {
             const int i = c * PER + ii;
             Spinor<float> p;
-            if (on && i < nv)
+            const auto sums = [&] {
+#pragma unroll
+                for (int k = 0; k < S; ++k) {
+                    float d[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int q = 0; q < 12; ++q) {
+                        const int h = q < 6 ? 0 : 2;
+                        // one product per statement: each becomes one fused multiply-add
+                        d[h] = d[h] + p.v[q].re * xv[k].v[q].re;
+                        d[h] = d[h] + p.v[q].im * xv[k].v[q].im;
+                        d[h + 1] = d[h + 1] + p.v[q].re * xv[k].v[q].im;
+                        d[h + 1] = d[h + 1] - p.v[q].im * xv[k].v[q].re;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[(ii * S + k) * 4 + e] = d[e];
+                }
+            };
+            if (on && i < nv) {
                 load_spinor<float, float>(field(m.P, m.P_stride, i), nullptr, m.g.V, s, p);
-            else
+                if (S == 1) sums();
+            } else {
 #pragma unroll
                 for (int q = 0; q < 12; ++q) p.v[q] = cmk(0.f, 0.f);
 #pragma unroll
-            for (int k = 0; k < S; ++k) {
-                float d[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int q = 0; q < 12; ++q) {
-                    const int h = q < 6 ? 0 : 2;
-                    // one product per statement: each becomes one fused multiply-add
-                    d[h] = d[h] + p.v[q].re * xv[k].v[q].re;
-                    d[h] = d[h] + p.v[q].im * xv[k].v[q].im;
-                    d[h + 1] = d[h + 1] + p.v[q].re * xv[k].v[q].im;
-                    d[h + 1] = d[h + 1] - p.v[q].im * xv[k].v[q].re;
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[(ii * S + k) * 4 + e] = d[e];
+                for (int e = 0; e < 4 * S; ++e) v[ii * S * 4 + e] = 0.f;
             }
+            if (S > 1) sums();
         }
         red[(w * nch + c) * 64 + lane] = transpose_sum64(v);
     }

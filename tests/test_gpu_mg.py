@@ -94,6 +94,24 @@ def test_restrict_prolong(built):
         assert rel_err(e[k], o.prolong(cc[k])) < 1e-6
 
 
+def test_ragged_large_aggregates():
+    """288 sites (a half-empty last wavefront) and 17 test vectors (one beyond a group of 16)."""
+    dims, adims, nv = (12, 12, 8, 4), (6, 6, 4, 2), 17
+    U = synth.gauge_field(dims, 0.6, seed=7)
+    v0 = synth.gaussian_spinor(dims, nv, seed=107)
+    announce(f"two-level setup dims={dims} aggregates={adims} n_vec={nv}")
+    g = tm.MG(dims, dev(U), KAPPA, 0.01, CSW, dev(v0), n_vec=nv, block_dims=adims, setup_iters=0)
+    o = oracle.MG(oracle.Operator(dims, U, oracle.kappa_to_m(KAPPA), 0.01, CSW), adims, nv, setup_iters=0)
+    o.setup(v0)
+    P, Dc = (host(t) for t in g.export())
+    assert np.abs(P - o.P).max() < 1e-5 * np.abs(o.P).max()
+    assert np.abs(Dc - o.Dc).max() < 1e-5 * np.abs(o.Dc).max()
+    r = synth.gaussian_spinor(dims, 2, seed=47)
+    c = host(g.restrict(dev(r)))
+    for k in range(2):
+        assert rel_err(c[k], o.restrict(r[k])) < 1e-5
+
+
 def test_coarse_operator(built):
     dims, U, g, o, op = built
     rng = np.random.default_rng(43)
